@@ -268,6 +268,20 @@ void timed_pair(kv_handle* h, int kernel, hipEvent_t* start, hipEvent_t* stop) {
   *stop = t.stop;
 }
 
+// The cache rewrite: keys and values in one launch, or in one each while their times are recorded.
+void enqueue_rebuild(kv_handle* h, const KvxBatch& b, int max_tnew, hipStream_t st) {
+  if (!h->timing_now || !(h->timing_mask & ((1u << KV_K_REBUILD_K) | (1u << KV_K_REBUILD_V)))) {
+    launch_rebuild(b, max_tnew, true, true, st);
+    return;
+  }
+  record(h, KV_K_REBUILD_K, true, st);
+  launch_rebuild(b, max_tnew, true, false, st);
+  record(h, KV_K_REBUILD_K, false, st);
+  record(h, KV_K_REBUILD_V, true, st);
+  launch_rebuild(b, max_tnew, false, true, st);
+  record(h, KV_K_REBUILD_V, false, st);
+}
+
 }  // namespace
 
 extern "C" {
@@ -536,12 +550,7 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
         record(h, KV_K_SELECT, false, sb);
       }
       if (!rebuild_after) {
-        record(h, KV_K_REBUILD_K, true, sb);
-        launch_rebuild_k(b, max_tnew, sb);
-        record(h, KV_K_REBUILD_K, false, sb);
-        record(h, KV_K_REBUILD_V, true, sb);
-        launch_rebuild_v(b, max_tnew, sb);
-        record(h, KV_K_REBUILD_V, false, sb);
+        enqueue_rebuild(h, b, max_tnew, sb);
       }
     }
     if (h->debug_checks) launch_check_finite(b, st);
@@ -579,12 +588,7 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
       hipStreamWaitEvent(st, h->ev_join, 0);
     }
     if (rebuild_after) {
-      record(h, KV_K_REBUILD_K, true, st);
-      launch_rebuild_k(b, max_tnew, st);
-      record(h, KV_K_REBUILD_K, false, st);
-      record(h, KV_K_REBUILD_V, true, st);
-      launch_rebuild_v(b, max_tnew, st);
-      record(h, KV_K_REBUILD_V, false, st);
+      enqueue_rebuild(h, b, max_tnew, st);
     }
     hipError_t le = hipGetLastError();
     if (le != hipSuccess) return fail(h, KV_E_HIP, "kv_step: launch failed: %s", hipGetErrorString(le));

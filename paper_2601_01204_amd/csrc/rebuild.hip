@@ -220,13 +220,11 @@ __device__ __forceinline__ void load_input16(const void* base, int64_t off, int 
 // its groups did), every other group is rebuilt in place: each thread reads its own row piece before any write,
 // and the group's old scale and zero-point are read before the second barrier and replaced after it.
 template <int B, bool M16, bool SLOTS>
-__global__ __launch_bounds__(256, 8) void rebuild_k_kernel(const KvxBatch b) {
-  const Geometry& g = b.g;
-  const Item it = b.items[blockIdx.z];
+__device__ __forceinline__ void rebuild_k_block(const Geometry& g, const Item& it, int block) {
   const int h = blockIdx.y;
   const int t_c = it.t_c;
   const int t_new = min(t_c + g.n_new, g.budget);
-  const int p0 = blockIdx.x * kTileK;
+  const int p0 = block * kTileK;
   if (p0 >= t_new) return;
   const uint8_t* cur = cache_half(g, it.cache, it.cur);
   uint8_t* nxt = cache_half(g, it.cache, SLOTS ? it.cur : it.cur ^ 1);
@@ -458,15 +456,12 @@ __global__ __launch_bounds__(256, 8) void rebuild_k_kernel(const KvxBatch b) {
 
 // Values and token ids.  The next cache's positions [0, t_new - n) are surviving tokens,
 // whose codes and (s, z) are carried; the last n positions are the new frame, quantised
-// per token over groups of v_group channels.  Two kinds of blocks share the launch: copy
-// blocks (a lane moves 16 bytes of one token's code row of one head, so 1, 2 or 4 lanes
+// per token over groups of v_group channels.  Two kinds of blocks: copy blocks (a lane moves 16 bytes of one token's code row of one head, so 1, 2 or 4 lanes
 // per row, and the row's metadata) and quantise blocks (64 new tokens per block, four
 // lanes per token).
 
 template <int B, bool M16>
-__global__ __launch_bounds__(256) void rebuild_v_kernel(const KvxBatch b, int n_copy_blocks) {
-  const Geometry& g = b.g;
-  const Item it = b.items[blockIdx.z];
+__device__ __forceinline__ void rebuild_v_block(const Geometry& g, const Item& it, int block, int n_copy_blocks) {
   const int h = blockIdx.y;
   const int t_c = it.t_c;
   const int t_new = min(t_c + g.n_new, g.budget);
@@ -478,9 +473,9 @@ __global__ __launch_bounds__(256) void rebuild_v_kernel(const KvxBatch b, int n_
   constexpr int kRow = 8 * B;
   const int ngv = kHeadDim / g.v_group;    // 1 or 2
 
-  if ((int)blockIdx.x < n_copy_blocks) {
+  if (block < n_copy_blocks) {
     constexpr int kLanes = kRow / 16;                      // lanes per row, 16 bytes of codes each
-    const int p = blockIdx.x * (256 / kLanes) + tid / kLanes;
+    const int p = block * (256 / kLanes) + tid / kLanes;
     const int part = tid % kLanes;
     if (p >= t_keep) return;
     const int src = it.prune ? keep[p] : p;
@@ -505,7 +500,7 @@ __global__ __launch_bounds__(256) void rebuild_v_kernel(const KvxBatch b, int n_
   const int levels = (1 << B) - 1;
   const int lanes_per_group = 4 / ngv;     // 4 or 2 lanes share one value group
   const int r = tid >> 2, cb = tid & 3;
-  const int i_new = ((int)blockIdx.x - n_copy_blocks) * kTileK + r;     // token of the new frame
+  const int i_new = (block - n_copy_blocks) * kTileK + r;     // token of the new frame
   const bool active = i_new < g.n_new;     // uniform over each group of 4 lanes
   // destination: behind the survivors, or (slot layout) the slot the selection assigned, the next unused one while filling
   int p = t_keep + i_new;
@@ -558,6 +553,21 @@ __global__ __launch_bounds__(256) void rebuild_v_kernel(const KvxBatch b, int n_
   if (h == 0 && cb == 0) reinterpret_cast<int32_t*>(nxt + g.lay.ids)[p] = it.frame * g.n + i_new;
 }
 
+// Keys and values of one step in one launch.  The key blocks keep the vector pipe busy, the value blocks memory, and
+// neither kind reads what the other writes, so they are dealt out alternately: of the n_k + n_v blocks of a head,
+// block x is a value block where x n_v / (n_k + n_v) steps to the next integer.  What it gives is a launch: 24 layers
+// of 782 tokens at a budget of 2048, one call each, 2017 -> 1852 us; eight caches of 4096 in the slot layout 283 -> 275
+// us; 24 caches of 16384 unchanged (2566 -> 2565 us, the key blocks fill the vector pipe either way).
+template <int KB, int VB, bool M16, bool SLOTS>
+__global__ __launch_bounds__(256, 8) void rebuild_kernel(const KvxBatch b, int n_k, int n_v, int n_copy_blocks) {
+  const Geometry& g = b.g;
+  const Item it = b.items[blockIdx.z];
+  const uint32_t tot = (uint32_t)(n_k + n_v), x = blockIdx.x;
+  const int v = (int)(x * (uint32_t)n_v / tot);                    // value blocks before this one
+  if ((int)((x + 1) * (uint32_t)n_v / tot) > v) rebuild_v_block<VB, M16>(g, it, v, n_copy_blocks);
+  else rebuild_k_block<KB, M16, SLOTS>(g, it, (int)x - v);
+}
+
 // Uncompressed baseline: append the frame's K and V as bf16 rows [H][t_cap][64].
 __global__ __launch_bounds__(256) void append_bf16_kernel(const KvxBatch b) {
   const Geometry& g = b.g;
@@ -594,51 +604,26 @@ __global__ __launch_bounds__(256) void append_bf16_kernel(const KvxBatch b) {
   if (h == 0 && c8 == 0) reinterpret_cast<int32_t*>(base + g.lay.ids)[it.t_c + i] = it.frame * g.n + i;
 }
 
-void launch_rebuild_k(const KvxBatch& b, int max_tnew, hipStream_t st) {
-  dim3 grid((max_tnew + kTileK - 1) / kTileK, b.g.H, b.n_items);
-#define KVX_RK(B, M, S) hipLaunchKernelGGL((rebuild_k_kernel<B, M, S>), grid, dim3(256), 0, st, b)
-  if (b.g.slots) {
-    if (b.g.meta16) {
-      if (b.g.k_bits == 2) KVX_RK(2, true, true); else KVX_RK(4, true, true);
-    } else {
-      switch (b.g.k_bits) {
-        case 2: KVX_RK(2, false, true); break;
-        case 4: KVX_RK(4, false, true); break;
-        default: KVX_RK(8, false, true); break;
-      }
-    }
-    return;
-  }
-  if (b.g.meta16) {
-    if (b.g.k_bits == 2) KVX_RK(2, true, false); else KVX_RK(4, true, false);
-    return;
-  }
-  switch (b.g.k_bits) {
-    case 2: KVX_RK(2, false, false); break;
-    case 4: KVX_RK(4, false, false); break;
-    default: KVX_RK(8, false, false); break;
-  }
-#undef KVX_RK
-}
-
-void launch_rebuild_v(const KvxBatch& b, int max_tnew, hipStream_t st) {
-  const int rows_per_block = 256 / (b.g.v_bits / 2);           // 16 bytes of codes per lane
+void launch_rebuild(const KvxBatch& b, int max_tnew, bool keys, bool values, hipStream_t st) {
+  const Geometry& g = b.g;
+  const int rows_per_block = 256 / (g.v_bits / 2);           // 16 bytes of codes per lane
   // the slot layout never moves a survivor: only the call's tokens are written
-  const int n_copy_blocks = b.g.slots ? 0 : (std::max(max_tnew - b.g.n_new, 0) + rows_per_block - 1) / rows_per_block;
-  dim3 grid(n_copy_blocks + (b.g.n_new + kTileK - 1) / kTileK, b.g.H, b.n_items);
-  if (b.g.meta16) {
-    switch (b.g.v_bits) {
-      case 2: hipLaunchKernelGGL((rebuild_v_kernel<2, true>), grid, dim3(256), 0, st, b, n_copy_blocks); break;
-      case 4: hipLaunchKernelGGL((rebuild_v_kernel<4, true>), grid, dim3(256), 0, st, b, n_copy_blocks); break;
-      default: hipLaunchKernelGGL((rebuild_v_kernel<8, true>), grid, dim3(256), 0, st, b, n_copy_blocks); break;
-    }
-    return;
+  const int n_copy = g.slots ? 0 : (std::max(max_tnew - g.n_new, 0) + rows_per_block - 1) / rows_per_block;
+  const int n_k = keys ? (max_tnew + kTileK - 1) / kTileK : 0;
+  const int n_v = values ? n_copy + (g.n_new + kTileK - 1) / kTileK : 0;
+  const dim3 grid(n_k + n_v, g.H, b.n_items);
+#define KVX_RB(K, V)                                                                                                      \
+  if (g.k_bits == K && g.v_bits == V) {                                                                                   \
+    if constexpr (K != 8) {                                                                                               \
+      if (g.meta16 && g.slots) hipLaunchKernelGGL((rebuild_kernel<K, V, true, true>), grid, dim3(256), 0, st, b, n_k, n_v, n_copy);   \
+      else if (g.meta16) hipLaunchKernelGGL((rebuild_kernel<K, V, true, false>), grid, dim3(256), 0, st, b, n_k, n_v, n_copy);        \
+    }                                                                                                                     \
+    if (!g.meta16 && g.slots) hipLaunchKernelGGL((rebuild_kernel<K, V, false, true>), grid, dim3(256), 0, st, b, n_k, n_v, n_copy);   \
+    else if (!g.meta16) hipLaunchKernelGGL((rebuild_kernel<K, V, false, false>), grid, dim3(256), 0, st, b, n_k, n_v, n_copy);        \
+    return;                                                                                                               \
   }
-  switch (b.g.v_bits) {
-    case 2: hipLaunchKernelGGL((rebuild_v_kernel<2, false>), grid, dim3(256), 0, st, b, n_copy_blocks); break;
-    case 4: hipLaunchKernelGGL((rebuild_v_kernel<4, false>), grid, dim3(256), 0, st, b, n_copy_blocks); break;
-    default: hipLaunchKernelGGL((rebuild_v_kernel<8, false>), grid, dim3(256), 0, st, b, n_copy_blocks); break;
-  }
+  KVX_RB(2, 2) KVX_RB(2, 4) KVX_RB(2, 8) KVX_RB(4, 2) KVX_RB(4, 4) KVX_RB(4, 8) KVX_RB(8, 2) KVX_RB(8, 4) KVX_RB(8, 8)
+#undef KVX_RB
 }
 
 void launch_append_bf16(const KvxBatch& b, hipStream_t st) {
