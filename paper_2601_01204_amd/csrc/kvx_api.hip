@@ -345,7 +345,6 @@ int kv_init(const kv_config* cfg, kv_handle** out) {
   off = 0;
   S.qbar = off;   off = align_up(off + (int64_t)g.n_pooled * h->f_max * kHeadDim * 4, 256);
   S.qt = off;     off = align_up(off + kHeadDim * 4, 256);
-  S.dots = off;   off = align_up(off + (unc ? 0 : (int64_t)g.H * g.t_cap * 4), 256);
   S.scores = off; off = align_up(off + (unc ? 0 : (int64_t)g.t_cap * 4), 256);
   S.keys = off;   off = align_up(off + (unc ? 0 : (int64_t)g.t_cap * 4), 256);
   S.keep = off;   off = align_up(off + (unc ? 0 : (int64_t)g.t_cap * 4), 256);
@@ -546,7 +545,7 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
         launch_score(b, max_tc, sb);
         record(h, KV_K_SCORE, false, sb);
         record(h, KV_K_SELECT, true, sb);
-        launch_select(b, max_tc, sb);
+        launch_select(b, sb);
         record(h, KV_K_SELECT, false, sb);
       }
       if (!rebuild_after) {

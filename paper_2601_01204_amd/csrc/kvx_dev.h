@@ -42,7 +42,6 @@ struct CacheLayout {
 struct ScratchLayout {
   int64_t qbar;       // [n_pooled][64] float: head-mean pooled query rows
   int64_t qt;         // [64] float: mean of the pooled rows
-  int64_t dots;       // [H][t_cap] float: per-head q~ . K~
   int64_t scores;     // [t_cap] float: importance score of middle tokens (index = cache position - n)
   int64_t keys;       // [t_cap] uint32: order-preserving image of the scores
   int64_t keep;       // [t_cap] int32: kept positions, ascending
@@ -123,7 +122,7 @@ void launch_attention16(const KvxBatch& b, hipStream_t st, hipEvent_t ev_start =
 void launch_combine(const KvxBatch& b, hipStream_t st);
 void launch_pool(const KvxBatch& b, hipStream_t st);
 void launch_score(const KvxBatch& b, int max_tc, hipStream_t st);
-void launch_select(const KvxBatch& b, int max_tc, hipStream_t st);
+void launch_select(const KvxBatch& b, hipStream_t st);
 void launch_rebuild(const KvxBatch& b, int max_tnew, bool keys, bool values, hipStream_t st);
 void launch_append_bf16(const KvxBatch& b, hipStream_t st);
 void launch_check_finite(const KvxBatch& b, hipStream_t st);

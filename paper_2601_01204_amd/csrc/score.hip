@@ -10,6 +10,11 @@
 
 namespace kvx {
 
+__device__ __forceinline__ uint32_t order_key(float x) {
+  const uint32_t u = __float_as_uint(x);
+  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
 // Eq. 2-3: one block per pooled row, eight lanes per head, eight channels per lane.  Per
 // (head, channel): add the row's tokens in ascending order starting from the first, divide
 // by the group size; then per channel add heads 0..H-1 in order starting from zero, divide
@@ -147,80 +152,112 @@ __device__ __forceinline__ void octet_as_floats(const uint32_t* w, int o, float 
 // Per head and middle token: D[h, j] = sum over channels of q~[c] K~[h, j, c], K~ = s (code - z) (Eq. 10), evaluated
 // with the per-group factors pulled out of the per-token work: a = q~[c] * s[c] and b = -float(z[c]) * a once per
 // (head, key group, channel), p[c] = fma(float(code[c]), a[c], b[c]) per token, then the stride-halving pairwise tree
-// p[c] += p[c + m] for m = 32, 16, ..., 1.  One thread holds one token's 64 channels; a block covers 256 consecutive
-// cache positions of one head, starting behind the first frame (whose tokens are never scored), and stages a and b of
-// the key groups it touches in LDS.
-constexpr int kScoreGroupsMax = 256 / 32 + 1;
+// p[c] += p[c + m] for m = 32, 16, ..., 1.  Then S_j = (D[0, j] + D[1, j] + ... + D[H-1, j]) / H, heads added in order
+// (Eq. 4-6), and the order-preserving key of the score.
+// A block covers 64 consecutive cache positions of all heads, one wave per head (the waves take turns if there are
+// more heads) and one token per lane, so the dots of a token meet in LDS and never travel through memory.  Blocks start at a
+// multiple of 64 positions, so a wave needs the factors of one key group (two of 32 tokens), which it stages for itself.
+// Against dots through memory and a launch of its own for the head sum: 24 layers of 782 tokens at a budget of 2048, one
+// call each, 1852 -> 1766 us; 24 caches of 16384 in one call unchanged (2498 -> 2501 us a step: vector-bound either way).
+constexpr int kScoreWaves = 16;
+constexpr int kMaxHeads = 64;
 template <int B>
-__global__ __launch_bounds__(256) void score_dots_kernel(const KvxBatch b) {
+__global__ __launch_bounds__(kScoreWaves * 64) void score_kernel(const KvxBatch b) {
   const Geometry& g = b.g;
-  const Item it = b.items[blockIdx.z];
+  const Item it = b.items[blockIdx.y];
   if (!it.prune) return;
-  const int h = blockIdx.y;
-  const int j0 = g.n + blockIdx.x * 256;
+  const int j0 = (g.n / 64 + (int)blockIdx.x) * 64;
   if (j0 >= it.t_c) return;
   const uint8_t* half = cache_half(g, it.cache, it.cur);
+  uint8_t* sc = cache_scratch(g, it.cache);
   constexpr int kRowWords = 2 * B;                 // 64 channels * B bits / 32
-  __shared__ __attribute__((aligned(16))) float s_a[kScoreGroupsMax][kHeadDim];
-  __shared__ __attribute__((aligned(16))) float s_b[kScoreGroupsMax][kHeadDim];
+  __shared__ __attribute__((aligned(16))) float s_a[kScoreWaves][2][kHeadDim];
+  __shared__ __attribute__((aligned(16))) float s_b[kScoreWaves][2][kHeadDim];
+  __shared__ float dots[kMaxHeads][64];
 
-  // the token's code row is requested first, so that its latency runs beside the staging of the group factors
-  const int j = j0 + threadIdx.x;
-  uint32_t w[kRowWords];
-  {
-    const int jl = min(j, it.t_c - 1);
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(half + g.lay.k_codes + ((int64_t)h * g.t_cap + jl) * (8 * B));
-#pragma unroll
-    for (int i = 0; i < kRowWords; ++i) w[i] = src[i];
-  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
+  const int j = j0 + lane;
+  const int jl = min(j, it.t_c - 1);
   const int k_shift = g.k_group == 64 ? 6 : 5;      // groups of 64 or 32 tokens
-  const int grp0 = j0 >> k_shift;
-  const int groups_in_block = ((min(j0 + 255, it.t_c - 1)) >> k_shift) - grp0 + 1;      // <= 5 or 9
-  const float* qt = reinterpret_cast<const float*>(cache_scratch(g, it.cache) + g.sl.qt);
-  for (int i = threadIdx.x; i < groups_in_block * kHeadDim; i += 256) {
-    const int gi = i >> 6, c = i & 63;
-    const int grp = grp0 + gi;
-    float sv, zf;
-    if (g.meta16) {
-      // halves: logit-domain scale a16 (s = a16 * fp32(1 / scale_log2)) and 1024 + z, channels of an octet in the order 0 4 1 5 2 6 3 7
-      const int64_t moff = ((int64_t)h * g.g_cap + grp) * kHeadDim + meta16_pos(c);
-      sv = (float)__builtin_bit_cast(_Float16, reinterpret_cast<const uint16_t*>(half + g.lay.k_scale)[moff]) * g.inv_scale_log2;
-      zf = (float)__builtin_bit_cast(_Float16, reinterpret_cast<const uint16_t*>(half + g.lay.k_zero)[moff]) - 1024.0f;
-    } else {
-      const int64_t moff = ((int64_t)h * g.g_cap + grp) * kHeadDim + c;
-      sv = reinterpret_cast<const float*>(half + g.lay.k_scale)[moff];
-      zf = (float)reinterpret_cast<const int32_t*>(half + g.lay.k_zero)[moff];
+  const int gi = k_shift == 6 ? 0 : lane >> 5;      // the lane's token's group within the block
+  const float qc = reinterpret_cast<const float*>(sc + g.sl.qt)[lane];
+  for (int h = wave; h < g.H; h += n_waves) {
+    // the token's code row is requested first, so that its latency runs beside the staging of the group factors
+    uint32_t w[kRowWords];
+    {
+      const uint32_t* src = reinterpret_cast<const uint32_t*>(half + g.lay.k_codes + ((int64_t)h * g.t_cap + jl) * (8 * B));
+#pragma unroll
+      for (int i = 0; i < kRowWords; ++i) w[i] = src[i];
     }
-    const float a = qt[c] * sv;
-    s_a[gi][c] = a;
-    s_b[gi][c] = (-zf) * a;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (q == 1 && k_shift == 6) break;
+      // (a group past the cache's end lies inside the buffer; its factors are not used)
+      const int grp = (j0 >> k_shift) + q;
+      float sv, zf;
+      if (g.meta16) {
+        // halves: logit-domain scale a16 (s = a16 * fp32(1 / scale_log2)) and 1024 + z, channels of an octet in the order 0 4 1 5 2 6 3 7
+        const int64_t moff = ((int64_t)h * g.g_cap + grp) * kHeadDim + meta16_pos(lane);
+        sv = (float)__builtin_bit_cast(_Float16, reinterpret_cast<const uint16_t*>(half + g.lay.k_scale)[moff]) * g.inv_scale_log2;
+        zf = (float)__builtin_bit_cast(_Float16, reinterpret_cast<const uint16_t*>(half + g.lay.k_zero)[moff]) - 1024.0f;
+      } else {
+        const int64_t moff = ((int64_t)h * g.g_cap + grp) * kHeadDim + lane;
+        sv = reinterpret_cast<const float*>(half + g.lay.k_scale)[moff];
+        zf = (float)reinterpret_cast<const int32_t*>(half + g.lay.k_zero)[moff];
+      }
+      const float a = qc * sv;
+      s_a[wave][q][lane] = a;
+      s_b[wave][q][lane] = (-zf) * a;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // the factors cross lanes of this wave only
+    __builtin_amdgcn_wave_barrier();
+
+    // The tree's upper levels octet by octet: m = 32 adds octet o + 4 to octet o, m = 16 octet 2 to 0 and 3 to 1, m = 8
+    // octet 1 to 0.  The same additions in an order that keeps few octets at a time in registers.
+    auto octet = [&](int o, float (&x)[8]) __attribute__((always_inline)) {
+      float f[8];
+      octet_as_floats<B>(w, o, f);
+      const float4 a0 = *reinterpret_cast<const float4*>(&s_a[wave][gi][8 * o]), a1 = *reinterpret_cast<const float4*>(&s_a[wave][gi][8 * o + 4]);
+      const float4 b0 = *reinterpret_cast<const float4*>(&s_b[wave][gi][8 * o]), b1 = *reinterpret_cast<const float4*>(&s_b[wave][gi][8 * o + 4]);
+      const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w}, c[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = __builtin_fmaf(f[e], a[e], c[e]);
+    };
+    float p[8], p1[8];
+#pragma unroll
+    for (int o = 0; o < 4; ++o) {
+      const int lo = ((o & 1) << 1) | (o >> 1);      // octets 0, 2, 1, 3
+      float x[8], y[8];
+      octet(lo, x);
+      octet(lo + 4, y);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float v = x[e] + y[e];
+        if (o == 0) p[e] = v;
+        else if (o == 1) p[e] = p[e] + v;
+        else if (o == 2) p1[e] = v;
+        else p1[e] = p1[e] + v;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) p[e] = p[e] + p1[e];
+#pragma unroll
+    for (int m = 4; m >= 1; m >>= 1) {
+#pragma unroll
+      for (int c = 0; c < m; ++c) p[c] = p[c] + p[c + m];
+    }
+    dots[h][lane] = p[0];
+    __builtin_amdgcn_wave_barrier();
   }
   __syncthreads();
-
-  if (j >= it.t_c) return;
-  const int gi = (j >> k_shift) - grp0;
-  float p[kHeadDim];
-#pragma unroll
-  for (int o = 0; o < 8; ++o) {
-    float f[8];
-    octet_as_floats<B>(w, o, f);
-    const float4 a0 = *reinterpret_cast<const float4*>(&s_a[gi][8 * o]), a1 = *reinterpret_cast<const float4*>(&s_a[gi][8 * o + 4]);
-    const float4 b0 = *reinterpret_cast<const float4*>(&s_b[gi][8 * o]), b1 = *reinterpret_cast<const float4*>(&s_b[gi][8 * o + 4]);
-    p[8 * o + 0] = __builtin_fmaf(f[0], a0.x, b0.x);
-    p[8 * o + 1] = __builtin_fmaf(f[1], a0.y, b0.y);
-    p[8 * o + 2] = __builtin_fmaf(f[2], a0.z, b0.z);
-    p[8 * o + 3] = __builtin_fmaf(f[3], a0.w, b0.w);
-    p[8 * o + 4] = __builtin_fmaf(f[4], a1.x, b1.x);
-    p[8 * o + 5] = __builtin_fmaf(f[5], a1.y, b1.y);
-    p[8 * o + 6] = __builtin_fmaf(f[6], a1.z, b1.z);
-    p[8 * o + 7] = __builtin_fmaf(f[7], a1.w, b1.w);
+  if (threadIdx.x < 64 && j >= g.n && j < it.t_c) {
+    float acc = dots[0][lane];
+    for (int h = 1; h < g.H; ++h) acc = acc + dots[h][lane];
+    const float s = acc / (float)g.H;
+    reinterpret_cast<float*>(sc + g.sl.scores)[j - g.n] = s;
+    reinterpret_cast<uint32_t*>(sc + g.sl.keys)[j - g.n] = order_key(s);
   }
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-#pragma unroll
-    for (int c = 0; c < m; ++c) p[c] = p[c] + p[c + m];
-  }
-  reinterpret_cast<float*>(cache_scratch(g, it.cache) + g.sl.dots)[(int64_t)h * g.t_cap + j] = p[0];
 }
 
 void launch_pool(const KvxBatch& b, hipStream_t st) {
@@ -229,11 +266,16 @@ void launch_pool(const KvxBatch& b, hipStream_t st) {
 }
 
 void launch_score(const KvxBatch& b, int max_tc, hipStream_t st) {
-  dim3 grid((std::max(max_tc - b.g.n, 1) + 255) / 256, b.g.H, b.n_items);      // the middle tokens: behind the first frame
+  // the middle tokens: behind the first frame, in blocks of 64 positions
+  const dim3 grid(std::max((max_tc + 63) / 64 - b.g.n / 64, 1), b.n_items);
+  // up to a block per compute unit latency counts: all of 16 heads at once.  Beyond, eight waves a block: at about 80
+  // registers a unit holds three such blocks but only one of 16 waves
+  const int waves = grid.x * grid.y <= 256 ? kScoreWaves : kScoreWaves / 2;
+  const dim3 block(64 * std::min(b.g.H, waves));
   switch (b.g.k_bits) {
-    case 2: hipLaunchKernelGGL(score_dots_kernel<2>, grid, dim3(256), 0, st, b); break;
-    case 4: hipLaunchKernelGGL(score_dots_kernel<4>, grid, dim3(256), 0, st, b); break;
-    default: hipLaunchKernelGGL(score_dots_kernel<8>, grid, dim3(256), 0, st, b); break;
+    case 2: hipLaunchKernelGGL(score_kernel<2>, grid, block, 0, st, b); break;
+    case 4: hipLaunchKernelGGL(score_kernel<4>, grid, block, 0, st, b); break;
+    default: hipLaunchKernelGGL(score_kernel<8>, grid, block, 0, st, b); break;
   }
 }
 

@@ -20,11 +20,6 @@ constexpr int kSelThreads = 1024;
 constexpr int kSelPerThread = 32;                              // keys held in registers per thread
 constexpr int kSelMaxM = kSelThreads * kSelPerThread;          // 32768 middle tokens
 
-__device__ __forceinline__ uint32_t order_key(float x) {
-  const uint32_t u = __float_as_uint(x);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
 // Exclusive prefix sum of one int per thread over a 1024-thread block.
 __device__ __forceinline__ int block_scan_excl(int v, int* wave_sums, int& total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -46,34 +41,6 @@ __device__ __forceinline__ int block_scan_excl(int v, int* wave_sums, int& total
   }
   total = tot;
   return base + inc - v;
-}
-
-// S_j = (D[0,j] + D[1,j] + ... + D[H-1,j]) / H for the middle tokens, heads added in order
-// (Eq. 4-6), and the order-preserving key of each score.  One thread per token, the H
-// loads of a token independent of each other.
-__global__ __launch_bounds__(256) void score_sum_kernel(const KvxBatch b) {
-  const Geometry& g = b.g;
-  const Item it = b.items[blockIdx.y];
-  if (!it.prune) return;
-  const int n = g.n, H = g.H;
-  const int M = it.t_c - n;
-  const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= M) return;
-  uint8_t* sc = cache_scratch(g, it.cache);
-  const float* d0 = reinterpret_cast<const float*>(sc + g.sl.dots) + n + i;
-  float acc = d0[0];
-  int h = 1;
-  for (; h + 7 < H; h += 8) {
-    float v[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = d0[(int64_t)(h + k) * g.t_cap];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) acc = acc + v[k];
-  }
-  for (; h < H; ++h) acc = acc + d0[(int64_t)h * g.t_cap];
-  const float s = acc / (float)H;
-  reinterpret_cast<float*>(sc + g.sl.scores)[i] = s;
-  reinterpret_cast<uint32_t*>(sc + g.sl.keys)[i] = order_key(s);
 }
 
 constexpr int kSelBins = 4096;
@@ -233,8 +200,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const KvxBatch b) {
   }
 }
 
-void launch_select(const KvxBatch& b, int max_tc, hipStream_t st) {
-  hipLaunchKernelGGL(score_sum_kernel, dim3((max_tc + 255) / 256, b.n_items), dim3(256), 0, st, b);
+void launch_select(const KvxBatch& b, hipStream_t st) {
   hipLaunchKernelGGL(select_kernel, dim3(b.n_items), dim3(kSelThreads), 0, st, b);
 }
 

@@ -1,0 +1,36 @@
+"""GPU parity of the update chain where its launches change shape: heads shared out over a block's waves,
+launches of more blocks than compute units, frames that end inside a block of 64 positions.  Scores, keep lists,
+codes and metadata are compared bit-for-bit with the oracle (through the C ABI)."""
+import pytest
+
+import synth_inputs as si
+from oracle import xstream_oracle as xo
+from tests import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_heads,n,k_bits,k_group,meta16,slots", [(11, 37, 4, 32, True, False), (17, 64, 2, 64, False, True), (3, 65, 8, 32, False, False)])
+def test_wide_launches(n_heads, n, k_bits, k_group, meta16, slots):
+    """40 caches of 401 positions in one call: more score blocks than compute units."""
+    import torch
+    streams, frames = 40, 402 // n + 2
+    w = si.Workload("wide", n_heads, 64, n, 3, 8, 401, frames, 1, streams, k_bits, k_group, 4, 32, "bf16", 51)
+    h = pu.make_handle(w, n_streams=streams, meta_format=1 if meta16 else 0, layout=1 if slots else 0)
+    checked = (0, 21, 39)
+    caches = {s: xo.OracleCache(pu.oracle_cfg(w, meta16, slots)) for s in checked}
+    sigmas = {s: si.key_channel_scales(w, s, 0) for s in checked}
+    for t in range(frames):
+        refs, dev = {}, {}
+        for s in checked:
+            q, k, v = si.frame_qkv(w, t, s, 0, sigmas[s])
+            refs[s] = caches[s].step(q, k, v)
+            dev[s] = tuple(pu.to_device(a, w) for a in (q, k, v))
+        # the other caches take the frames of a checked one
+        outs = [torch.empty(dev[0][0].shape, dtype=torch.float32, device="cuda:0") for _ in range(streams)]
+        h.step_batched([(s, 0, *dev[s if s in dev else 0], outs[s]) for s in range(streams)])
+        torch.cuda.synchronize()
+        for s in checked:
+            pu.check_output(outs[s].cpu().numpy(), refs[s], f"stream {s} frame {t}")
+            pu.check_state(h.export(s, 0), caches[s], f"stream {s} frame {t}")
+    h.close()
