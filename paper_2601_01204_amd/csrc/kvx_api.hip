@@ -545,7 +545,7 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
         launch_score(b, max_tc, sb);
         record(h, KV_K_SCORE, false, sb);
         record(h, KV_K_SELECT, true, sb);
-        launch_select(b, sb);
+        launch_select(b, max_tc, sb);
         record(h, KV_K_SELECT, false, sb);
       }
       if (!rebuild_after) {

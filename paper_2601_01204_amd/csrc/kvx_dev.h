@@ -122,7 +122,7 @@ void launch_attention16(const KvxBatch& b, hipStream_t st, hipEvent_t ev_start =
 void launch_combine(const KvxBatch& b, hipStream_t st);
 void launch_pool(const KvxBatch& b, hipStream_t st);
 void launch_score(const KvxBatch& b, int max_tc, hipStream_t st);
-void launch_select(const KvxBatch& b, hipStream_t st);
+void launch_select(const KvxBatch& b, int max_tc, hipStream_t st);
 void launch_rebuild(const KvxBatch& b, int max_tnew, bool keys, bool values, hipStream_t st);
 void launch_append_bf16(const KvxBatch& b, hipStream_t st);
 void launch_check_finite(const KvxBatch& b, hipStream_t st);

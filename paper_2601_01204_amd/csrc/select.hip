@@ -4,47 +4,65 @@
 // order-preserving uint32 image of their fp32 bits, equal scores keep the lower
 // position, so the result is unique and bit-exact.
 //
-// One workgroup of 1024 threads per cache.  Each thread keeps its share of the keys in
-// registers (element i of thread t is position t + 1024 i, so the loads coalesce); a
-// 3-pass most-significant-digit-first radix select (12, 10 and 10 bits) over an LDS
-// histogram finds the key of the last token to drop; keep flags go to LDS and a block scan
-// over contiguous chunks compacts the survivors in position order.  The first digit takes
-// sign, exponent and three mantissa bits, so scores of one magnitude still spread over
-// several bins and the LDS atomics of a wave rarely pile onto one address; after it only
-// the keys of one bin remain candidates.
+// One workgroup of 1024 threads per cache, bound by latency: the number of block barriers
+// and the instructions fetched for the first time, not the work per key.  The keys go to
+// LDS once (their first digit is counted on the way) and every later pass is a short loop
+// over them, so the code stays small whatever the cache's length.  A 3-pass
+// most-significant-digit-first radix select (12, 10 and 10 bits, a histogram each, all
+// cleared up front) finds the key of the last token to drop; the first digit takes sign,
+// exponent and three mantissa bits, so scores of one magnitude still spread over several
+// bins and the LDS atomics of a wave rarely pile onto one address.  Then every wave takes a
+// contiguous run of positions, counts its kept and its equal-to-threshold keys by ballots,
+// and after one barrier writes its survivors in position order at the offset the earlier
+// waves' counts give.
 #include "kvx_dev.h"
+
+#include <algorithm>
 
 namespace kvx {
 
 constexpr int kSelThreads = 1024;
-constexpr int kSelPerThread = 32;                              // keys held in registers per thread
-constexpr int kSelMaxM = kSelThreads * kSelPerThread;          // 32768 middle tokens
+constexpr int kSelWaves = kSelThreads / 64;
+constexpr int kSelBins0 = 4096, kSelBins = 1024;       // bins of the first and of the two later digits
 
-// Exclusive prefix sum of one int per thread over a 1024-thread block.
-__device__ __forceinline__ int block_scan_excl(int v, int* wave_sums, int& total) {
+// Of `per` consecutive bins per thread, find the bin that holds the sh[1]-th smallest candidate (counting from 1):
+// that bin is added to the prefix sh[0], sh[1] becomes the rank within it and sh[2] its count.  Ends with a barrier.
+template <int PER>
+__device__ __forceinline__ void find_bin(const int* hist, int shift, int* wave_sums, volatile int* sh) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int inc = v;
+  int c[PER], cnt = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) { c[j] = hist[threadIdx.x * PER + j]; cnt += c[j]; }
+  int inc = cnt;
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     const int t = __shfl_up(inc, d);
     if (lane >= d) inc += t;
   }
-  __syncthreads();                 // wave_sums may still be read from a previous call
   if (lane == 63) wave_sums[wave] = inc;
+  const int rem = sh[1];
+  const uint32_t prefix = (uint32_t)sh[0];
   __syncthreads();
-  int base = 0, tot = 0;
+  int before = inc - cnt;
+  for (int w = 0; w < wave; ++w) before += wave_sums[w];
+  if (before < rem && before + cnt >= rem) {            // exactly one thread
 #pragma unroll
-  for (int w = 0; w < 16; ++w) {
-    const int s = wave_sums[w];
-    if (w < wave) base += s;
-    tot += s;
+    for (int j = 0; j < PER; ++j) {
+      if (before < rem && before + c[j] >= rem) {
+        sh[0] = (int)(prefix | ((uint32_t)(threadIdx.x * PER + j) << shift));
+        sh[1] = rem - before;
+        sh[2] = c[j];
+        before = rem;                                   // no later bin matches
+      } else {
+        before += c[j];
+      }
+    }
   }
-  total = tot;
-  return base + inc - v;
+  __syncthreads();
 }
 
-constexpr int kSelBins = 4096;
-
+// LDS: histograms, then the keys (dynamic, sized for the longest cache of the launch: at most 24.1 KB + 128 KB)
+constexpr int kSelLdsInts = kSelBins0 + 2 * kSelBins;
 __global__ __launch_bounds__(kSelThreads) void select_kernel(const KvxBatch b) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.x];
@@ -59,127 +77,69 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const KvxBatch b) {
   const uint32_t* keys = reinterpret_cast<const uint32_t*>(sc + g.sl.keys);
   int32_t* keep = reinterpret_cast<int32_t*>(sc + g.sl.keep);
   int32_t* sel = reinterpret_cast<int32_t*>(sc + g.sl.sel);
-  const int tid = threadIdx.x;
-  const int used = (M + kSelThreads - 1) / kSelThreads;      // keys per thread actually present (<= kSelPerThread)
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 
-  __shared__ int hist[kSelBins];
-  __shared__ int wave_sums[16];
-  __shared__ uint32_t sh_prefix;
-  __shared__ int sh_remaining;
+  extern __shared__ int lds[];
+  int* hist0 = lds;
+  int* hist1 = lds + kSelBins0;
+  int* hist2 = hist1 + kSelBins;
+  uint32_t* key = reinterpret_cast<uint32_t*>(lds + kSelLdsInts);
+  __shared__ int wave_sums[3][kSelWaves];
+  __shared__ int wave_gt[kSelWaves], wave_eq[kSelWaves];
+  __shared__ int sh[3];                  // prefix (as bits), rank wanted, count of the found bin
   __shared__ int sh_p0;
-  __shared__ int sh_eq;
-  __shared__ uint8_t flags[kSelMaxM];
 
-  uint32_t key[kSelPerThread];
-#pragma unroll
-  for (int k = 0; k < kSelPerThread; ++k) {
-    const int i = tid + k * kSelThreads;
-    key[k] = (k < used && i < M) ? keys[i] : 0u;
-  }
+  for (int i = tid; i < kSelLdsInts; i += kSelThreads) lds[i] = 0;
   if (tid == 0) {
-    sh_prefix = 0u;
-    sh_remaining = n_drop;
+    sh[0] = 0;
+    sh[1] = n_drop;
     sh_p0 = T;
   }
   __syncthreads();
-
   // Key of the n_drop-th smallest element, digit by digit.
-  uint32_t mask = 0u;
-#pragma unroll
-  for (int pass = 0; pass < 3; ++pass) {
-    const int shift = pass == 0 ? 20 : (pass == 1 ? 10 : 0);
-    const int bins = pass == 0 ? 4096 : 1024;
-    for (int i = tid; i < bins; i += kSelThreads) hist[i] = 0;
-    __syncthreads();
-    const uint32_t prefix = sh_prefix;
-#pragma unroll
-    for (int k = 0; k < kSelPerThread; ++k) {
-      if (k < used) {
-        const int i = tid + k * kSelThreads;
-        if (i < M && (key[k] & mask) == prefix) atomicAdd(&hist[(key[k] >> shift) & (uint32_t)(bins - 1)], 1);
-      }
-    }
-    __syncthreads();
-    {
-      // the bin holding the rem-th smallest candidate: each thread owns bins / 1024 consecutive
-      // bins, counts before each thread's bins by a block scan
-      const int per = bins / kSelThreads;                   // 4 or 1
-      int c4[4] = {0, 0, 0, 0};
-      int cnt = 0;
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        if (j < per) { c4[j] = hist[tid * per + j]; cnt += c4[j]; }
-      int tot_unused;
-      int before = block_scan_excl(cnt, wave_sums, tot_unused);
-      const int rem = sh_remaining;
-      __syncthreads();
-      if (before < rem && before + cnt >= rem) {           // exactly one thread
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (j < per) {
-            if (before < rem && before + c4[j] >= rem) {
-              sh_remaining = rem - before;
-              sh_prefix = prefix | ((uint32_t)(tid * per + j) << shift);
-              sh_eq = c4[j];                                // after the last pass: keys equal to the threshold
-              before = rem;                                 // no later bin matches
-            } else {
-              before += c4[j];
-            }
-          }
-        }
-      }
-    }
-    mask |= (uint32_t)(bins - 1) << shift;
-    __syncthreads();
-  }
-  const uint32_t thr = sh_prefix;
-  const int need_eq = sh_remaining;              // equal-keyed tokens to drop (highest positions first)
-  const int total_eq = sh_eq;
-  const int eq_keep = total_eq - need_eq;        // equal-keyed tokens kept: the eq_keep lowest positions
-
-  // Keep flags: 1 = keep, 0 = drop, 2 = equal to the threshold (resolved by position below).
-#pragma unroll
-  for (int k = 0; k < kSelPerThread; ++k) {
-    const int i = tid + k * kSelThreads;
-    if (k < used && i < M) flags[i] = key[k] > thr ? 1 : (key[k] == thr ? (eq_keep == 0 ? 0 : 2) : 0);
+  for (int i = tid; i < M; i += kSelThreads) {
+    const uint32_t k = keys[i];
+    key[i] = k;
+    atomicAdd(&hist0[k >> 20], 1);
   }
   __syncthreads();
-
-  // Contiguous chunk of middle positions per thread, so prefix sums follow position order.
-  const int chunk = (M + kSelThreads - 1) / kSelThreads;
-  const int c0 = min(tid * chunk, M), c1 = min(c0 + chunk, M);
-  int tot;
-  if (eq_keep > 0) {                              // ties straddle the cut: the lowest positions stay
-    int eq_cnt = 0;
-    for (int i = c0; i < c1; ++i) eq_cnt += (flags[i] == 2);
-    int eq_rank = block_scan_excl(eq_cnt, wave_sums, tot);
-    for (int i = c0; i < c1; ++i)
-      if (flags[i] == 2) {
-        flags[i] = eq_rank < eq_keep ? 1 : 0;
-        ++eq_rank;
-      }
+  find_bin<kSelBins0 / kSelThreads>(hist0, 20, wave_sums[0], sh);
+  const uint32_t top = (uint32_t)sh[0] >> 20;
+  for (int i = tid; i < M; i += kSelThreads) {
+    const uint32_t k = key[i];
+    if (k >> 20 == top) atomicAdd(&hist1[(k >> 10) & (kSelBins - 1)], 1);
   }
-  int kept_cnt = 0;
-  for (int i = c0; i < c1; ++i) kept_cnt += flags[i];
-  int out = block_scan_excl(kept_cnt, wave_sums, tot);
-  int first_drop = T;
+  __syncthreads();
+  find_bin<kSelBins / kSelThreads>(hist1, 10, wave_sums[1], sh);
+  const uint32_t top2 = (uint32_t)sh[0] >> 10;
+  for (int i = tid; i < M; i += kSelThreads) {
+    const uint32_t k = key[i];
+    if (k >> 10 == top2) atomicAdd(&hist2[k & (kSelBins - 1)], 1);
+  }
+  __syncthreads();
+  find_bin<kSelBins / kSelThreads>(hist2, 0, wave_sums[2], sh);
+  const uint32_t thr = (uint32_t)sh[0];
+  const int eq_keep = sh[2] - sh[1];             // equal-keyed tokens kept: the eq_keep lowest positions
+
+  // This wave's run of positions, 64 at a time.
+  const int run = ((M + kSelThreads - 1) / kSelThreads) * 64;
+  const int i0 = min(wave * run, M), i1 = min(i0 + run, M);
+  int gt = 0, eq = 0;
+  for (int i = i0 + lane; i - lane < i1; i += 64) {
+    const uint32_t k = i < i1 ? key[i] : 0u;
+    gt += __popcll(__ballot(i < i1 && k > thr));
+    eq += __popcll(__ballot(i < i1 && k == thr));
+  }
+  if (lane == 0) {
+    wave_gt[wave] = gt;
+    wave_eq[wave] = eq;
+  }
+  // the first frame and the call's own tokens are always kept
+  for (int i = tid; i < n; i += kSelThreads) keep[i] = i;
+  for (int i = tid; i < n_cur; i += kSelThreads) keep[n + k_keep + i] = t_c + i;
   // slot layout: the freed slots in ascending order, then the never-used tail, take the call's tokens in order
   int32_t* newtok = reinterpret_cast<int32_t*>(sc + g.sl.newtok);
   int32_t* assign = reinterpret_cast<int32_t*>(sc + g.sl.assign);
-  for (int i = c0; i < c1; ++i) {
-    if (flags[i]) {
-      keep[n + out] = n + i;
-      if (g.slots) newtok[n + i] = -1;
-      ++out;
-    } else {
-      if (first_drop == T) first_drop = n + i;
-      if (g.slots) {
-        const int d = i - out;             // dropped tokens before this one
-        assign[d] = n + i;
-        newtok[n + i] = d;
-      }
-    }
-  }
   if (g.slots) {
     for (int i = tid; i < n; i += kSelThreads) newtok[i] = -1;
     for (int sl = t_c + tid; sl < g.budget; sl += kSelThreads) {
@@ -188,20 +148,48 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const KvxBatch b) {
       newtok[sl] = d;
     }
   }
+  __syncthreads();
+  int gt_before = 0, eq_before = 0, tot_gt = 0;
+  for (int w = 0; w < kSelWaves; ++w) {
+    if (w < wave) { gt_before += wave_gt[w]; eq_before += wave_eq[w]; }
+    tot_gt += wave_gt[w];
+  }
+  int out = gt_before + min(eq_before, eq_keep);   // survivors in front of this wave's run
+  const uint64_t below = (1ull << lane) - 1ull;
+  int first_drop = T;
+  for (int i = i0 + lane; i - lane < i1; i += 64) {
+    const bool in = i < i1;
+    const uint32_t k = in ? key[i] : 0u;
+    const uint64_t is_eq = __ballot(in && k == thr);
+    const bool kept = in && (k > thr || (k == thr && eq_before + __popcll(is_eq & below) < eq_keep));
+    const uint64_t is_kept = __ballot(kept);
+    const int pos = out + __popcll(is_kept & below);
+    if (kept) {
+      keep[n + pos] = n + i;
+      if (g.slots) newtok[n + i] = -1;
+    } else if (in) {
+      first_drop = min(first_drop, n + i);
+      if (g.slots) {
+        const int d = i - pos;             // dropped tokens before this one
+        assign[d] = n + i;
+        newtok[n + i] = d;
+      }
+    }
+    out += __popcll(is_kept);
+    eq_before += __popcll(is_eq);
+  }
   if (first_drop < T) atomicMin(&sh_p0, first_drop);
-  // the first frame and the call's own tokens are always kept
-  for (int i = tid; i < n; i += kSelThreads) keep[i] = i;
-  for (int i = tid; i < n_cur; i += kSelThreads) keep[n + k_keep + i] = t_c + i;
   __syncthreads();
   if (tid == 0) {
     sel[0] = sh_p0;
     sel[1] = sh_p0 / g.k_group;
-    sel[3] = tot;                                 // survivors among the middle tokens (= k)
+    sel[3] = tot_gt + eq_keep;                    // survivors among the middle tokens (= k)
   }
 }
 
-void launch_select(const KvxBatch& b, hipStream_t st) {
-  hipLaunchKernelGGL(select_kernel, dim3(b.n_items), dim3(kSelThreads), 0, st, b);
+void launch_select(const KvxBatch& b, int max_tc, hipStream_t st) {
+  const size_t lds = (size_t)(kSelLdsInts + std::max(max_tc - b.g.n, 0)) * 4;
+  hipLaunchKernelGGL(select_kernel, dim3(b.n_items), dim3(kSelThreads), lds, st, b);
 }
 
 }  // namespace kvx
