@@ -17,7 +17,14 @@
 // lo = truncated remainder, together 16 significand bits) and S^T takes two bf16 MFMAs
 // (v_mfma_f32_32x32x16_bf16) against the exact bf16 queries.  P and V~ go through the
 // f16 MFMA (v_mfma_f32_32x32x16_f16, 11 significand bits, same rate).  fp32 inputs are
-// split the same way (queries too).
+// split the same way (queries too).  The keys of an uncompressed cache and of a bf16 frame
+// are exact in one bf16 operand as long as the logit factor stays out of it: that kernel
+// (KB = VB = 16) takes one MFMA per step from a zero accumulator and applies the factor and
+// the softmax reference to the 32 x 64 logits by one fused operation each, which saves per
+// tile and wave 256 cycles of matrix work, 8 operand reads and the split in the staging: two
+// layers over their first 24 frames of 1041 tokens 4741 -> 3807 us.  The compressed kernels
+// do not take that path for the frame's own tiles: with both forms in one kernel registers
+// spill (24 x 16384 tokens, 3207 -> 3300 us).
 //
 // Softmax.  The softmax scale times log2(e) is folded into the keys as they are staged,
 // so S^T is already in log2 units.  Each query keeps a reference m and p = 2^(s - m) is
@@ -86,6 +93,7 @@ template <int B> struct Octet;
 template <> struct Octet<2> { typedef uint16_t type; };
 template <> struct Octet<4> { typedef uint32_t type; };
 template <> struct Octet<8> { typedef uint2 type; };
+template <> struct Octet<16> { typedef uint4 type; };      // bf16 rows (not loaded as codes)
 
 template <int B>
 __device__ __forceinline__ int octet_code(const typename Octet<B>::type& w, int e) {
@@ -151,6 +159,11 @@ __device__ __forceinline__ void pin_qk_steps(std::integer_sequence<int, I...>) {
   ((sched_group<0x100, ((I + AHEAD < 8) ? 2 : 0) + (((I & 1) == 0 && (I >> 1) + 2 < 4) ? NB + (F32 ? 1 : 0) : 0)>(),
     sched_group<0x008, (F32 ? 3 : 2) * NB>()), ...);
 }
+// The same for tiles whose keys are one bf16 operand: one K read and one MFMA per step.
+template <int AHEAD, int... I>
+__device__ __forceinline__ void pin_qk1_steps(std::integer_sequence<int, I...>) {
+  ((sched_group<0x100, ((I + AHEAD < 8) ? 1 : 0) + (((I & 1) == 0 && (I >> 1) + 2 < 4) ? 1 : 0)>(), sched_group<0x008, 1>()), ...);
+}
 
 // Linear block id -> (column, query tile), column = (item, split, head).  Workgroups go to the 8 XCDs round-robin by
 // id and each XCD has its own L2, so the query tiles of one column, which read the same K/V codes, get ids that are
@@ -166,6 +179,7 @@ __device__ __forceinline__ void decode_block(int bid, int n_cols, int n_qtiles, 
   col = grp * 8 + (rest - qt * gsize);
 }
 
+// KB = VB = 16: the uncompressed bf16 cache with bf16 inputs (with fp32 inputs it goes through the F32IN kernels).
 template <int KB, int VB, bool F32IN>
 __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch b) {
   const Geometry& g = b.g;
@@ -182,7 +196,8 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
   const int hf = lane >> 5;
 
   __shared__ __attribute__((aligned(16))) uint16_t lds_khi[2][kTileElems];
-  __shared__ __attribute__((aligned(16))) uint16_t lds_klo[2][kTileElems];
+  constexpr bool UNC = KB == 16;
+  __shared__ __attribute__((aligned(16))) uint16_t lds_klo[UNC ? 1 : 2][UNC ? 8 : kTileElems];
   __shared__ __attribute__((aligned(16))) uint16_t lds_v[2][kTileElems];
   constexpr int kQSets = F32IN ? 2 : 1;                   // bf16 queries: one fragment set; fp32: hi and lo
   __shared__ uint4 lds_q[kAttnMaxWaves * kQSets * 4 * 64];   // waves x sets x 4 channel steps x 64 lanes
@@ -197,7 +212,7 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
   const int tile_end = (int)(((int64_t)nt * (split + 1)) / g.n_splits);
 
   const uint8_t* half = cache_half(g, it.cache, it.cur);
-  const bool compressed = !g.uncompressed;
+  const bool compressed = F32IN ? !g.uncompressed : !UNC;
   const float sc = g.scale_log2;
   // Query rows of this wave: block `wave` of the tile's q_blocks 32-row blocks; a wave
   // without rows (fewer than 8 blocks in the tile, or a ragged last tile) only stages.
@@ -337,15 +352,17 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
       bz = bc = bm = ba;
       oc0 = oc1 = om0 = om1 = oa0;
     }
-    raw.c[0] = *reinterpret_cast<const CodeT*>(bc + oc0);
-    raw.c[1] = *reinterpret_cast<const CodeT*>(bc + oc1);
+    if constexpr (!UNC) {
+      raw.c[0] = *reinterpret_cast<const CodeT*>(bc + oc0);
+      raw.c[1] = *reinterpret_cast<const CodeT*>(bc + oc1);
+    }
     raw.a[0] = *reinterpret_cast<const uint4*>(ba + oa0);
     raw.a[1] = *reinterpret_cast<const uint4*>(ba + oa1);
-    if constexpr (ROLE_K || F32IN) {
+    if constexpr ((ROLE_K && !UNC) || F32IN) {
       raw.a[2] = *reinterpret_cast<const uint4*>(bz + oa2);
       raw.a[3] = *reinterpret_cast<const uint4*>(bz + oa3);
     }
-    if constexpr (!ROLE_K) {
+    if constexpr (!ROLE_K && !UNC) {
       raw.m[0] = *reinterpret_cast<const uint2*>(bm + om0);
       raw.m[1] = *reinterpret_cast<const uint2*>(bm + om1);
     }
@@ -369,7 +386,7 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
   // De-quantise / convert the raw registers of `tile` into LDS buffer `buf`.
   auto decode_store = [&](auto rolec, const auto& raw, int tile, int buf) __attribute__((always_inline)) {
     constexpr bool ROLE_K = decltype(rolec)::value;
-    if (tile < ntc && compressed) {
+    if constexpr (!UNC) if (tile < ntc && compressed) {
       // s * (code - z) evaluated as fma(code, s, -z * s): one conversion and one fused
       // operation per value (the result differs from Eq. 10's by a rounding of z * s, far
       // below what the bf16 pair or the f16 value keeps)
@@ -407,10 +424,21 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
         }
         store_v_pair(buf, va, vb);
       }
-    } else {
+      return;
+    }
+    {
       int base_row, limit;
       if (tile < ntc) { base_row = tile * kTileK; limit = t_c; } else { base_row = (tile - ntc) * kTileK; limit = n; }
       const bool ok0 = base_row + key_a < limit, ok1 = base_row + key_a + 1 < limit;
+      if constexpr (ROLE_K && UNC) {
+        // bf16 keys as they are, the logit factor is applied to their logits
+        uint4 r0 = raw.a[0], r1 = raw.a[1];
+        if (!ok0) r0 = make_uint4(0, 0, 0, 0);
+        if (!ok1) r1 = make_uint4(0, 0, 0, 0);
+        *reinterpret_cast<uint4*>(lds_khi[buf] + key_a * kLdsRow + co * 8) = r0;
+        *reinterpret_cast<uint4*>(lds_khi[buf] + (key_a + 1) * kLdsRow + co * 8) = r1;
+        return;
+      }
       float x0[8], x1[8];
       if (F32IN && tile >= ntc) {
         if constexpr (F32IN) {
@@ -456,13 +484,42 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
       const int ks = i >> 1, mb = i & 1;
       const int aoff = (mb * 32 + l32) * kLdsRow + ks * 16 + hf * 8;
       ah[i] = *reinterpret_cast<const bf16x8*>(lds_khi[kbuf] + aoff);
-      al[i] = *reinterpret_cast<const bf16x8*>(lds_klo[kbuf] + aoff);
+      if constexpr (!UNC) al[i] = *reinterpret_cast<const bf16x8*>(lds_klo[kbuf] + aoff);
+    };
+    auto read_k1 = [&](int i) __attribute__((always_inline)) {
+      ah[i] = *reinterpret_cast<const bf16x8*>(lds_khi[kbuf] + ((i & 1) * 32 + l32) * kLdsRow + (i >> 1) * 16 + hf * 8);
     };
     auto read_q = [&](int ks) __attribute__((always_inline)) {
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) qh[ks][nb] = __builtin_bit_cast(bf16x8, qbase[ks * 64]);
       if constexpr (F32IN) ql[ks] = __builtin_bit_cast(bf16x8, qbase[(1 * 4 + ks) * 64]);
     };
+    if constexpr (UNC) {
+      // bf16 keys, unscaled: one MFMA per step
+      f32x16 zero;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+      read_q(0);
+#pragma unroll
+      for (int i = 0; i < kAhead; ++i) read_k1(i);
+      read_q(1);
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int ks = i >> 1, mb = i & 1;
+        if (i + kAhead < 8) read_k1(i + kAhead);
+        if (mb == 0 && ks + 2 < 4) read_q(ks + 2);
+        s[mb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], qh[ks][0], ks == 0 ? zero : s[mb][0], 0, 0, 0);
+      }
+      sched_group<0x100, kAhead + 2>();
+      pin_qk1_steps<kAhead>(std::make_integer_sequence<int, 8>{});
+      __builtin_amdgcn_s_setprio(0);
+      const float nm = -m_ref[0];
+#pragma unroll
+      for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[mb][0][r] = __builtin_fmaf(s[mb][0][r], sc, nm);
+    } else {
     read_q(0);
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) read_k(i);
@@ -485,6 +542,7 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
     sched_group<0x100, 2 * kAhead + 2 * NB + (F32IN ? 2 : 0)>();
     pin_qk_steps<NB, F32IN, kAhead>(std::make_integer_sequence<int, 8>{});
     __builtin_amdgcn_s_setprio(0);
+    }
 
     // keys this lane's query may see in the tile: a cache tile's valid rows (ragged last tile), or the own keys up
     // to the end of the query's frame (frame-wise causal mask; also covers the ragged end of the call's rows)
@@ -730,7 +788,10 @@ static void launch_attn_t(const KvxBatch& b, hipStream_t st, hipEvent_t ev_start
   dim3 grid(g.n_qtiles * g.H * b.n_items * g.n_splits);
   const dim3 block(64 * (g.q_blocks > 8 ? g.q_blocks : 8));      // a wave per query block, at least the 8 staging waves
   // with events: the runtime stamps them at the kernel's own start and end (what a kernel trace reports)
-  if (ev_start) {
+  if constexpr (KB == 16) {
+    if (ev_start) hipExtLaunchKernelGGL((attn_kernel<KB, VB, false>), grid, block, 0, st, ev_start, ev_stop, 0, b);
+    else hipLaunchKernelGGL((attn_kernel<KB, VB, false>), grid, block, 0, st, b);
+  } else if (ev_start) {
     if (g.in_f32) hipExtLaunchKernelGGL((attn_kernel<KB, VB, true>), grid, block, 0, st, ev_start, ev_stop, 0, b);
     else hipExtLaunchKernelGGL((attn_kernel<KB, VB, false>), grid, block, 0, st, ev_start, ev_stop, 0, b);
   } else {
@@ -740,6 +801,8 @@ static void launch_attn_t(const KvxBatch& b, hipStream_t st, hipEvent_t ev_start
 }
 
 void launch_attention(const KvxBatch& b, int /*max_tiles*/, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  if (b.g.uncompressed && !b.g.in_f32) { launch_attn_t<16, 16>(b, st, ev_start, ev_stop); return; }
+  // fp32 inputs over an uncompressed cache: the code widths play no part
   const int kb = b.g.uncompressed ? 4 : b.g.k_bits, vb = b.g.uncompressed ? 4 : b.g.v_bits;
 #define KVX_CASE(K, V) if (kb == K && vb == V) { launch_attn_t<K, V>(b, st, ev_start, ev_stop); return; }
   KVX_CASE(4, 4) KVX_CASE(8, 8) KVX_CASE(2, 4) KVX_CASE(2, 2) KVX_CASE(4, 8) KVX_CASE(8, 4) KVX_CASE(4, 2) KVX_CASE(2, 8) KVX_CASE(8, 2)
