@@ -553,11 +553,27 @@ __device__ __forceinline__ void rebuild_v_block(const Geometry& g, const Item& i
   if (h == 0 && cb == 0) reinterpret_cast<int32_t*>(nxt + g.lay.ids)[p] = it.frame * g.n + i_new;
 }
 
-// Keys and values of one step in one launch.  The key blocks keep the vector pipe busy, the value blocks memory, and
-// neither kind reads what the other writes, so they are dealt out alternately: of the n_k + n_v blocks of a head,
-// block x is a value block where x n_v / (n_k + n_v) steps to the next integer.  What it gives is a launch: 24 layers
-// of 782 tokens at a budget of 2048, one call each, 2017 -> 1852 us; eight caches of 4096 in the slot layout 283 -> 275
-// us; 24 caches of 16384 unchanged (2566 -> 2565 us, the key blocks fill the vector pipe either way).
+// The two on their own, for launches of more than kMergedBlocks blocks and while their times are recorded.
+template <int B, bool M16, bool SLOTS>
+__global__ __launch_bounds__(256, 8) void rebuild_k_kernel(const KvxBatch b) {
+  const Geometry& g = b.g;
+  const Item it = b.items[blockIdx.z];
+  rebuild_k_block<B, M16, SLOTS>(g, it, blockIdx.x);
+}
+template <int B, bool M16>
+__global__ __launch_bounds__(256) void rebuild_v_kernel(const KvxBatch b, int n_copy_blocks) {
+  const Geometry& g = b.g;
+  const Item it = b.items[blockIdx.z];
+  rebuild_v_block<B, M16>(g, it, blockIdx.x, n_copy_blocks);
+}
+
+// Keys and values of one step in one launch.  Neither kind of block reads what the other writes, so they are dealt out
+// alternately: of the n_k + n_v blocks of a head, block x is a value block where x n_v / (n_k + n_v) steps to the next
+// integer.  What it gives is a launch: 24 layers of 782 tokens at a budget of 2048, one call each, 2017 -> 1852 us; eight
+// caches of 4096 in the slot layout 283 -> 275 us.  In a long launch the value blocks stream more slowly than on their
+// own, because each holds the key blocks' 22 KB of LDS: 24 caches of 16384 take 328 us against 231 + 88, 48 of 24576
+// 958 against 666 + 253, so from about 100 us on (kMergedBlocks) the two go separately.
+constexpr int kMergedBlocks = 32768;
 template <int KB, int VB, bool M16, bool SLOTS>
 __global__ __launch_bounds__(256, 8) void rebuild_kernel(const KvxBatch b, int n_k, int n_v, int n_copy_blocks) {
   const Geometry& g = b.g;
@@ -604,6 +620,17 @@ __global__ __launch_bounds__(256) void append_bf16_kernel(const KvxBatch b) {
   if (h == 0 && c8 == 0) reinterpret_cast<int32_t*>(base + g.lay.ids)[it.t_c + i] = it.frame * g.n + i;
 }
 
+template <int KB, int VB, bool M16, bool SLOTS>
+static void launch_rebuild_t(const KvxBatch& b, int n_k, int n_v, int n_copy, hipStream_t st) {
+  const dim3 block(256);
+  if (n_k > 0 && n_v > 0 && (int64_t)(n_k + n_v) * b.g.H * b.n_items <= kMergedBlocks) {
+    hipLaunchKernelGGL((rebuild_kernel<KB, VB, M16, SLOTS>), dim3(n_k + n_v, b.g.H, b.n_items), block, 0, st, b, n_k, n_v, n_copy);
+    return;
+  }
+  if (n_k > 0) hipLaunchKernelGGL((rebuild_k_kernel<KB, M16, SLOTS>), dim3(n_k, b.g.H, b.n_items), block, 0, st, b);
+  if (n_v > 0) hipLaunchKernelGGL((rebuild_v_kernel<VB, M16>), dim3(n_v, b.g.H, b.n_items), block, 0, st, b, n_copy);
+}
+
 void launch_rebuild(const KvxBatch& b, int max_tnew, bool keys, bool values, hipStream_t st) {
   const Geometry& g = b.g;
   const int rows_per_block = 256 / (g.v_bits / 2);           // 16 bytes of codes per lane
@@ -611,16 +638,14 @@ void launch_rebuild(const KvxBatch& b, int max_tnew, bool keys, bool values, hip
   const int n_copy = g.slots ? 0 : (std::max(max_tnew - g.n_new, 0) + rows_per_block - 1) / rows_per_block;
   const int n_k = keys ? (max_tnew + kTileK - 1) / kTileK : 0;
   const int n_v = values ? n_copy + (g.n_new + kTileK - 1) / kTileK : 0;
-  const dim3 grid(n_k + n_v, g.H, b.n_items);
-#define KVX_RB(K, V)                                                                                                      \
-  if (g.k_bits == K && g.v_bits == V) {                                                                                   \
-    if constexpr (K != 8) {                                                                                               \
-      if (g.meta16 && g.slots) hipLaunchKernelGGL((rebuild_kernel<K, V, true, true>), grid, dim3(256), 0, st, b, n_k, n_v, n_copy);   \
-      else if (g.meta16) hipLaunchKernelGGL((rebuild_kernel<K, V, true, false>), grid, dim3(256), 0, st, b, n_k, n_v, n_copy);        \
-    }                                                                                                                     \
-    if (!g.meta16 && g.slots) hipLaunchKernelGGL((rebuild_kernel<K, V, false, true>), grid, dim3(256), 0, st, b, n_k, n_v, n_copy);   \
-    else if (!g.meta16) hipLaunchKernelGGL((rebuild_kernel<K, V, false, false>), grid, dim3(256), 0, st, b, n_k, n_v, n_copy);        \
-    return;                                                                                                               \
+#define KVX_RB(K, V)                                                                                \
+  if (g.k_bits == K && g.v_bits == V) {                                                             \
+    if constexpr (K != 8) {                                                                         \
+      if (g.meta16 && g.slots) return launch_rebuild_t<K, V, true, true>(b, n_k, n_v, n_copy, st);  \
+      if (g.meta16) return launch_rebuild_t<K, V, true, false>(b, n_k, n_v, n_copy, st);            \
+    }                                                                                               \
+    if (g.slots) return launch_rebuild_t<K, V, false, true>(b, n_k, n_v, n_copy, st);               \
+    return launch_rebuild_t<K, V, false, false>(b, n_k, n_v, n_copy, st);                           \
   }
   KVX_RB(2, 2) KVX_RB(2, 4) KVX_RB(2, 8) KVX_RB(4, 2) KVX_RB(4, 4) KVX_RB(4, 8) KVX_RB(8, 2) KVX_RB(8, 4) KVX_RB(8, 8)
 #undef KVX_RB

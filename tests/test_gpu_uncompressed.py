@@ -1,0 +1,37 @@
+"""The uncompressed bf16 cache at the edges of its tiles: frames of one row, around one query block and around one key
+tile, forced key-range splits, logits far apart; against Eq. 1 in 64 bits (through the C ABI).  Probabilities and
+values are rounded to 11 bits on the way (2^-12 each, relative), everything else is exact or fp32, so an output of unit
+RMS is off by a few 2^-12: the bars of parity_util (2e-2 largest, 2e-3 mean) leave room for peaked rows only."""
+import numpy as np
+import pytest
+
+from tests import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,splits,k_scale", [(1, 0, 1.0), (31, 3, 1.0), (33, 0, 4.0), (64, 2, 1.0), (65, 16, 4.0), (385, 0, 1.0)])
+def test_tile_edges(n, splits, k_scale):
+    import torch
+    import paper_2601_01204_amd as kvx
+    H, d, frames = 3, 64, 5
+    rng = np.random.default_rng(60 + n)
+    h = kvx.KvHandle(n_heads=H, tokens_per_frame=n, n_special=0, budget_tokens=frames * n, mode=kvx.KV_UNCOMPRESSED_BF16, max_frames=frames,
+                     out_dtype=kvx.KV_F32)
+    if splits:
+        h.set_option("attention_splits", splits)
+    keys, values = [], []
+    for t in range(frames):
+        q, k, v = (torch.from_numpy(rng.standard_normal((n, H, d)).astype(np.float32) * s).to("cuda:0").to(torch.bfloat16)
+                   for s in (1.0, k_scale, 1.0))
+        out = torch.empty((n, H, d), dtype=torch.float32, device="cuda:0")
+        h.step(q, k, v, out)
+        torch.cuda.synchronize()
+        keys.append(k.double().cpu().numpy())
+        values.append(v.double().cpu().numpy())
+        K, V, Q = np.concatenate(keys), np.concatenate(values), q.double().cpu().numpy()
+        s = np.einsum("qhd,khd->hqk", Q, K) / np.sqrt(d)
+        p = np.exp(s - s.max(-1, keepdims=True))
+        ref = np.einsum("hqk,khd->qhd", p / p.sum(-1, keepdims=True), V)
+        pu.check_output(out.cpu().numpy(), ref, f"n {n} frame {t}")
+    h.close()
