@@ -539,7 +539,7 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     if (!g0.uncompressed) {
       if (any_prune) {
         record(h, KV_K_POOL, true, sb);
-        launch_pool(b, sb);
+        launch_pool(b, max_tc, sb);
         record(h, KV_K_POOL, false, sb);
         record(h, KV_K_SCORE, true, sb);
         launch_score(b, max_tc, sb);

@@ -7,6 +7,7 @@
 #include "kvx_dev.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace kvx {
 
@@ -15,13 +16,18 @@ __device__ __forceinline__ uint32_t order_key(float x) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// Eq. 2-3: one block per pooled row, eight lanes per head, eight channels per lane.  Per
+// Eq. 2-3: one block per pooled row, sixteen lanes per head, four channels per lane.  Per
 // (head, channel): add the row's tokens in ascending order starting from the first, divide
 // by the group size; then per channel add heads 0..H-1 in order starting from zero, divide
 // by H.  A group's tokens are requested sixteen at a time before any is added, so a row
-// costs one memory round trip.
+// costs one memory round trip.  Bound by latency, of which fetching the kernel's code is a
+// good part: rows are addressed from one uniform pointer, the input type is a template
+// argument, and four channels a lane (not eight) halve the code and double the waves.
+// Against eight unrolled channels a lane with 64-bit addresses per token: one cache of 782 or
+// 1041 tokens 11 -> 4.5 us, 24 caches 24 -> 14 us, 48 caches of 1374 tokens 39 -> 26 us.
 constexpr int kPoolBatch = 16;
-__global__ __launch_bounds__(512) void pool_rows_kernel(const KvxBatch b) {
+template <bool F32IN>
+__global__ __launch_bounds__(1024) void pool_rows_kernel(const KvxBatch b) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.y];
   if (!it.prune) return;
@@ -37,46 +43,44 @@ __global__ __launch_bounds__(512) void pool_rows_kernel(const KvxBatch b) {
     e = min(a + g.pool_group, (fr + 1) * g.n);
   }
   __shared__ __attribute__((aligned(16))) float pooled[64][kHeadDim];     // up to 64 heads
-  const int h = threadIdx.x >> 3, c0 = (threadIdx.x & 7) * 8;
+  typedef typename std::conditional<F32IN, float4, uint2>::type Raw;      // four channels as they come
+  constexpr int kElt = F32IN ? 4 : 2;
+  const int h = threadIdx.x >> 4, c0 = (threadIdx.x & 15) * 4;
   if (h < g.H) {
-    float acc[8];
+    const int64_t lane_off = ((int64_t)h * g.head_stride + c0) * kElt, step = g.tok_stride * kElt;
+    float acc[4] = {0.f, 0.f, 0.f, 0.f};
     for (int t0 = a; t0 < e; t0 += kPoolBatch) {
-      float v[kPoolBatch][8];
+      Raw v[kPoolBatch];
+      const uint8_t* p = reinterpret_cast<const uint8_t*>(it.q) + t0 * step;
 #pragma unroll
       for (int k = 0; k < kPoolBatch; ++k) {
-        const int t = min(t0 + k, e - 1);                  // clamped: a repeated token is loaded but not added
-        const int64_t off = (int64_t)t * g.tok_stride + (int64_t)h * g.head_stride + c0;
-        if (g.in_f32) {
-          const float4* q = reinterpret_cast<const float4*>(reinterpret_cast<const float*>(it.q) + off);
-          const float4 x0 = q[0], x1 = q[1];
-          v[k][0] = x0.x; v[k][1] = x0.y; v[k][2] = x0.z; v[k][3] = x0.w;
-          v[k][4] = x1.x; v[k][5] = x1.y; v[k][6] = x1.z; v[k][7] = x1.w;
-        } else {
-          const uint4 x = *reinterpret_cast<const uint4*>(reinterpret_cast<const uint16_t*>(it.q) + off);
-          const uint32_t w[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            v[k][2 * j] = __uint_as_float(w[j] << 16);
-            v[k][2 * j + 1] = __uint_as_float(w[j] & 0xFFFF0000u);
-          }
-        }
+        v[k] = *reinterpret_cast<const Raw*>(p + lane_off);
+        if (t0 + k + 1 < e) p += step;                     // a repeated token is loaded but not added
       }
 #pragma unroll
       for (int k = 0; k < kPoolBatch; ++k) {
         if (t0 + k < e) {
+          float x[4];
+          if constexpr (F32IN) {
+            x[0] = v[k].x; x[1] = v[k].y; x[2] = v[k].z; x[3] = v[k].w;
+          } else {
+            x[0] = __uint_as_float(v[k].x << 16); x[1] = __uint_as_float(v[k].x & 0xFFFF0000u);
+            x[2] = __uint_as_float(v[k].y << 16); x[3] = __uint_as_float(v[k].y & 0xFFFF0000u);
+          }
+          const bool first = k == 0 && t0 == a;
 #pragma unroll
-          for (int j = 0; j < 8; ++j) acc[j] = (t0 + k == a) ? v[k][j] : acc[j] + v[k][j];
+          for (int j = 0; j < 4; ++j) acc[j] = first ? x[j] : acc[j] + x[j];
         }
       }
     }
     const float cnt = (float)(e - a);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) pooled[h][c0 + j] = acc[j] / cnt;
+    *reinterpret_cast<float4*>(&pooled[h][c0]) = make_float4(acc[0] / cnt, acc[1] / cnt, acc[2] / cnt, acc[3] / cnt);
   }
   __syncthreads();
   if (threadIdx.x < 64) {
     const int c = threadIdx.x;
     float acc = 0.f;
+#pragma unroll 4
     for (int hh = 0; hh < g.H; ++hh) acc = acc + pooled[hh][c];
     reinterpret_cast<float*>(cache_scratch(g, it.cache) + g.sl.qbar)[row * kHeadDim + c] = acc / (float)g.H;
   }
@@ -159,9 +163,10 @@ __device__ __forceinline__ void octet_as_floats(const uint32_t* w, int o, float 
 // multiple of 64 positions, so a wave needs the factors of one key group (two of 32 tokens), which it stages for itself.
 // Against dots through memory and a launch of its own for the head sum: 24 layers of 782 tokens at a budget of 2048, one
 // call each, 1852 -> 1766 us; 24 caches of 16384 in one call unchanged (2498 -> 2501 us a step: vector-bound either way).
+// MEAN: the block forms q~ itself, in pool_mean_kernel's order, from the pooled rows (one LDS load of at most 128).
 constexpr int kScoreWaves = 16;
 constexpr int kMaxHeads = 64;
-template <int B>
+template <int B, bool MEAN>
 __global__ __launch_bounds__(kScoreWaves * 64) void score_kernel(const KvxBatch b) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.y];
@@ -180,15 +185,35 @@ __global__ __launch_bounds__(kScoreWaves * 64) void score_kernel(const KvxBatch 
   const int jl = min(j, it.t_c - 1);
   const int k_shift = g.k_group == 64 ? 6 : 5;      // groups of 64 or 32 tokens
   const int gi = k_shift == 6 ? 0 : lane >> 5;      // the lane's token's group within the block
-  const float qc = reinterpret_cast<const float*>(sc + g.sl.qt)[lane];
-  for (int h = wave; h < g.H; h += n_waves) {
-    // the token's code row is requested first, so that its latency runs beside the staging of the group factors
-    uint32_t w[kRowWords];
-    {
-      const uint32_t* src = reinterpret_cast<const uint32_t*>(half + g.lay.k_codes + ((int64_t)h * g.t_cap + jl) * (8 * B));
+  // a head's code row of the lane's token is requested first, so that its latency runs beside the staging of the factors
+  uint32_t w[kRowWords];
+  auto load_row = [&](int h) __attribute__((always_inline)) {
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(half + g.lay.k_codes + ((int64_t)h * g.t_cap + jl) * (8 * B));
 #pragma unroll
-      for (int i = 0; i < kRowWords; ++i) w[i] = src[i];
+    for (int i = 0; i < kRowWords; ++i) w[i] = src[i];
+  };
+  float qc;
+  if constexpr (MEAN) {
+    load_row(wave);
+    __shared__ __attribute__((aligned(16))) float rows[kMeanRows][kHeadDim];
+    __shared__ float s_qt[kHeadDim];
+    const float4* qbar = reinterpret_cast<const float4*>(sc + g.sl.qbar);
+    const int n_rows = g.n_pooled * (g.n_new / g.n);
+    for (int i = threadIdx.x; i < n_rows * 16; i += blockDim.x) reinterpret_cast<float4*>(rows)[i] = qbar[i];
+    __syncthreads();
+    if (wave == 0) {
+      float acc = 0.f;
+#pragma unroll 8
+      for (int r = 0; r < n_rows; ++r) acc = acc + rows[r][lane];
+      s_qt[lane] = acc / (float)n_rows;
     }
+    __syncthreads();
+    qc = s_qt[lane];
+  } else {
+    qc = reinterpret_cast<const float*>(sc + g.sl.qt)[lane];
+  }
+  for (int h = wave; h < g.H; h += n_waves) {
+    if (!MEAN || h != wave) load_row(h);
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       if (q == 1 && k_shift == 6) break;
@@ -260,22 +285,37 @@ __global__ __launch_bounds__(kScoreWaves * 64) void score_kernel(const KvxBatch 
   }
 }
 
-void launch_pool(const KvxBatch& b, hipStream_t st) {
-  hipLaunchKernelGGL(pool_rows_kernel, dim3(b.g.n_pooled * (b.g.n_new / b.g.n), b.n_items), dim3(std::max(64, 8 * b.g.H)), 0, st, b);
-  hipLaunchKernelGGL(pool_mean_kernel, dim3(b.n_items), dim3(1024), 0, st, b);
+// A launch of up to a score block per compute unit is bound by its chain of dependent launches: there every score block
+// forms the row mean for itself (about 1 us) and the mean's launch (4.3 us) falls away.
+static bool mean_in_score(const KvxBatch& b, int score_blocks) {
+  return score_blocks * b.n_items <= 256 && b.g.n_pooled * (b.g.n_new / b.g.n) <= kMeanRows;
+}
+// blocks of 64 positions that hold middle tokens: behind the first frame
+static int score_blocks(const KvxBatch& b, int max_tc) { return std::max((max_tc + 63) / 64 - b.g.n / 64, 1); }
+
+void launch_pool(const KvxBatch& b, int max_tc, hipStream_t st) {
+  const dim3 rows(b.g.n_pooled * (b.g.n_new / b.g.n), b.n_items), block(std::max(64, 16 * b.g.H));
+  if (b.g.in_f32) hipLaunchKernelGGL(pool_rows_kernel<true>, rows, block, 0, st, b);
+  else hipLaunchKernelGGL(pool_rows_kernel<false>, rows, block, 0, st, b);
+  if (!mean_in_score(b, score_blocks(b, max_tc))) hipLaunchKernelGGL(pool_mean_kernel, dim3(b.n_items), dim3(1024), 0, st, b);
 }
 
-void launch_score(const KvxBatch& b, int max_tc, hipStream_t st) {
-  // the middle tokens: behind the first frame, in blocks of 64 positions
-  const dim3 grid(std::max((max_tc + 63) / 64 - b.g.n / 64, 1), b.n_items);
+template <int B>
+static void launch_score_t(const KvxBatch& b, int max_tc, hipStream_t st) {
+  const dim3 grid(score_blocks(b, max_tc), b.n_items);
   // up to a block per compute unit latency counts: all of 16 heads at once.  Beyond, eight waves a block: at about 80
   // registers a unit holds three such blocks but only one of 16 waves
   const int waves = grid.x * grid.y <= 256 ? kScoreWaves : kScoreWaves / 2;
   const dim3 block(64 * std::min(b.g.H, waves));
+  if (mean_in_score(b, grid.x)) hipLaunchKernelGGL((score_kernel<B, true>), grid, block, 0, st, b);
+  else hipLaunchKernelGGL((score_kernel<B, false>), grid, block, 0, st, b);
+}
+
+void launch_score(const KvxBatch& b, int max_tc, hipStream_t st) {
   switch (b.g.k_bits) {
-    case 2: hipLaunchKernelGGL(score_kernel<2>, grid, block, 0, st, b); break;
-    case 4: hipLaunchKernelGGL(score_kernel<4>, grid, block, 0, st, b); break;
-    default: hipLaunchKernelGGL(score_kernel<8>, grid, block, 0, st, b); break;
+    case 2: launch_score_t<2>(b, max_tc, st); break;
+    case 4: launch_score_t<4>(b, max_tc, st); break;
+    default: launch_score_t<8>(b, max_tc, st); break;
   }
 }
 

@@ -4,7 +4,7 @@ namespace kvx {
 void launch_attention(const KvxBatch&, int, hipStream_t, hipEvent_t, hipEvent_t) {}
 void launch_attention16(const KvxBatch&, hipStream_t, hipEvent_t, hipEvent_t) {}
 void launch_combine(const KvxBatch&, hipStream_t) {}
-void launch_pool(const KvxBatch&, hipStream_t) {}
+void launch_pool(const KvxBatch&, int, hipStream_t) {}
 void launch_score(const KvxBatch&, int, hipStream_t) {}
 void launch_select(const KvxBatch&, int, hipStream_t) {}
 void launch_rebuild(const KvxBatch&, int, bool, bool, hipStream_t) {}

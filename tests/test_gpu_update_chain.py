@@ -10,6 +10,13 @@ from tests import parity_util as pu
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("n,pool_group", [(129, 1), (128, 1), (200, 2)])
+def test_pooled_rows_around_one_lds_load(n, pool_group):
+    """129, 128 and 101 pooled rows: the row mean in a launch of its own, and in the scoring blocks up to 128 rows."""
+    w = si.Workload("rows", 2, 64, n, 2, pool_group, 3 * n + 5, 6, 1, 1, 4, 64, 4, 64, "bf16", 52)
+    pu.run_stream(w, 6)
+
+
 @pytest.mark.parametrize("n_heads,n,k_bits,k_group,meta16,slots", [(11, 37, 4, 32, True, False), (17, 64, 2, 64, False, True), (3, 65, 8, 32, False, False)])
 def test_wide_launches(n_heads, n, k_bits, k_group, meta16, slots):
     """40 caches of 401 positions in one call: more score blocks than compute units."""
