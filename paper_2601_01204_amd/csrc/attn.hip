@@ -180,8 +180,8 @@ __device__ __forceinline__ void decode_block(int bid, int n_cols, int n_qtiles, 
 }
 
 // KB = VB = 16: the uncompressed bf16 cache with bf16 inputs (with fp32 inputs it goes through the F32IN kernels).
-template <int KB, int VB, bool F32IN>
-__global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch b) {
+template <int KB, int VB, bool F32IN, int N>
+__global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
   int bid, qt;
   decode_block(blockIdx.x, g.H * g.n_splits * b.n_items, g.n_qtiles, bid, qt);
@@ -738,7 +738,8 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
 }
 
 // Merge the split-KV partials: out = sum_s w_s O_s / sum_s w_s l_s, w_s = 2^(m_s - max m).
-__global__ __launch_bounds__(256) void combine_kernel(const KvxBatch b) {
+template <int N>
+__global__ __launch_bounds__(256) void combine_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.z];
   const int h = blockIdx.y;
@@ -789,14 +790,14 @@ static void launch_attn_t(const KvxBatch& b, hipStream_t st, hipEvent_t ev_start
   const dim3 block(64 * (g.q_blocks > 8 ? g.q_blocks : 8));      // a wave per query block, at least the 8 staging waves
   // with events: the runtime stamps them at the kernel's own start and end (what a kernel trace reports)
   if constexpr (KB == 16) {
-    if (ev_start) hipExtLaunchKernelGGL((attn_kernel<KB, VB, false>), grid, block, 0, st, ev_start, ev_stop, 0, b);
-    else hipLaunchKernelGGL((attn_kernel<KB, VB, false>), grid, block, 0, st, b);
+    if (ev_start) with_batch(b, [&](const auto& bb) { hipExtLaunchKernelGGL((attn_kernel<KB, VB, false, KVX_ITEMS(bb)>), grid, block, 0, st, ev_start, ev_stop, 0, bb); });
+    else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((attn_kernel<KB, VB, false, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
   } else if (ev_start) {
-    if (g.in_f32) hipExtLaunchKernelGGL((attn_kernel<KB, VB, true>), grid, block, 0, st, ev_start, ev_stop, 0, b);
-    else hipExtLaunchKernelGGL((attn_kernel<KB, VB, false>), grid, block, 0, st, ev_start, ev_stop, 0, b);
+    if (g.in_f32) with_batch(b, [&](const auto& bb) { hipExtLaunchKernelGGL((attn_kernel<KB, VB, true, KVX_ITEMS(bb)>), grid, block, 0, st, ev_start, ev_stop, 0, bb); });
+    else with_batch(b, [&](const auto& bb) { hipExtLaunchKernelGGL((attn_kernel<KB, VB, false, KVX_ITEMS(bb)>), grid, block, 0, st, ev_start, ev_stop, 0, bb); });
   } else {
-    if (g.in_f32) hipLaunchKernelGGL((attn_kernel<KB, VB, true>), grid, block, 0, st, b);
-    else hipLaunchKernelGGL((attn_kernel<KB, VB, false>), grid, block, 0, st, b);
+    if (g.in_f32) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((attn_kernel<KB, VB, true, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
+    else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((attn_kernel<KB, VB, false, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
   }
 }
 
@@ -813,7 +814,7 @@ void launch_combine(const KvxBatch& b, hipStream_t st) {
   const Geometry& g = b.g;
   if (g.n_splits <= 1) return;
   dim3 grid((g.n_new + 15) / 16, g.H, b.n_items);
-  hipLaunchKernelGGL(combine_kernel, grid, dim3(256), 0, st, b);
+  with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((combine_kernel<KVX_ITEMS(bb)>), grid, dim3(256), 0, st, bb); });
 }
 
 }  // namespace kvx

@@ -143,8 +143,8 @@ __device__ __forceinline__ void decode_block(int bid, int n_cols, int n_qtiles, 
   col = grp * 8 + (rest - qt * gsize);
 }
 
-template <int KB, int VB>
-__global__ __launch_bounds__(kAttnMaxWaves * 64) void attn16_kernel(const KvxBatch b) {
+template <int KB, int VB, int N>
+__global__ __launch_bounds__(kAttnMaxWaves * 64) void attn16_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
   int bid, qt;
   decode_block(blockIdx.x, g.H * g.n_splits * b.n_items, g.n_qtiles, bid, qt);
@@ -553,8 +553,8 @@ static void launch_t(const KvxBatch& b, hipStream_t st, hipEvent_t ev_start, hip
   const Geometry& g = b.g;
   dim3 grid(g.n_qtiles * g.H * b.n_items * g.n_splits);
   const dim3 block(64 * (g.q_blocks > 8 ? g.q_blocks : 8));      // a wave per query block, at least the 8 staging waves
-  if (ev_start) hipExtLaunchKernelGGL((attn16_kernel<KB, VB>), grid, block, 0, st, ev_start, ev_stop, 0, b);
-  else hipLaunchKernelGGL((attn16_kernel<KB, VB>), grid, block, 0, st, b);
+  if (ev_start) with_batch(b, [&](const auto& bb) { hipExtLaunchKernelGGL((attn16_kernel<KB, VB, KVX_ITEMS(bb)>), grid, block, 0, st, ev_start, ev_stop, 0, bb); });
+  else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((attn16_kernel<KB, VB, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
 }
 
 }  // namespace a16

@@ -5,7 +5,8 @@
 
 namespace kvx {
 
-__global__ __launch_bounds__(256) void check_finite_kernel(const KvxBatch b) {
+template <int N>
+__global__ __launch_bounds__(256) void check_finite_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.z];
   const void* src = blockIdx.y == 0 ? it.q : (blockIdx.y == 1 ? it.k : it.v);
@@ -32,7 +33,7 @@ __global__ __launch_bounds__(256) void check_finite_kernel(const KvxBatch b) {
 
 void launch_check_finite(const KvxBatch& b, hipStream_t st) {
   const int64_t lanes = (int64_t)b.g.n_new * b.g.H * 8;
-  hipLaunchKernelGGL(check_finite_kernel, dim3((unsigned)((lanes + 255) / 256), 3, b.n_items), dim3(256), 0, st, b);
+  with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((check_finite_kernel<KVX_ITEMS(bb)>), dim3((unsigned)((lanes + 255) / 256), 3, b.n_items), dim3(256), 0, st, bb); });
 }
 
 }  // namespace kvx

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace kvx {
 
 constexpr int kHeadDim = 64;        // d; the kernels are written for 64 channels per head
@@ -101,12 +103,34 @@ struct Item {
   int32_t pad0, pad1;
 };
 
-struct KvxBatch {
+// Kernel argument of a launch over up to N caches.  A launch copies its whole argument into the queue's argument
+// memory, so a call on one cache passes room for one (0.4 KB) instead of the 3.4 KB of a full batch.
+template <int N>
+struct KvxBatchT {
+  static constexpr int kItems = N;
   Geometry g;
   int32_t n_items;
   int32_t pad;
-  Item items[kMaxItems];
+  Item items[N];
 };
+typedef KvxBatchT<kMaxItems> KvxBatch;
+
+// Calls f with the smallest argument that holds the batch: f(const KvxBatchT<N>&).
+template <typename F>
+inline void with_batch(const KvxBatch& b, F&& f) {
+  if (b.n_items == 1) {
+    KvxBatchT<1> one;
+    one.g = b.g;
+    one.n_items = 1;
+    one.pad = 0;
+    one.items[0] = b.items[0];
+    f(one);
+  } else {
+    f(b);
+  }
+}
+// inside f: the number of caches its argument holds, as a constant
+#define KVX_ITEMS(bb) (std::remove_reference_t<decltype(bb)>::kItems)
 
 // ---- device-side address helpers ------------------------------------------------
 __device__ __forceinline__ uint8_t* cache_half(const Geometry& g, int cache, int half) {

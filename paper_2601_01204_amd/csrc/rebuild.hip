@@ -554,14 +554,14 @@ __device__ __forceinline__ void rebuild_v_block(const Geometry& g, const Item& i
 }
 
 // The two on their own, for launches of more than kMergedBlocks blocks and while their times are recorded.
-template <int B, bool M16, bool SLOTS>
-__global__ __launch_bounds__(256, 8) void rebuild_k_kernel(const KvxBatch b) {
+template <int B, bool M16, bool SLOTS, int N>
+__global__ __launch_bounds__(256, 8) void rebuild_k_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.z];
   rebuild_k_block<B, M16, SLOTS>(g, it, blockIdx.x);
 }
-template <int B, bool M16>
-__global__ __launch_bounds__(256) void rebuild_v_kernel(const KvxBatch b, int n_copy_blocks) {
+template <int B, bool M16, int N>
+__global__ __launch_bounds__(256) void rebuild_v_kernel(const KvxBatchT<N> b, int n_copy_blocks) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.z];
   rebuild_v_block<B, M16>(g, it, blockIdx.x, n_copy_blocks);
@@ -574,8 +574,8 @@ __global__ __launch_bounds__(256) void rebuild_v_kernel(const KvxBatch b, int n_
 // own, because each holds the key blocks' 22 KB of LDS: 24 caches of 16384 take 328 us against 231 + 88, 48 of 24576
 // 958 against 666 + 253, so from about 100 us on (kMergedBlocks) the two go separately.
 constexpr int kMergedBlocks = 32768;
-template <int KB, int VB, bool M16, bool SLOTS>
-__global__ __launch_bounds__(256, 8) void rebuild_kernel(const KvxBatch b, int n_k, int n_v, int n_copy_blocks) {
+template <int KB, int VB, bool M16, bool SLOTS, int N>
+__global__ __launch_bounds__(256, 8) void rebuild_kernel(const KvxBatchT<N> b, int n_k, int n_v, int n_copy_blocks) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.z];
   const uint32_t tot = (uint32_t)(n_k + n_v), x = blockIdx.x;
@@ -585,7 +585,8 @@ __global__ __launch_bounds__(256, 8) void rebuild_kernel(const KvxBatch b, int n
 }
 
 // Uncompressed baseline: append the frame's K and V as bf16 rows [H][t_cap][64].
-__global__ __launch_bounds__(256) void append_bf16_kernel(const KvxBatch b) {
+template <int N>
+__global__ __launch_bounds__(256) void append_bf16_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.z];
   const int h = blockIdx.y;
@@ -624,11 +625,11 @@ template <int KB, int VB, bool M16, bool SLOTS>
 static void launch_rebuild_t(const KvxBatch& b, int n_k, int n_v, int n_copy, hipStream_t st) {
   const dim3 block(256);
   if (n_k > 0 && n_v > 0 && (int64_t)(n_k + n_v) * b.g.H * b.n_items <= kMergedBlocks) {
-    hipLaunchKernelGGL((rebuild_kernel<KB, VB, M16, SLOTS>), dim3(n_k + n_v, b.g.H, b.n_items), block, 0, st, b, n_k, n_v, n_copy);
+    with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((rebuild_kernel<KB, VB, M16, SLOTS, KVX_ITEMS(bb)>), dim3(n_k + n_v, b.g.H, b.n_items), block, 0, st, bb, n_k, n_v, n_copy); });
     return;
   }
-  if (n_k > 0) hipLaunchKernelGGL((rebuild_k_kernel<KB, M16, SLOTS>), dim3(n_k, b.g.H, b.n_items), block, 0, st, b);
-  if (n_v > 0) hipLaunchKernelGGL((rebuild_v_kernel<VB, M16>), dim3(n_v, b.g.H, b.n_items), block, 0, st, b, n_copy);
+  if (n_k > 0) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((rebuild_k_kernel<KB, M16, SLOTS, KVX_ITEMS(bb)>), dim3(n_k, b.g.H, b.n_items), block, 0, st, bb); });
+  if (n_v > 0) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((rebuild_v_kernel<VB, M16, KVX_ITEMS(bb)>), dim3(n_v, b.g.H, b.n_items), block, 0, st, bb, n_copy); });
 }
 
 void launch_rebuild(const KvxBatch& b, int max_tnew, bool keys, bool values, hipStream_t st) {
@@ -653,7 +654,7 @@ void launch_rebuild(const KvxBatch& b, int max_tnew, bool keys, bool values, hip
 
 void launch_append_bf16(const KvxBatch& b, hipStream_t st) {
   dim3 grid((b.g.n_new + 31) / 32, b.g.H, b.n_items);
-  hipLaunchKernelGGL(append_bf16_kernel, grid, dim3(256), 0, st, b);
+  with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((append_bf16_kernel<KVX_ITEMS(bb)>), grid, dim3(256), 0, st, bb); });
 }
 
 }  // namespace kvx

@@ -26,8 +26,8 @@ __device__ __forceinline__ uint32_t order_key(float x) {
 // Against eight unrolled channels a lane with 64-bit addresses per token: one cache of 782 or
 // 1041 tokens 11 -> 4.5 us, 24 caches 24 -> 14 us, 48 caches of 1374 tokens 39 -> 26 us.
 constexpr int kPoolBatch = 16;
-template <bool F32IN>
-__global__ __launch_bounds__(1024) void pool_rows_kernel(const KvxBatch b) {
+template <bool F32IN, int N>
+__global__ __launch_bounds__(1024) void pool_rows_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.y];
   if (!it.prune) return;
@@ -92,7 +92,8 @@ __global__ __launch_bounds__(1024) void pool_rows_kernel(const KvxBatch b) {
 // 128 at a time by the whole block (one memory round trip per 128 rows), then one thread
 // per channel adds them in order.
 constexpr int kMeanRows = 128;
-__global__ __launch_bounds__(1024) void pool_mean_kernel(const KvxBatch b) {
+template <int N>
+__global__ __launch_bounds__(1024) void pool_mean_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.x];
   if (!it.prune) return;
@@ -166,8 +167,8 @@ __device__ __forceinline__ void octet_as_floats(const uint32_t* w, int o, float 
 // MEAN: the block forms q~ itself, in pool_mean_kernel's order, from the pooled rows (one LDS load of at most 128).
 constexpr int kScoreWaves = 16;
 constexpr int kMaxHeads = 64;
-template <int B, bool MEAN>
-__global__ __launch_bounds__(kScoreWaves * 64) void score_kernel(const KvxBatch b) {
+template <int B, bool MEAN, int N>
+__global__ __launch_bounds__(kScoreWaves * 64) void score_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.y];
   if (!it.prune) return;
@@ -295,9 +296,9 @@ static int score_blocks(const KvxBatch& b, int max_tc) { return std::max((max_tc
 
 void launch_pool(const KvxBatch& b, int max_tc, hipStream_t st) {
   const dim3 rows(b.g.n_pooled * (b.g.n_new / b.g.n), b.n_items), block(std::max(64, 16 * b.g.H));
-  if (b.g.in_f32) hipLaunchKernelGGL(pool_rows_kernel<true>, rows, block, 0, st, b);
-  else hipLaunchKernelGGL(pool_rows_kernel<false>, rows, block, 0, st, b);
-  if (!mean_in_score(b, score_blocks(b, max_tc))) hipLaunchKernelGGL(pool_mean_kernel, dim3(b.n_items), dim3(1024), 0, st, b);
+  if (b.g.in_f32) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((pool_rows_kernel<true, KVX_ITEMS(bb)>), rows, block, 0, st, bb); });
+  else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((pool_rows_kernel<false, KVX_ITEMS(bb)>), rows, block, 0, st, bb); });
+  if (!mean_in_score(b, score_blocks(b, max_tc))) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((pool_mean_kernel<KVX_ITEMS(bb)>), dim3(b.n_items), dim3(1024), 0, st, bb); });
 }
 
 template <int B>
@@ -307,8 +308,8 @@ static void launch_score_t(const KvxBatch& b, int max_tc, hipStream_t st) {
   // registers a unit holds three such blocks but only one of 16 waves
   const int waves = grid.x * grid.y <= 256 ? kScoreWaves : kScoreWaves / 2;
   const dim3 block(64 * std::min(b.g.H, waves));
-  if (mean_in_score(b, grid.x)) hipLaunchKernelGGL((score_kernel<B, true>), grid, block, 0, st, b);
-  else hipLaunchKernelGGL((score_kernel<B, false>), grid, block, 0, st, b);
+  if (mean_in_score(b, grid.x)) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((score_kernel<B, true, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
+  else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((score_kernel<B, false, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
 }
 
 void launch_score(const KvxBatch& b, int max_tc, hipStream_t st) {

@@ -63,7 +63,8 @@ __device__ __forceinline__ void find_bin(const int* hist, int shift, int* wave_s
 
 // LDS: histograms, then the keys (dynamic, sized for the longest cache of the launch: at most 24.1 KB + 128 KB)
 constexpr int kSelLdsInts = kSelBins0 + 2 * kSelBins;
-__global__ __launch_bounds__(kSelThreads) void select_kernel(const KvxBatch b) {
+template <int N>
+__global__ __launch_bounds__(kSelThreads) void select_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.x];
   if (!it.prune) return;
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const KvxBatch b) {
 
 void launch_select(const KvxBatch& b, int max_tc, hipStream_t st) {
   const size_t lds = (size_t)(kSelLdsInts + std::max(max_tc - b.g.n, 0)) * 4;
-  hipLaunchKernelGGL(select_kernel, dim3(b.n_items), dim3(kSelThreads), lds, st, b);
+  with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((select_kernel<KVX_ITEMS(bb)>), dim3(b.n_items), dim3(kSelThreads), lds, st, bb); });
 }
 
 }  // namespace kvx
