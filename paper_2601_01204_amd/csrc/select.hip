@@ -98,24 +98,41 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const KvxBatchT<N> 
   }
   __syncthreads();
   // Key of the n_drop-th smallest element, digit by digit.
-  for (int i = tid; i < M; i += kSelThreads) {
-    const uint32_t k = keys[i];
-    key[i] = k;
-    atomicAdd(&hist0[k >> 20], 1);
+  constexpr int kBatch = 8;                              // keys requested before any is counted
+  for (int b0 = tid; b0 < M; b0 += kBatch * kSelThreads) {
+    uint32_t k[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) k[u] = keys[min(b0 + u * kSelThreads, M - 1)];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const int i = b0 + u * kSelThreads;
+      if (i < M) {
+        key[i] = k[u];
+        atomicAdd(&hist0[k[u] >> 20], 1);
+      }
+    }
   }
   __syncthreads();
   find_bin<kSelBins0 / kSelThreads>(hist0, 20, wave_sums[0], sh);
   const uint32_t top = (uint32_t)sh[0] >> 20;
-  for (int i = tid; i < M; i += kSelThreads) {
-    const uint32_t k = key[i];
-    if (k >> 20 == top) atomicAdd(&hist1[(k >> 10) & (kSelBins - 1)], 1);
+  for (int b0 = tid; b0 < M; b0 += kBatch * kSelThreads) {
+    uint32_t k[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) k[u] = key[min(b0 + u * kSelThreads, M - 1)];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+      if (b0 + u * kSelThreads < M && k[u] >> 20 == top) atomicAdd(&hist1[(k[u] >> 10) & (kSelBins - 1)], 1);
   }
   __syncthreads();
   find_bin<kSelBins / kSelThreads>(hist1, 10, wave_sums[1], sh);
   const uint32_t top2 = (uint32_t)sh[0] >> 10;
-  for (int i = tid; i < M; i += kSelThreads) {
-    const uint32_t k = key[i];
-    if (k >> 10 == top2) atomicAdd(&hist2[k & (kSelBins - 1)], 1);
+  for (int b0 = tid; b0 < M; b0 += kBatch * kSelThreads) {
+    uint32_t k[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) k[u] = key[min(b0 + u * kSelThreads, M - 1)];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+      if (b0 + u * kSelThreads < M && k[u] >> 10 == top2) atomicAdd(&hist2[k[u] & (kSelBins - 1)], 1);
   }
   __syncthreads();
   find_bin<kSelBins / kSelThreads>(hist2, 0, wave_sums[2], sh);
@@ -126,10 +143,16 @@ __global__ __launch_bounds__(kSelThreads) void select_kernel(const KvxBatchT<N> 
   const int run = ((M + kSelThreads - 1) / kSelThreads) * 64;
   const int i0 = min(wave * run, M), i1 = min(i0 + run, M);
   int gt = 0, eq = 0;
-  for (int i = i0 + lane; i - lane < i1; i += 64) {
-    const uint32_t k = i < i1 ? key[i] : 0u;
-    gt += __popcll(__ballot(i < i1 && k > thr));
-    eq += __popcll(__ballot(i < i1 && k == thr));
+  for (int b0 = i0 + lane; b0 - lane < i1; b0 += kBatch * 64) {
+    uint32_t k[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) k[u] = key[min(b0 + u * 64, M - 1)];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      const bool in = b0 + u * 64 < i1;
+      gt += __popcll(__ballot(in && k[u] > thr));
+      eq += __popcll(__ballot(in && k[u] == thr));
+    }
   }
   if (lane == 0) {
     wave_gt[wave] = gt;
