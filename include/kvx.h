@@ -298,7 +298,8 @@ int kv_read_timing(kv_handle* h, float* total_ms, int32_t* launches);
  *   "debug_checks"                1: every step first scans q, k and v for infinities and NaNs
  *                                 and reports them through kv_stats (nonfinite_flag); 0 (default)
  *   "overlap_update"              1 (default): when attention alone cannot fill the chip (one or
- *                                 a few caches per call), scoring, pruning and re-quantisation
+ *                                 a few caches per call) and is long enough to repay the fork and
+ *                                 join (about 40 us of host time), scoring, pruning and re-quantisation
  *                                 run on a second stream of the library next to attention,
  *                                 joined back into hip_stream before kv_step returns (slot
  *                                 layout: pooling, scoring and selection do; its writers always

@@ -201,12 +201,14 @@ int validate(const kv_config* c) {
   return KV_OK;
 }
 
+constexpr double kOverlapSteps = 10.0;   // attention estimate (tile steps of about 2.3 us) from which the second stream pays
+
 // Key-range splits per (item, head, query tile) column.  A workgroup occupies a compute
 // unit by itself, so a launch runs in rounds of `target_wgs` workgroups; the estimate below
 // is rounds x (tiles per workgroup + a fixed per-workgroup cost of about three tiles for the
 // first loads and the partial-result store), and the split count with the smallest
 // estimate wins (fewer splits on ties: less merge traffic).
-int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tiles, int target_wgs) {
+int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tiles, int target_wgs, double* estimate = nullptr) {
   int s;
   if (h->splits_override > 0) {
     s = h->splits_override;
@@ -217,11 +219,13 @@ int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tile
     const int cap = (int)std::min<int64_t>(kMaxSplits, std::max<int64_t>(4, (2 * (int64_t)target_wgs) / base));
     double best = 0.0;
     s = 1;
+    if (estimate) *estimate = 0.0;
     for (int c = 1; c <= cap; ++c) {
       const int64_t rounds = (base * c + target_wgs - 1) / target_wgs;
       const double cost = (double)rounds * ((double)tiles / c + 3.0) + (c > 1 ? 1.0 : 0.0);
       if (c == 1 || cost < best * 0.98) { best = cost; s = c; }
     }
+    if (estimate) *estimate = best;
   }
   s = std::max(1, std::min(s, (int)kMaxSplits));
   s = std::min(s, std::max(1, min_tiles));
@@ -522,7 +526,14 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     // order (attention reads what the update wrote) keep everything in order on the caller's stream.
     const bool may_overlap = h->overlap != 0 && h->side && !g0.uncompressed && !update_first;
     const bool small_launch = (int64_t)cnt * g0.H * g0.n_qtiles <= (int64_t)h->n_cus;
-    const bool beside = may_overlap && (h->overlap == 2 || small_launch);
+    // The fork and the join cost the host about 40 us a call (an event record and a wait each), so that a call with the
+    // second stream issues in 67 us and one without in 27.  A short attention launch is not worth that: in order on one
+    // stream an fp32 layer of 69 tokens takes 34 us instead of 68 (estimate 4 tile steps, attention 12 us), 782 tokens at
+    // a budget of 2048 take 61 us beside and 65 in order (12 steps, 31 us), 1041 tokens at 4096 69 and 73 (19 steps, 41
+    // us), at 8192 94 and 109 (32 steps).
+    double steps = 0.0;
+    pick_splits(h, b.g, cnt, min_tiles, h->n_cus, &steps);
+    const bool beside = may_overlap && (h->overlap == 2 || (small_launch && (steps == 0.0 || steps >= kOverlapSteps)));
     // a small launch leaves a quarter of the compute units to the chain next to it
     b.g.n_splits = pick_splits(h, b.g, cnt, min_tiles, ((beside && small_launch) || h->target_explicit) ? h->target_wgs : h->n_cus);
     // never more splits than the partial-result buffers hold (an explicit "attention_splits" may ask for more)
