@@ -273,9 +273,9 @@ const char* kv_last_error(kv_handle* h);
 enum kv_kernel_id {
   KV_K_ATTENTION = 0, /* fused de-quantise + attention (Eq. 1, Eq. 10)          */
   KV_K_COMBINE = 1,   /* merge of the split-KV partial results                   */
-  KV_K_POOL = 2,      /* pooled query (Eq. 2-3 and the row mean of Eq. 6)        */
-  KV_K_SCORE = 3,     /* per-head q~ . K~ over the cached tokens (Eq. 4-5)       */
-  KV_K_SELECT = 4,    /* head sum, top-k, keep list                              */
+  KV_K_POOL = 2,      /* pooled query (Eq. 2-3; larger launches: row mean of Eq. 6) */
+  KV_K_SCORE = 3,     /* q~ . K~ per head and the head sum (Eq. 4-6)             */
+  KV_K_SELECT = 4,    /* top-k, keep list                                        */
   KV_K_REBUILD_K = 5, /* compaction + per-channel key (re)quantisation (Eq. 7-9) */
   KV_K_REBUILD_V = 6, /* value carry / per-token quantisation, token ids         */
   KV_K_COUNT = 7
@@ -284,7 +284,8 @@ enum kv_kernel_id {
 /* Measurement aid: while bit (1 << id) of kernel_mask is set, every launch of that class
  * is bracketed by HIP events recorded on the stream it runs on.  kv_read_timing waits
  * for the recorded events, writes per class the summed duration in milliseconds and the
- * number of launches (host arrays of KV_K_COUNT entries) and clears the record. */
+ * number of launches (host arrays of KV_K_COUNT entries) and clears the record.  While
+ * either rebuild class is timed, key and value rebuild are launched separately. */
 int kv_set_timing(kv_handle* h, uint32_t kernel_mask);
 int kv_read_timing(kv_handle* h, float* total_ms, int32_t* launches);
 
