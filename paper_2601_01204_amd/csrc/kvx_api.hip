@@ -493,7 +493,7 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     b.g.out_head_stride = head_stride;
     b.n_items = cnt;
     b.pad = 0;
-    int max_tc = 0, max_tnew = 0, min_tiles = 1 << 30;
+    int max_tc = 0, max_tnew = 0, min_tiles = 1 << 30, max_tiles = 1;
     bool any_prune = false;
     for (int i = 0; i < cnt; ++i) {
       const kv_step_item& src = items[base + i];
@@ -514,6 +514,7 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
       max_tnew = std::max(max_tnew, t_after);
       const int tiles = update_first ? (t_after + kTileK - 1) / kTileK : (cs.t_c + kTileK - 1) / kTileK + (n_new + kTileK - 1) / kTileK;
       min_tiles = std::min(min_tiles, tiles);
+      max_tiles = std::max(max_tiles, tiles);
     }
     b.g.part_o = part_o;
     b.g.part_ml = part_ml;
@@ -527,12 +528,15 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     const bool may_overlap = h->overlap != 0 && h->side && !g0.uncompressed && !update_first;
     const bool small_launch = (int64_t)cnt * g0.H * g0.n_qtiles <= (int64_t)h->n_cus;
     // The fork and the join cost the host about 40 us a call (an event record and a wait each), so that a call with the
-    // second stream issues in 67 us and one without in 27.  A short attention launch is not worth that: in order on one
-    // stream an fp32 layer of 69 tokens takes 34 us instead of 68 (estimate 4 tile steps, attention 12 us), 782 tokens at
-    // a budget of 2048 take 61 us beside and 65 in order (12 steps, 31 us), 1041 tokens at 4096 69 and 73 (19 steps, 41
-    // us), at 8192 94 and 109 (32 steps).
+    // second stream issues in 60 us or more and one without in 27.  A short attention launch is not worth that.  In order
+    // and beside, us a step, calls back to back: 69 tokens, fp32 (4.4 tile steps) 34 and 59; 400 at a budget of 1024 (6.9)
+    // 47 and 64; 523 at 2048 (9.1) 57 and 64; 1374 at 2800, 6 heads (10.6) 61 and 62; 782 at 1600 (11.6) 61 and 61, at
+    // 2048 (13.0) 62 and 59; 1041 at 2400 (15.0) 70 and 60, at 4096 (20.2) 81 and 66.  Where other work of the GPU hides
+    // the issue the two meet earlier (400 tokens 49 and 54, 523 at 1500 58 and 54, at 2048 60 and 53).
+    // A launch lasts as long as its longest cache, so the estimate goes by that one: a stream that starts beside a full
+    // cache of 16384 tokens (523 tokens a frame, 6 heads) takes 107 us a step in order and 82 beside.
     double steps = 0.0;
-    pick_splits(h, b.g, cnt, min_tiles, h->n_cus, &steps);
+    pick_splits(h, b.g, cnt, max_tiles, h->n_cus, &steps);
     const bool beside = may_overlap && (h->overlap == 2 || (small_launch && (steps == 0.0 || steps >= kOverlapSteps)));
     // a small launch leaves a quarter of the compute units to the chain next to it
     b.g.n_splits = pick_splits(h, b.g, cnt, min_tiles, ((beside && small_launch) || h->target_explicit) ? h->target_wgs : h->n_cus);

@@ -42,7 +42,8 @@ inline hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v 
 inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = reinterpret_cast<hipStream_t>(std::malloc(1)); return hipSuccess; }
 inline hipError_t hipStreamDestroy(hipStream_t s) { std::free(s); return hipSuccess; }
 inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
-inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+inline int stub_stream_waits = 0;      // waits enqueued so far: a step on two streams makes two, one in order none
+inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { ++stub_stream_waits; return hipSuccess; }
 inline hipError_t hipEventCreate(hipEvent_t* e) { *e = reinterpret_cast<hipEvent_t>(std::malloc(1)); return hipSuccess; }
 inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
 inline hipError_t hipEventDestroy(hipEvent_t e) { std::free(e); return hipSuccess; }

@@ -6,6 +6,8 @@
 #include <random>
 #include <vector>
 
+#include <hip/hip_runtime.h>
+
 #include "../../include/kvx.h"
 
 #define CHECK(cond)                                                                   \
@@ -177,9 +179,36 @@ void one_format(int meta, int layout, int kb, int kg, int vb, int vg) {
   kv_destroy(h2);
 }
 
+// The update chain goes to the second stream where attention is long, which the longest cache of a call decides.
+void second_stream_by_the_longest_cache() {
+  kv_config c = base_config(KV_META_F32, KV_LAYOUT_COMPACT, 4, 64, 4, 64);
+  c.n_streams = 2; c.n_layers = 1; c.n_heads = 2; c.tokens_per_frame = 64; c.budget_tokens = 8192; c.max_frames_per_step = 1;
+  kv_handle* h = nullptr;
+  CHECK(kv_init(&c, &h) == KV_OK && h);
+  const int64_t ts = (int64_t)c.n_heads * 64, hs = 64;
+  std::vector<uint16_t> q((size_t)c.tokens_per_frame * ts), o(q.size());
+  kv_step_item items[2];
+  for (int i = 0; i < 2; ++i) { items[i].stream = i; items[i].layer = 0; items[i].q = items[i].k = items[i].v = q.data(); items[i].out = o.data(); }
+  auto waits = [&](int n, const kv_step_item* it) {
+    const int before = stub_stream_waits;
+    CHECK(kv_step_batched(h, n, it, ts, hs, nullptr) == KV_OK);
+    return stub_stream_waits - before;
+  };
+  CHECK(waits(2, items) == 0);                                               // two short caches: in order
+  for (int f = 0; f < 200; ++f) waits(1, items);                             // stream 0 fills up
+  CHECK(waits(1, items) == 2);
+  CHECK(kv_reset(h, 1, 0) == KV_OK);
+  CHECK(waits(2, items) == 2);                                               // a stream that starts beside a full cache
+  CHECK(waits(1, items + 1) == 0);
+  CHECK(kv_set_option(h, "overlap_update", 0) == KV_OK && waits(2, items) == 0);
+  CHECK(kv_set_option(h, "overlap_update", 2) == KV_OK && waits(1, items + 1) == 2);
+  kv_destroy(h);
+}
+
 }  // namespace
 
 int main() {
+  second_stream_by_the_longest_cache();
   for (int meta : {KV_META_F32, KV_META_F16})
     for (int layout : {KV_LAYOUT_COMPACT, KV_LAYOUT_SLOTS}) {
       one_format(meta, layout, 4, 64, 4, 64);
