@@ -365,6 +365,7 @@ int kv_init(const kv_config* cfg, kv_handle** out) {
     return rc;
   }
   h->n_cus = cus;
+  g.n_cus = cus;
   h->target_wgs = std::max(1, cus * 3 / 4);
   {
     const hipError_t e = static_scratch_address(h->device, &h->static_scratch);

@@ -87,6 +87,7 @@ struct Geometry {
   float inv_scale_log2;   // fp32(1 / scale_log2): s = a * inv_scale_log2 in the 16-bit metadata format
   int32_t meta16;         // 1: 16-bit scales and zero-points
   int32_t slots;          // 1: slot-stable layout (one buffer, tokens never move), 0: compacting double buffer
+  int32_t n_cus;          // compute units of the device
 };
 
 struct Item {
@@ -131,6 +132,19 @@ inline void with_batch(const KvxBatch& b, F&& f) {
 }
 // inside f: the number of caches its argument holds, as a constant
 #define KVX_ITEMS(bb) (std::remove_reference_t<decltype(bb)>::kItems)
+
+// ---- launch shape of the scoring kernel ------------------------------------------
+// Blocks of 64 positions per cache that hold middle tokens: behind the first frame.
+inline int score_blocks(const KvxBatch& b, int max_tc) {
+  const int blocks = (max_tc + 63) / 64 - b.g.n / 64;
+  return blocks > 1 ? blocks : 1;
+}
+// A launch of up to a score block per compute unit is bound by its chain of dependent launches: there every score block
+// forms the row mean for itself (about 1 us) and the mean's launch (4.3 us) falls away.
+constexpr int kMeanRows = 128;      // pooled rows brought into LDS at a time
+inline bool mean_in_score(const KvxBatch& b, int max_tc) {
+  return score_blocks(b, max_tc) * b.n_items <= b.g.n_cus && b.g.n_pooled * (b.g.n_new / b.g.n) <= kMeanRows;
+}
 
 // ---- device-side address helpers ------------------------------------------------
 __device__ __forceinline__ uint8_t* cache_half(const Geometry& g, int cache, int half) {

@@ -91,7 +91,6 @@ __global__ __launch_bounds__(1024) void pool_rows_kernel(const KvxBatchT<N> b) {
 // through the kernel boundary and no block has to fence.  The rows are brought into LDS
 // 128 at a time by the whole block (one memory round trip per 128 rows), then one thread
 // per channel adds them in order.
-constexpr int kMeanRows = 128;
 template <int N>
 __global__ __launch_bounds__(1024) void pool_mean_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
@@ -286,19 +285,11 @@ __global__ __launch_bounds__(kScoreWaves * 64) void score_kernel(const KvxBatchT
   }
 }
 
-// A launch of up to a score block per compute unit is bound by its chain of dependent launches: there every score block
-// forms the row mean for itself (about 1 us) and the mean's launch (4.3 us) falls away.
-static bool mean_in_score(const KvxBatch& b, int score_blocks) {
-  return score_blocks * b.n_items <= 256 && b.g.n_pooled * (b.g.n_new / b.g.n) <= kMeanRows;
-}
-// blocks of 64 positions that hold middle tokens: behind the first frame
-static int score_blocks(const KvxBatch& b, int max_tc) { return std::max((max_tc + 63) / 64 - b.g.n / 64, 1); }
-
 void launch_pool(const KvxBatch& b, int max_tc, hipStream_t st) {
   const dim3 rows(b.g.n_pooled * (b.g.n_new / b.g.n), b.n_items), block(std::max(64, 16 * b.g.H));
   if (b.g.in_f32) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((pool_rows_kernel<true, KVX_ITEMS(bb)>), rows, block, 0, st, bb); });
   else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((pool_rows_kernel<false, KVX_ITEMS(bb)>), rows, block, 0, st, bb); });
-  if (!mean_in_score(b, score_blocks(b, max_tc))) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((pool_mean_kernel<KVX_ITEMS(bb)>), dim3(b.n_items), dim3(1024), 0, st, bb); });
+  if (!mean_in_score(b, max_tc)) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((pool_mean_kernel<KVX_ITEMS(bb)>), dim3(b.n_items), dim3(1024), 0, st, bb); });
 }
 
 template <int B>
@@ -306,9 +297,9 @@ static void launch_score_t(const KvxBatch& b, int max_tc, hipStream_t st) {
   const dim3 grid(score_blocks(b, max_tc), b.n_items);
   // up to a block per compute unit latency counts: all of 16 heads at once.  Beyond, eight waves a block: at about 80
   // registers a unit holds three such blocks but only one of 16 waves
-  const int waves = grid.x * grid.y <= 256 ? kScoreWaves : kScoreWaves / 2;
+  const int waves = (int)(grid.x * grid.y) <= b.g.n_cus ? kScoreWaves : kScoreWaves / 2;
   const dim3 block(64 * std::min(b.g.H, waves));
-  if (mean_in_score(b, grid.x)) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((score_kernel<B, true, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
+  if (mean_in_score(b, max_tc)) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((score_kernel<B, true, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
   else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((score_kernel<B, false, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
 }
 

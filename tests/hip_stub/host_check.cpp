@@ -205,9 +205,26 @@ void second_stream_by_the_longest_cache() {
   kv_destroy(h);
 }
 
+// "A block per compute unit" means the units the device has: 63 score blocks on 64 of them and on 48.
+void launch_rules_by_the_device(int cus, bool inside) {
+  stub_cus = cus;
+  kv_config c = base_config(KV_META_F32, KV_LAYOUT_COMPACT, 4, 64, 4, 64);
+  c.n_streams = c.n_layers = 1; c.tokens_per_frame = 64; c.budget_tokens = 4096; c.max_frames_per_step = 1;
+  kv_handle* h = nullptr;
+  CHECK(kv_init(&c, &h) == KV_OK && h);
+  const int64_t ts = (int64_t)c.n_heads * 64, hs = 64;
+  std::vector<uint16_t> q((size_t)c.tokens_per_frame * ts), o(q.size());
+  for (int f = 0; f < 66; ++f) CHECK(kv_step(h, 0, 0, q.data(), q.data(), q.data(), ts, hs, o.data(), nullptr) == KV_OK);
+  CHECK(stub_mean_in_score == inside);
+  kv_destroy(h);
+  stub_cus = 256;
+}
+
 }  // namespace
 
 int main() {
+  launch_rules_by_the_device(64, true);
+  launch_rules_by_the_device(48, false);
   second_stream_by_the_longest_cache();
   for (int meta : {KV_META_F32, KV_META_F16})
     for (int layout : {KV_LAYOUT_COMPACT, KV_LAYOUT_SLOTS}) {

@@ -5,7 +5,7 @@ void launch_attention(const KvxBatch&, int, hipStream_t, hipEvent_t, hipEvent_t)
 void launch_attention16(const KvxBatch&, hipStream_t, hipEvent_t, hipEvent_t) {}
 void launch_combine(const KvxBatch&, hipStream_t) {}
 void launch_pool(const KvxBatch&, int, hipStream_t) {}
-void launch_score(const KvxBatch&, int, hipStream_t) {}
+void launch_score(const KvxBatch& b, int max_tc, hipStream_t) { stub_mean_in_score = mean_in_score(b, max_tc); }
 void launch_select(const KvxBatch&, int, hipStream_t) {}
 void launch_rebuild(const KvxBatch&, int, bool, bool, hipStream_t) {}
 void launch_append_bf16(const KvxBatch&, hipStream_t) {}
