@@ -17,17 +17,26 @@ def test_pooled_rows_around_one_lds_load(n, pool_group):
     pu.run_stream(w, 6)
 
 
-@pytest.mark.parametrize("n_heads,n,k_bits,k_group,meta16,slots", [(11, 37, 4, 32, True, False), (17, 64, 2, 64, False, True), (3, 65, 8, 32, False, False)])
-def test_wide_launches(n_heads, n, k_bits, k_group, meta16, slots):
-    """40 caches of 401 positions in one call: more score blocks than compute units."""
+@pytest.mark.parametrize("n_heads,n,budget,k_bits,k_group,meta16,slots", [
+    (11, 37, 513, 4, 32, True, False), (17, 64, 513, 2, 64, False, True), (3, 65, 513, 8, 32, False, False),
+    (1, 50, 513, 4, 64, True, False), (19, 40, 513, 8, 64, False, False), (5, 200, 2300, 4, 64, True, True)])
+def test_wide_launches(n_heads, n, budget, k_bits, k_group, meta16, slots):
+    """48 caches in one call: more score blocks than compute units on every pruning frame (and, at 2300 positions, as
+    many as six times the units), so the row mean has a launch of its own and a block's waves take turns over the heads."""
     import torch
-    streams, frames = 40, 402 // n + 2
-    w = si.Workload("wide", n_heads, 64, n, 3, 8, 401, frames, 1, streams, k_bits, k_group, 4, 32, "bf16", 51)
+    streams, frames = 48, budget // n + 3
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    w = si.Workload("wide", n_heads, 64, n, 3, 8, budget, frames, 1, streams, k_bits, k_group, 4, 32, "bf16", 51)
     h = pu.make_handle(w, n_streams=streams, meta_format=1 if meta16 else 0, layout=1 if slots else 0)
-    checked = (0, 21, 39)
+    checked = (0, 21, 47)
     caches = {s: xo.OracleCache(pu.oracle_cfg(w, meta16, slots)) for s in checked}
     sigmas = {s: si.key_channel_scales(w, s, 0) for s in checked}
+    wide = 0
     for t in range(frames):
+        t_c = caches[0].cache_len
+        if t_c + n > budget:
+            assert streams * (-(-t_c // 64) - n // 64) > units
+            wide += 1
         refs, dev = {}, {}
         for s in checked:
             q, k, v = si.frame_qkv(w, t, s, 0, sigmas[s])
@@ -40,4 +49,5 @@ def test_wide_launches(n_heads, n, k_bits, k_group, meta16, slots):
         for s in checked:
             pu.check_output(outs[s].cpu().numpy(), refs[s], f"stream {s} frame {t}")
             pu.check_state(h.export(s, 0), caches[s], f"stream {s} frame {t}")
+    assert wide >= 2
     h.close()
