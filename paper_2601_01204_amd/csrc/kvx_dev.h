@@ -146,6 +146,26 @@ inline bool mean_in_score(const KvxBatch& b, int max_tc) {
   return score_blocks(b, max_tc) * b.n_items <= b.g.n_cus && b.g.n_pooled * (b.g.n_new / b.g.n) <= kMeanRows;
 }
 
+// Waves of a scoring block, which take turns over the heads.  Up to a block per compute unit latency counts: all of 16 heads
+// at once.  Beyond, no more than eight, since a unit holds one block of 16 waves but three of eight, and of those as many as
+// put six waves on every SIMD, at least four: a wave requests its next head's codes before it works on this one's, so two
+// turns are better than one.  us at 48 caches of 16384 tokens, 4-bit codes: 9 heads 85 with 16 waves, 59 with eight, 54 with
+// four; 16 heads 140, 92 and 89.5; two waves are no better than four.  Rows of 8-bit codes take four loads and gain from
+// eight waves once each still has two turns: 8 heads 92 with eight and 81 with four, 12 heads 115 and 117, 16 heads 148
+// and 152.  Then no more than keep the number of turns, so that nine heads take three turns of three waves and not of four.
+constexpr int kScoreWaves = 16;
+inline int score_waves(int H, int k_bits, int blocks, int n_cus) {
+  int waves = kScoreWaves;
+  if (blocks > n_cus) {
+    waves = k_bits == 8 && H > 8 ? 8 : (24 * n_cus + blocks - 1) / blocks;
+    waves = waves < 4 ? 4 : (waves > 8 ? 8 : waves);
+  }
+  const int turns = (H + waves - 1) / waves;
+  return (H + turns - 1) / turns;
+}
+// LDS of a scoring block: two groups' factors a and b of each wave, then the dots of every head.
+inline size_t score_lds_bytes(int H, int waves) { return (size_t)(waves * 4 * kHeadDim + H * 64) * 4; }
+
 // ---- device-side address helpers ------------------------------------------------
 __device__ __forceinline__ uint8_t* cache_half(const Geometry& g, int cache, int half) {
   return g.arena + (int64_t)cache * g.lay.cache_bytes + (int64_t)half * g.lay.half_bytes;

@@ -158,14 +158,16 @@ __device__ __forceinline__ void octet_as_floats(const uint32_t* w, int o, float 
 // (head, key group, channel), p[c] = fma(float(code[c]), a[c], b[c]) per token, then the stride-halving pairwise tree
 // p[c] += p[c + m] for m = 32, 16, ..., 1.  Then S_j = (D[0, j] + D[1, j] + ... + D[H-1, j]) / H, heads added in order
 // (Eq. 4-6), and the order-preserving key of the score.
-// A block covers 64 consecutive cache positions of all heads, one wave per head (the waves take turns if there are
-// more heads) and one token per lane, so the dots of a token meet in LDS and never travel through memory.  Blocks start at a
-// multiple of 64 positions, so a wave needs the factors of one key group (two of 32 tokens), which it stages for itself.
-// Against dots through memory and a launch of its own for the head sum: 24 layers of 782 tokens at a budget of 2048, one
-// call each, 1852 -> 1766 us; 24 caches of 16384 in one call unchanged (2498 -> 2501 us a step: vector-bound either way).
+// A block covers 64 consecutive cache positions of all heads, one token per lane; its waves take turns over the heads (see
+// score_waves) and the dots of a token meet in LDS, so they never travel through memory.  Blocks start at a multiple of 64
+// positions, so a wave needs the factors of one key group (two of 32 tokens), which it stages for itself.  Bound by vector
+// instructions; the code row and the factors of a wave's next head are requested before the arithmetic of this one, and the
+// block holds the LDS its waves and heads need and no more, so that six to seven waves a SIMD cover what is left.
+// us at 48 caches of 16384 tokens, 4-bit codes, against blocks of one shape for all head counts (32 KB of LDS, eight waves,
+// nothing requested ahead): 1 head 27 -> 12, 4 heads 41 -> 30, 9 heads 78 -> 56, 16 heads 112 -> 89; and with the selection
+// behind it, against dots through memory and a launch of its own for the head sum: 41 -> 32, 62 -> 50, 86 -> 76, 130 -> 109.
+// 24 layers of 782 tokens at a budget of 2048, one call each, 1852 -> 1766 us a frame for the launch saved.
 // MEAN: the block forms q~ itself, in pool_mean_kernel's order, from the pooled rows (one LDS load of at most 128).
-constexpr int kScoreWaves = 16;
-constexpr int kMaxHeads = 64;
 template <int B, bool MEAN, int N>
 __global__ __launch_bounds__(kScoreWaves * 64) void score_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
@@ -176,25 +178,40 @@ __global__ __launch_bounds__(kScoreWaves * 64) void score_kernel(const KvxBatchT
   const uint8_t* half = cache_half(g, it.cache, it.cur);
   uint8_t* sc = cache_scratch(g, it.cache);
   constexpr int kRowWords = 2 * B;                 // 64 channels * B bits / 32
-  __shared__ __attribute__((aligned(16))) float s_a[kScoreWaves][2][kHeadDim];
-  __shared__ __attribute__((aligned(16))) float s_b[kScoreWaves][2][kHeadDim];
-  __shared__ float dots[kMaxHeads][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n_waves = blockDim.x >> 6;
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  float* s_a = lds + wave * (4 * kHeadDim);        // [2 groups][64] of this wave, b behind a
+  float* s_b = s_a + 2 * kHeadDim;
+  float* dots = lds + n_waves * (4 * kHeadDim);    // [H][64]
 
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
   const int j = j0 + lane;
   const int jl = min(j, it.t_c - 1);
   const int k_shift = g.k_group == 64 ? 6 : 5;      // groups of 64 or 32 tokens
   const int gi = k_shift == 6 ? 0 : lane >> 5;      // the lane's token's group within the block
-  // a head's code row of the lane's token is requested first, so that its latency runs beside the staging of the factors
-  uint32_t w[kRowWords];
-  auto load_row = [&](int h) __attribute__((always_inline)) {
-    const uint32_t* src = reinterpret_cast<const uint32_t*>(half + g.lay.k_codes + ((int64_t)h * g.t_cap + jl) * (8 * B));
+  // (a group past the cache's end lies inside the buffer; its factors are not used)
+  const int grp = j0 >> k_shift;
+  uint32_t w[kRowWords];                            // a head's code row of the lane's token
+  uint32_t rs[2], rz[2];                            // scale and zero-point of this lane's channel as they are stored
+  auto load_head = [&](int h, uint32_t (&w)[kRowWords], uint32_t (&rs)[2], uint32_t (&rz)[2]) __attribute__((always_inline)) {
+    const uint32_t* src = reinterpret_cast<const uint32_t*>(half + g.lay.k_codes + (int64_t)h * g.t_cap * (8 * B) + (uint32_t)(jl * (8 * B)));
 #pragma unroll
     for (int i = 0; i < kRowWords; ++i) w[i] = src[i];
+    const int64_t moff = ((int64_t)h * g.g_cap + grp) * kHeadDim;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (q == 1 && k_shift == 6) break;
+      if (g.meta16) {
+        rs[q] = (reinterpret_cast<const uint16_t*>(half + g.lay.k_scale) + moff + q * kHeadDim)[meta16_pos(lane)];
+        rz[q] = (reinterpret_cast<const uint16_t*>(half + g.lay.k_zero) + moff + q * kHeadDim)[meta16_pos(lane)];
+      } else {
+        rs[q] = (reinterpret_cast<const uint32_t*>(half + g.lay.k_scale) + moff + q * kHeadDim)[lane];
+        rz[q] = (reinterpret_cast<const uint32_t*>(half + g.lay.k_zero) + moff + q * kHeadDim)[lane];
+      }
+    }
   };
+  load_head(wave, w, rs, rz);      // requested first: its latency runs beside the row mean
   float qc;
   if constexpr (MEAN) {
-    load_row(wave);
     __shared__ __attribute__((aligned(16))) float rows[kMeanRows][kHeadDim];
     __shared__ float s_qt[kHeadDim];
     const float4* qbar = reinterpret_cast<const float4*>(sc + g.sl.qbar);
@@ -212,38 +229,38 @@ __global__ __launch_bounds__(kScoreWaves * 64) void score_kernel(const KvxBatchT
   } else {
     qc = reinterpret_cast<const float*>(sc + g.sl.qt)[lane];
   }
-  for (int h = wave; h < g.H; h += n_waves) {
-    if (!MEAN || h != wave) load_row(h);
+  for (int h = wave;; h += n_waves) {
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       if (q == 1 && k_shift == 6) break;
-      // (a group past the cache's end lies inside the buffer; its factors are not used)
-      const int grp = (j0 >> k_shift) + q;
       float sv, zf;
       if (g.meta16) {
         // halves: logit-domain scale a16 (s = a16 * fp32(1 / scale_log2)) and 1024 + z, channels of an octet in the order 0 4 1 5 2 6 3 7
-        const int64_t moff = ((int64_t)h * g.g_cap + grp) * kHeadDim + meta16_pos(lane);
-        sv = (float)__builtin_bit_cast(_Float16, reinterpret_cast<const uint16_t*>(half + g.lay.k_scale)[moff]) * g.inv_scale_log2;
-        zf = (float)__builtin_bit_cast(_Float16, reinterpret_cast<const uint16_t*>(half + g.lay.k_zero)[moff]) - 1024.0f;
+        sv = (float)__builtin_bit_cast(_Float16, (uint16_t)rs[q]) * g.inv_scale_log2;
+        zf = (float)__builtin_bit_cast(_Float16, (uint16_t)rz[q]) - 1024.0f;
       } else {
-        const int64_t moff = ((int64_t)h * g.g_cap + grp) * kHeadDim + lane;
-        sv = reinterpret_cast<const float*>(half + g.lay.k_scale)[moff];
-        zf = (float)reinterpret_cast<const int32_t*>(half + g.lay.k_zero)[moff];
+        sv = __uint_as_float(rs[q]);
+        zf = (float)(int32_t)rz[q];
       }
       const float a = qc * sv;
-      s_a[wave][q][lane] = a;
-      s_b[wave][q][lane] = (-zf) * a;
+      s_a[q * kHeadDim + lane] = a;
+      s_b[q * kHeadDim + lane] = (-zf) * a;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");    // the factors cross lanes of this wave only
     __builtin_amdgcn_wave_barrier();
 
+    uint32_t wn[kRowWords], rsn[2], rzn[2];         // of the next head this wave takes
+    const bool more = h + n_waves < g.H;
+    if (more) load_head(h + n_waves, wn, rsn, rzn);
     // The tree's upper levels octet by octet: m = 32 adds octet o + 4 to octet o, m = 16 octet 2 to 0 and 3 to 1, m = 8
     // octet 1 to 0.  The same additions in an order that keeps few octets at a time in registers.
     auto octet = [&](int o, float (&x)[8]) __attribute__((always_inline)) {
       float f[8];
       octet_as_floats<B>(w, o, f);
-      const float4 a0 = *reinterpret_cast<const float4*>(&s_a[wave][gi][8 * o]), a1 = *reinterpret_cast<const float4*>(&s_a[wave][gi][8 * o + 4]);
-      const float4 b0 = *reinterpret_cast<const float4*>(&s_b[wave][gi][8 * o]), b1 = *reinterpret_cast<const float4*>(&s_b[wave][gi][8 * o + 4]);
+      const float* pa = s_a + gi * kHeadDim + 8 * o;
+      const float* pb = s_b + gi * kHeadDim + 8 * o;
+      const float4 a0 = *reinterpret_cast<const float4*>(pa), a1 = *reinterpret_cast<const float4*>(pa + 4);
+      const float4 b0 = *reinterpret_cast<const float4*>(pb), b1 = *reinterpret_cast<const float4*>(pb + 4);
       const float a[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w}, c[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = __builtin_fmaf(f[e], a[e], c[e]);
@@ -272,13 +289,23 @@ __global__ __launch_bounds__(kScoreWaves * 64) void score_kernel(const KvxBatchT
 #pragma unroll
       for (int c = 0; c < m; ++c) p[c] = p[c] + p[c + m];
     }
-    dots[h][lane] = p[0];
+    dots[h * 64 + lane] = p[0];
     __builtin_amdgcn_wave_barrier();
+    if (!more) break;
+#pragma unroll
+    for (int i = 0; i < kRowWords; ++i) w[i] = wn[i];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      if (q == 1 && k_shift == 6) break;
+      rs[q] = rsn[q];
+      rz[q] = rzn[q];
+    }
   }
   __syncthreads();
-  if (threadIdx.x < 64 && j >= g.n && j < it.t_c) {
-    float acc = dots[0][lane];
-    for (int h = 1; h < g.H; ++h) acc = acc + dots[h][lane];
+  if (wave == 0 && j >= g.n && j < it.t_c) {
+    float acc = dots[lane];
+#pragma unroll 4
+    for (int h = 1; h < g.H; ++h) acc = acc + dots[h * 64 + lane];
     const float s = acc / (float)g.H;
     reinterpret_cast<float*>(sc + g.sl.scores)[j - g.n] = s;
     reinterpret_cast<uint32_t*>(sc + g.sl.keys)[j - g.n] = order_key(s);
@@ -294,13 +321,11 @@ void launch_pool(const KvxBatch& b, int max_tc, hipStream_t st) {
 
 template <int B>
 static void launch_score_t(const KvxBatch& b, int max_tc, hipStream_t st) {
-  const dim3 grid(score_blocks(b, max_tc), b.n_items);
-  // up to a block per compute unit latency counts: all of 16 heads at once.  Beyond, eight waves a block: at about 80
-  // registers a unit holds three such blocks but only one of 16 waves
-  const int waves = (int)(grid.x * grid.y) <= b.g.n_cus ? kScoreWaves : kScoreWaves / 2;
-  const dim3 block(64 * std::min(b.g.H, waves));
-  if (mean_in_score(b, max_tc)) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((score_kernel<B, true, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
-  else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((score_kernel<B, false, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
+  const int blocks = score_blocks(b, max_tc), waves = score_waves(b.g.H, B, blocks * b.n_items, b.g.n_cus);
+  const dim3 grid(blocks, b.n_items), block(64 * waves);
+  const size_t lds = score_lds_bytes(b.g.H, waves);
+  if (mean_in_score(b, max_tc)) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((score_kernel<B, true, KVX_ITEMS(bb)>), grid, block, lds, st, bb); });
+  else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((score_kernel<B, false, KVX_ITEMS(bb)>), grid, block, lds, st, bb); });
 }
 
 void launch_score(const KvxBatch& b, int max_tc, hipStream_t st) {

@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include "../../include/kvx.h"
+#include "kvx_dev.h"
 
 #define CHECK(cond)                                                                   \
   do {                                                                                \
@@ -220,9 +221,24 @@ void launch_rules_by_the_device(int cus, bool inside) {
   stub_cus = 256;
 }
 
+// Scoring blocks: every head has a wave's turn and no turn is nearly empty; in a launch of more than a block per compute
+// unit the blocks leave LDS for six waves on each of a unit's four SIMDs, whatever the head count.
+void score_block_shapes() {
+  for (int i = 0; i < 128; ++i)
+    for (int blocks : {1, 60, 256, 257, 300, 800, 1600, 6000, 18000}) {
+      const int H = 1 + i % 64, waves = kvx::score_waves(H, i < 64 ? 4 : 8, blocks, 256), turns = (H + waves - 1) / waves;
+      CHECK(waves >= 1 && waves <= H && waves <= kvx::kScoreWaves);
+      CHECK(waves * turns - H < turns);
+      if (blocks <= 256) continue;
+      CHECK(waves <= 8);
+      CHECK(kvx::score_lds_bytes(H, waves) * ((24 + waves - 1) / waves) <= 160 * 1024);
+    }
+}
+
 }  // namespace
 
 int main() {
+  score_block_shapes();
   launch_rules_by_the_device(64, true);
   launch_rules_by_the_device(48, false);
   second_stream_by_the_longest_cache();
