@@ -22,7 +22,9 @@
 // (KB = VB = 16) takes one MFMA per step from a zero accumulator and applies the factor and
 // the softmax reference to the 32 x 64 logits by one fused operation each, which saves per
 // tile and wave 256 cycles of matrix work, 8 operand reads and the split in the staging: two
-// layers over their first 24 frames of 1041 tokens 4741 -> 3807 us.  The compressed kernels
+// layers over their first 24 frames of 1041 tokens 4741 -> 3807 us.  It is also closer to Eq. 1
+// in 64 bits, which the key pairs' 16 bits are not exact for: relative error of fp32 outputs
+// 1.19e-4 -> 1.12e-4 (1041 tokens, 6 frames), 9.4e-5 -> 8.3e-5 (523, 10), 4.3e-5 -> 3.2e-5 (69, 12).  The compressed kernels
 // do not take that path for the frame's own tiles: with both forms in one kernel registers
 // spill (24 x 16384 tokens, 3207 -> 3300 us).
 //
@@ -214,6 +216,11 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
   const uint8_t* half = cache_half(g, it.cache, it.cur);
   const bool compressed = F32IN ? !g.uncompressed : !UNC;
   const float sc = g.scale_log2;
+  // Uncompressed keys enter the product as they are, so it could leave fp32's range where the logit does not.  A factor below
+  // one is therefore taken in two parts: its power of two with the queries (exact, once per workgroup: 0.3 % of the two-layer
+  // clip above), the rest with the logits.
+  const int sc_exp = UNC ? max(min((int)(__float_as_uint(sc) >> 23) - 127, 0), -126) : 0;
+  const float q_factor = __uint_as_float((uint32_t)(127 + sc_exp) << 23), s_factor = UNC ? ldexpf(sc, -sc_exp) : sc;
   // Query rows of this wave: block `wave` of the tile's q_blocks 32-row blocks; a wave
   // without rows (fewer than 8 blocks in the tile, or a ragged last tile) only stages.
   constexpr int NB = 1;
@@ -228,7 +235,8 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
   // ---- this wave's query fragments (B operand of S^T = K Q^T) ---------------------
   // They live in a private LDS region of the wave, one 16-byte entry per lane and
   // 16-channel step (fp32 input: a second set for the lo parts), and are re-read every
-  // tile: the registers they would occupy hold the -m block below instead.
+  // tile: the registers they would occupy hold the -m block below instead (the kernel of the
+  // uncompressed cache takes its accumulators from zero and has no such block).
   // They are loaded together with the first tile's raw data, so that the two global
   // latencies overlap (rows past the frame repeat its last row; their output is not stored).
   uint4* qbase = lds_q + (wave * kQSets * 4) * 64 + lane;
@@ -255,8 +263,19 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
         qbase[(1 * 4 + ks) * 64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
       }
     } else {
-      const uint4 q0 = *reinterpret_cast<const uint4*>(qrow), q1 = *reinterpret_cast<const uint4*>(qrow + 32);
-      const uint4 q2 = *reinterpret_cast<const uint4*>(qrow + 64), q3 = *reinterpret_cast<const uint4*>(qrow + 96);
+      uint4 q0 = *reinterpret_cast<const uint4*>(qrow), q1 = *reinterpret_cast<const uint4*>(qrow + 32);
+      uint4 q2 = *reinterpret_cast<const uint4*>(qrow + 64), q3 = *reinterpret_cast<const uint4*>(qrow + 96);
+      if constexpr (UNC) {
+        // (a word's lower half rides along in the upper one's significand and is cut off again)
+        auto scaled = [&](uint32_t w) __attribute__((always_inline)) {
+          return __builtin_amdgcn_perm(__float_as_uint(__uint_as_float(w) * q_factor), __float_as_uint(__uint_as_float(w << 16) * q_factor), 0x07060302u);
+        };
+        auto scaled4 = [&](uint4 q) __attribute__((always_inline)) { return make_uint4(scaled(q.x), scaled(q.y), scaled(q.z), scaled(q.w)); };
+        q0 = scaled4(q0);
+        q1 = scaled4(q1);
+        q2 = scaled4(q2);
+        q3 = scaled4(q3);
+      }
       qbase[0 * 64] = q0;
       qbase[1 * 64] = q1;
       qbase[2 * 64] = q2;
@@ -486,9 +505,6 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
       ah[i] = *reinterpret_cast<const bf16x8*>(lds_khi[kbuf] + aoff);
       if constexpr (!UNC) al[i] = *reinterpret_cast<const bf16x8*>(lds_klo[kbuf] + aoff);
     };
-    auto read_k1 = [&](int i) __attribute__((always_inline)) {
-      ah[i] = *reinterpret_cast<const bf16x8*>(lds_khi[kbuf] + ((i & 1) * 32 + l32) * kLdsRow + (i >> 1) * 16 + hf * 8);
-    };
     auto read_q = [&](int ks) __attribute__((always_inline)) {
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) qh[ks][nb] = __builtin_bit_cast(bf16x8, qbase[ks * 64]);
@@ -501,13 +517,13 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
       for (int r = 0; r < 16; ++r) zero[r] = 0.f;
       read_q(0);
 #pragma unroll
-      for (int i = 0; i < kAhead; ++i) read_k1(i);
+      for (int i = 0; i < kAhead; ++i) read_k(i);
       read_q(1);
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const int ks = i >> 1, mb = i & 1;
-        if (i + kAhead < 8) read_k1(i + kAhead);
+        if (i + kAhead < 8) read_k(i + kAhead);
         if (mb == 0 && ks + 2 < 4) read_q(ks + 2);
         s[mb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], qh[ks][0], ks == 0 ? zero : s[mb][0], 0, 0, 0);
       }
@@ -518,7 +534,7 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
 #pragma unroll
       for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[mb][0][r] = __builtin_fmaf(s[mb][0][r], sc, nm);
+        for (int r = 0; r < 16; ++r) s[mb][0][r] = __builtin_fmaf(s[mb][0][r], s_factor, nm);
     } else {
     read_q(0);
 #pragma unroll
@@ -623,7 +639,7 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
 #pragma unroll
           for (int r = 0; r < 16; ++r) s[mb][nb][r] -= delta;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) negm[nb][r] = -m_ref[nb];
+        for (int r = 0; r < 16 && !UNC; ++r) negm[nb][r] = -m_ref[nb];
       }
       probabilities();
     }

@@ -35,3 +35,29 @@ def test_tile_edges(n, splits, k_scale):
         ref = np.einsum("hqk,khd->qhd", p / p.sum(-1, keepdims=True), V)
         pu.check_output(out.cpu().numpy(), ref, f"n {n} frame {t}")
     h.close()
+
+
+def test_logits_near_the_top_of_fp32():
+    """Products of queries and keys beyond fp32's range whose scaled logits (times log2 e / 8) are inside it: rows are one-hot."""
+    import torch
+    import paper_2601_01204_amd as kvx
+    n, H, d, frames = 70, 2, 64, 3
+    rng = np.random.default_rng(77)
+    h = kvx.KvHandle(n_heads=H, tokens_per_frame=n, n_special=0, budget_tokens=frames * n, mode=kvx.KV_UNCOMPRESSED_BF16, max_frames=frames,
+                     out_dtype=kvx.KV_F32)
+    keys, values, overflowed = [], [], 0
+    for t in range(frames):
+        q, k, v = (torch.from_numpy((rng.standard_normal((n, H, d)) * s).astype(np.float32)).to("cuda:0").to(torch.bfloat16)
+                   for s in (2.0 ** 63, 2.0 ** 61, 1.0))
+        out = torch.empty((n, H, d), dtype=torch.float32, device="cuda:0")
+        h.step(q, k, v, out)
+        torch.cuda.synchronize()
+        keys.append(k.double().cpu().numpy())
+        values.append(v.double().cpu().numpy())
+        s = np.einsum("qhd,khd->hqk", q.double().cpu().numpy(), np.concatenate(keys))
+        overflowed += int((s.max(-1) > np.finfo(np.float32).max).sum())
+        best = s.argmax(-1)                                       # [H, n]
+        ref = np.stack([np.concatenate(values)[best[i], i] for i in range(H)], axis=1)
+        pu.check_output(out.cpu().numpy(), ref, f"frame {t}")
+    assert overflowed > n
+    h.close()
