@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 def test_maximum_budget():
-    """budget_tokens = 32768, the cap: 32248 middle tokens, so the selection kernel holds its full
-    32 keys per thread; the cache fills at the 64th frame and is pruned three times."""
+    """budget_tokens = 32768, the cap: 32248 middle tokens, whose keys take the selection kernel to 153.6 KB
+    of LDS; the cache fills at the 64th frame and is pruned three times."""
     w = si.Workload("max_budget", 2, 64, 520, 5, 16, 32768, 68, 1, 1, 4, 64, 4, 64, "bf16", 21)
     quiet = lambda *a, **k: None
     pu.run_stream(w, 67, check_every=9, log=quiet)

@@ -1,8 +1,8 @@
 """The three stream schedules of a step (option "overlap_update": 0 everything in order on the caller's stream,
 1 the library's choice, 2 the update chain on the library's second stream at any launch size) only reorder
 independent kernels: every one of them must leave bit-identical caches and outputs, on one cache per call (a launch
-that cannot fill the chip) and on a batch whose attention launch has more workgroup columns than the chip has compute
-units, in both layouts.  Schedule 1 of the same streams is compared with the oracle here as well."""
+that cannot fill the chip, short enough for schedule 1 to keep in order, and long enough for it to take the second
+stream) and on a batch whose attention launch has more workgroup columns than the chip has compute units, in both layouts.  Schedule 1 of the same streams is compared with the oracle here as well."""
 import numpy as np
 import pytest
 
@@ -36,10 +36,11 @@ def _same_export(a, b, what):
 
 
 @pytest.mark.parametrize("slots", [False, True])
-@pytest.mark.parametrize("n_layers", [1, 24])
-def test_every_schedule_gives_the_same_bits(n_layers, slots):
+@pytest.mark.parametrize("n_layers,heads,budget,frames", [(1, 16, 256, 8), (1, 2, 8192, 121), (24, 16, 256, 8)])
+def test_every_schedule_gives_the_same_bits(n_layers, heads, budget, frames, slots):
     import torch
-    w = _w(n_layers=n_layers)
+    # 8192 tokens of two heads in 16 key ranges: an estimate of 12 tile steps, above the 10 from which the second stream pays
+    w = _w(n_layers=n_layers, n_heads=heads, budget_tokens=budget, frames=frames)
     # 24 caches x 16 heads x 1 query tile = 384 workgroup columns: more than the 256 compute units
     handles = []
     for mode in (0, 1, 2):
@@ -49,7 +50,7 @@ def test_every_schedule_gives_the_same_bits(n_layers, slots):
     checked = (0, n_layers - 1) if n_layers > 1 else (0,)
     caches = {l: xo.OracleCache(pu.oracle_cfg(w, True, slots)) for l in checked}
     sig = [si.key_channel_scales(w, 0, l) for l in range(n_layers)]
-    for t in range(w.frames):                     # pruning starts at the fourth frame
+    for t in range(w.frames):                     # pruning starts at the fourth (119th) frame
         frames = [si.frame_qkv(w, t, 0, l, sig[l]) for l in range(n_layers)]
         dev = [tuple(pu.to_device(a, w) for a in f) for f in frames]
         refs = {l: caches[l].step(*frames[l]) for l in checked}
@@ -63,7 +64,7 @@ def test_every_schedule_gives_the_same_bits(n_layers, slots):
             a = outs[0][l].cpu().numpy().view(np.uint32)
             for m in (1, 2):
                 assert np.array_equal(a, outs[m][l].cpu().numpy().view(np.uint32)), f"frame {t} layer {l}: outputs of schedules 0 and {m} differ"
-        for l in checked:
+        for l in checked if budget < 1000 or t > 116 else ():
             pu.check_output(outs[1][l].cpu().numpy(), refs[l], f"frame {t} layer {l}")
             ex = [h.export(0, l) for h in handles]
             pu.check_state(ex[1], caches[l], f"frame {t} layer {l}")

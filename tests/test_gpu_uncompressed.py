@@ -61,3 +61,37 @@ def test_logits_near_the_top_of_fp32():
         pu.check_output(out.cpu().numpy(), ref, f"frame {t}")
     assert overflowed > n
     h.close()
+
+
+def test_several_caches_in_one_call():
+    """Two and three caches of one handle in a call, at different fill levels and one of them restarted."""
+    import torch
+    import paper_2601_01204_amd as kvx
+    n, H, d, frames = 67, 3, 64, 6
+    rng = np.random.default_rng(78)
+    h = kvx.KvHandle(n_streams=3, n_layers=1, n_heads=H, tokens_per_frame=n, n_special=0, budget_tokens=frames * n, mode=kvx.KV_UNCOMPRESSED_BF16,
+                     max_frames=frames, out_dtype=kvx.KV_F32)
+    past = {0: [], 1: [], 2: []}
+
+    def step(streams):
+        items, refs = [], []
+        for s in streams:
+            q, k, v = (torch.from_numpy(rng.standard_normal((n, H, d)).astype(np.float32)).to("cuda:0").to(torch.bfloat16) for _ in range(3))
+            items.append((s, 0, q, k, v, torch.empty((n, H, d), dtype=torch.float32, device="cuda:0")))
+            past[s].append((k.double().cpu().numpy(), v.double().cpu().numpy()))
+            K, V = (np.concatenate([kv[i] for kv in past[s]]) for i in (0, 1))
+            p = np.einsum("qhd,khd->hqk", q.double().cpu().numpy(), K) / np.sqrt(d)
+            p = np.exp(p - p.max(-1, keepdims=True))
+            refs.append(np.einsum("hqk,khd->qhd", p / p.sum(-1, keepdims=True), V))
+        h.step_batched(items)
+        torch.cuda.synchronize()
+        for it, ref in zip(items, refs):
+            pu.check_output(it[5].cpu().numpy(), ref, f"stream {it[0]} after {len(past[it[0]])} frames")
+
+    for streams in ((0,), (0, 1), (2, 0, 1), (1, 2)):
+        step(streams)
+    h.reset(0, 0)
+    past[0].clear()
+    for streams in ((0, 1, 2), (0, 2)):
+        step(streams)
+    h.close()

@@ -51,3 +51,34 @@ def test_wide_launches(n_heads, n, budget, k_bits, k_group, meta16, slots):
             pu.check_state(h.export(s, 0), caches[s], f"stream {s} frame {t}")
     assert wide >= 2
     h.close()
+
+
+@pytest.mark.parametrize("slots", [False, True])
+@pytest.mark.parametrize("k_bits,v_bits,meta16", [(k, v, m) for k in (2, 4, 8) for v in (2, 4, 8) for m in ((False, True) if k != 8 else (False,))])
+def test_key_and_value_rebuild_apart(k_bits, v_bits, meta16, slots):
+    """Key and value rebuild as launches of their own, which a call takes while either is timed (and above 32768
+    blocks), on one and on two caches a call, for every combination of code widths."""
+    import torch
+    k_group, v_group = (32, 64) if (k_bits + v_bits) % 4 else (64, 32)
+    w = si.Workload("apart", 3, 64, 45, 3, 8, 230, 8, 1, 2, k_bits, k_group, v_bits, v_group, "bf16", 53)
+    h = pu.make_handle(w, n_streams=2, meta_format=1 if meta16 else 0, layout=1 if slots else 0)
+    h.set_option("timing_every", 1)
+    h.set_timing(1 << 5)                      # the key rebuild
+    caches = [xo.OracleCache(pu.oracle_cfg(w, meta16, slots)) for _ in range(2)]
+    sigmas = [si.key_channel_scales(w, s, 0) for s in range(2)]
+    launches = 0
+    for t in range(w.frames):
+        items, refs = [], []
+        for s in range(2) if t != 2 else range(1):          # one cache alone once, so that the two lengths differ
+            q, k, v = si.frame_qkv(w, t, s, 0, sigmas[s])
+            refs.append((s, caches[s].step(q, k, v)))
+            dev = tuple(pu.to_device(a, w) for a in (q, k, v))
+            items.append((s, 0, *dev, torch.empty(dev[0].shape, dtype=torch.float32, device="cuda:0")))
+        h.step_batched(items)
+        torch.cuda.synchronize()
+        for (s, ref), it in zip(refs, items):
+            pu.check_output(it[5].cpu().numpy(), ref, f"stream {s} frame {t}")
+            pu.check_state(h.export(s, 0), caches[s], f"stream {s} frame {t}")
+        launches += 1
+    assert h.read_timing()["rebuild_k"][1] == launches
+    h.close()
