@@ -76,12 +76,13 @@ def alg_bytes(w, meta_bytes=8):
     k_meta = H * (L // w.k_group) * d * meta_bytes
     v_meta = H * L * (d // w.v_group) * meta_bytes
     return {
-        # middle key codes + their (s, z) read, D[h, j] written
-        "score": H * mid * d * kb / 8 + H * (mid // w.k_group) * d * meta_bytes + H * mid * 4,
+        # middle key codes + their (s, z) read, a score and its key written per token
+        "score": H * mid * d * kb / 8 + H * (mid // w.k_group) * d * meta_bytes + mid * 8,
         # survivors' key codes + (s, z) read, new frame read, next cache written
         "rebuild_k": 2 * (H * L * d * kb / 8 + k_meta) + n * H * d * 2,
         "rebuild_v": 2 * (H * L * d * vb / 8 + v_meta) + n * H * d * 2,
-        "select": H * mid * 4 + 6 * mid * 4 + L * 4,
+        # the scores' keys read, the keep list written
+        "select": mid * 4 + L * 4,
     }
 
 
@@ -134,7 +135,8 @@ class StackRun:
 
 
 def kernel_times(run, steps):
-    """Per-kernel durations with the cache update after attention on one stream (each kernel by itself)."""
+    """Per-kernel durations with everything in order on one stream (each kernel by itself; key and value rebuild are
+    launched apart while they are timed, which a call of up to 32768 rebuild blocks otherwise does in one launch)."""
     run.h.set_option("overlap_update", 0)
     run.h.set_option("timing_every", 1)
     run.h.set_timing(0x7F)
@@ -269,7 +271,7 @@ def aux_small_budgets(torch, kvx, si, dev, steps):
     needs frames of at most 1024 tokens (first and current frame are always kept), so it runs on 518 x 294 frames
     (782 tokens); 4096 and 8192 on 518 x 392 frames (1041 tokens)."""
     import dataclasses
-    out = {}
+    out = {"kernel_us": "timed kernel by kernel, with key and value rebuild launched apart; the timed steps launch them as one"}
     base = si.WORKLOADS["vggt_layer"]
     for n, L in ((782, 2048), (1041, 4096), (1041, 8192)):
         w = dataclasses.replace(base, tokens_per_frame=n, budget_tokens=L)

@@ -107,7 +107,7 @@ struct kv_handle {
   std::vector<int64_t> seen_in_call;   // per cache: the step call that last named it (duplicate check without a per-call allocation)
   int64_t call_id = 0;
   uint8_t* arena = nullptr;
-  uint8_t* work = nullptr;             // per-cache working memory (pooled query, dots, scores, keep list, counters)
+  uint8_t* work = nullptr;             // per-cache working memory (pooled query, scores, keep list, slot assignment, counters)
   void* static_scratch = nullptr;      // this device's address of the file-scope `scratch` array (kv_step_static)
   float* part_o = nullptr;
   float* part_ml = nullptr;
@@ -522,8 +522,9 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     // The cache-update chain runs next to attention on the library's second stream when attention alone cannot fill
     // the chip (fewer workgroup columns than compute units: one or a few caches per call).  The attention workgroups
     // of a launch that fills the chip hold every vector register of their compute units, so another kernel's
-    // workgroups only get a unit between two of them: there the chain follows attention on the caller's stream
-    // unless "overlap_update" 2 asks for the second stream at any size.  The slot layout's writers always follow
+    // workgroups only get a unit between two of them: there everything runs in order on the caller's stream, the chain in
+    // front of attention (both read the half that the step started from, the chain writes the other), unless
+    // "overlap_update" 2 asks for the second stream at any size.  The slot layout's writers always follow
     // attention (they update the buffer it reads); "overlap_update" 0, the uncompressed baseline and the update-first
     // order (attention reads what the update wrote) keep everything in order on the caller's stream.
     const bool may_overlap = h->overlap != 0 && h->side && !g0.uncompressed && !update_first;
