@@ -27,7 +27,7 @@ PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 # HBM bytes per launch of the dominant kernel come from a rocprofv3 --pmc run whose summary and figures are
 # tracked in profiles/; the file names the sources it was measured on, and a stale file yields traffic = null.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "attn_kernel_vggt_stack_traffic.json")
-KERNEL_SOURCES = ("attn.hip", "attn16.hip", "kvx_dev.h")
+KERNEL_SOURCES = ("attn.hip", "attn16.hip", "attn_tile.h", "kvx_dev.h")
 
 
 def kernel_source_hash() -> str:
@@ -443,7 +443,7 @@ def main():
                    "keys_per_step": L + n, "layers": NL, "attention_splits": args.splits or "auto"},
         "roofline": {"bound": "mfma", "achieved": round(achieved, 2), "peak": PEAK_MFMA_TFLOPS, "unit": "TFLOP/s",
                      "frac": round(achieved / PEAK_MFMA_TFLOPS, 4), "traffic": attention_traffic("vggt_stack", args.meta),
-                     "kernel": "attn16_kernel" if meta16 else "attn_kernel", "flops_per_launch": flops, "avg_launch_us": round(attn_s * 1e6, 2)},
+                     "kernel": "attn_tile_kernel", "flops_per_launch": flops, "avg_launch_us": round(attn_s * 1e6, 2)},
         "hbm_kernels": hbm_report(w, NL, us, 4 if meta16 else 8),
         "kernel_us": {k: round(v, 2) for k, v in us.items()},
         "kv_bytes": {"live_per_cache": st["bytes_live_per_cache"], "live_per_frame_step": st["bytes_live_per_cache"] * NL,

@@ -1,52 +1,23 @@
-// Attention of one frame's queries over [de-quantised cache ; the frame's own K/V]
-// (paper Sec. 3.1 Eq. 1 with the de-quantisation of Sec. 3.3 Eq. 10 fused in).
+// Attention over caches with fp32 metadata and uncompressed caches (the kernel of attn_tile.h), attention of fp32 inputs (the
+// kernel below) and the merge of split-KV partials.
 //
-// Work decomposition: a workgroup owns a tile of up to 12 32-row query blocks of one head
-// (the frame's blocks cut evenly over tiles), one block per wave, so 8 to 12 waves, and a
-// contiguous range of 64-key tiles (split-KV).  Per tile waves 0-3 de-quantise the K
-// codes and waves 4-7 the V codes once into LDS (K row-major, V transposed), then every
-// wave runs S^T = K Q^T and O^T += V^T P^T on the matrix cores with an online softmax in
-// registers.  Computing the transposed products puts a query in a lane and its keys in
-// that lane's registers, so the probabilities feed the second MFMA straight from
-// registers (the key order inside a 16-key step is a permutation shared by V^T's LDS
-// layout) and the row statistics stay in the lane.
+// fp32 inputs (paper Sec. 3.1 Eq. 1 with the de-quantisation of Sec. 3.3 Eq. 10 fused in).  Work decomposition: a workgroup owns
+// a tile of up to 12 32-row query blocks of one head (the frame's blocks cut evenly over tiles), one block per wave, so 8 to 12
+// waves, and a contiguous range of 64-key tiles (split-KV).  Per tile waves 0-3 de-quantise the K codes and waves 4-7 the V
+// codes once into LDS (K row-major, V transposed), then every wave runs S^T = K Q^T and O^T += V^T P^T on the matrix cores with
+// an online softmax in registers.
 //
-// Precision.  A de-quantised key s * (code - z) is an fp32 value; rounding it to 8
-// significand bits perturbs the logits of the dominant key channels by ~1e-2, far above
-// the output tolerance.  K~ is therefore held as a bf16 pair hi + lo (hi = truncation,
-// lo = truncated remainder, together 16 significand bits) and S^T takes two bf16 MFMAs
-// (v_mfma_f32_32x32x16_bf16) against the exact bf16 queries.  P and V~ go through the
-// f16 MFMA (v_mfma_f32_32x32x16_f16, 11 significand bits, same rate).  fp32 inputs are
-// split the same way (queries too).  The keys of an uncompressed cache and of a bf16 frame
-// are exact in one bf16 operand as long as the logit factor stays out of it: that kernel
-// (KB = VB = 16) takes one MFMA per step from a zero accumulator and applies the factor and
-// the softmax reference to the 32 x 64 logits by one fused operation each, which saves per
-// tile and wave 256 cycles of matrix work, 8 operand reads and the split in the staging: two
-// layers over their first 24 frames of 1041 tokens 4741 -> 3807 us.  It is also closer to Eq. 1
-// in 64 bits, which the key pairs' 16 bits are not exact for: relative error of fp32 outputs
-// 1.19e-4 -> 1.12e-4 (1041 tokens, 6 frames), 9.4e-5 -> 8.3e-5 (523, 10), 4.3e-5 -> 3.2e-5 (69, 12).  The compressed kernels
-// do not take that path for the frame's own tiles: with both forms in one kernel registers
-// spill (24 x 16384 tokens, 3207 -> 3300 us).
+// Precision.  Keys s * (code - z) and queries are held as bf16 pairs hi + lo (hi = truncation, lo = truncated remainder,
+// together 16 significand bits) and S^T takes three bf16 MFMAs (v_mfma_f32_32x32x16_bf16) per step.  P and V~ go through the f16
+// MFMA (v_mfma_f32_32x32x16_f16, 11 significand bits, same rate).  The queries' two fragment sets are why this kernel is not the
+// one of attn_tile.h: they would not fit its registers.
 //
-// Softmax.  The softmax scale times log2(e) is folded into the keys as they are staged,
-// so S^T is already in log2 units.  Each query keeps a reference m and p = 2^(s - m) is
-// formed without looking at the tile's maximum first: f16 holds p up to 2^16, and a key
-// further above m than that makes p, and so the row sum, infinite.  Only then (a rare,
-// wave-uniform branch) is m raised for every row whose largest key exceeds it by more
-// than kRescaleGap, O and l are rescaled and the tile's probabilities are formed again.
-//
-// Schedule.  A wave issues in order.  Measured on gfx950, its independent vector
-// instructions do run under its own MFMAs, but every 16-byte LDS operand read holds the
-// wave for about as long as it holds the SIMD's LDS return path (16 cycles), so a single
-// wave that interleaves its reads, MFMAs and softmax arithmetic gains little over doing
-// them one after the other; the overlap has to come from different waves of a SIMD being
-// in different phases.  A SIMD holds up to three waves of the workgroup (w, w + 4, w + 8),
-// each with the same matrix work; waves 0-3 compute a tile and then stage K of the next
-// one, waves 4-7 stage V first and then compute, waves 8-11 only compute, so their MFMA and
-// vector stretches fall at different times between two barriers.
-#include "kvx_dev.h"
-
-#include <hip/hip_ext.h>
+// Softmax.  The softmax scale times log2(e) is folded into the keys as they are staged, so S^T is already in log2 units.  Each
+// query keeps a reference m and p = 2^(s - m) is formed without looking at the tile's maximum first: f16 holds p up to 2^16,
+// and a key further above m than that makes p, and so the row sum, infinite.  Only then (a rare, wave-uniform branch) is m
+// raised for every row whose largest key exceeds it by more than kRescaleGap, O and l are rescaled and the tile's
+// probabilities are formed again.
+#include "attn_tile.h"
 
 #include <type_traits>
 #include <utility>
@@ -95,7 +66,6 @@ template <int B> struct Octet;
 template <> struct Octet<2> { typedef uint16_t type; };
 template <> struct Octet<4> { typedef uint32_t type; };
 template <> struct Octet<8> { typedef uint2 type; };
-template <> struct Octet<16> { typedef uint4 type; };      // bf16 rows (not loaded as codes)
 
 template <int B>
 __device__ __forceinline__ int octet_code(const typename Octet<B>::type& w, int e) {
@@ -138,7 +108,7 @@ __device__ __forceinline__ void octet_floats(const typename Octet<B>::type& w, f
 // selected), so the loads of a later tile stay in flight across the barriers.
 //   cached K tile : c = the two rows' codes, a[0..1] = the channels' scales, a[2..3] = zero-points
 //   cached V tile : c = codes, m = the two rows' (scale, zero-point)
-//   bf16 rows     : a[0], a[1] = the two rows (own frame, uncompressed cache)
+//   bf16 rows     : a[0], a[1] = the two rows (uncompressed cache)
 //   fp32 rows     : a[0..1] = first row, a[2..3] = second row (own frame)
 // Registers a tile does not use are loaded from a valid dummy address.
 template <int B>
@@ -161,32 +131,12 @@ __device__ __forceinline__ void pin_qk_steps(std::integer_sequence<int, I...>) {
   ((sched_group<0x100, ((I + AHEAD < 8) ? 2 : 0) + (((I & 1) == 0 && (I >> 1) + 2 < 4) ? NB + (F32 ? 1 : 0) : 0)>(),
     sched_group<0x008, (F32 ? 3 : 2) * NB>()), ...);
 }
-// The same for tiles whose keys are one bf16 operand: one K read and one MFMA per step.
-template <int AHEAD, int... I>
-__device__ __forceinline__ void pin_qk1_steps(std::integer_sequence<int, I...>) {
-  ((sched_group<0x100, ((I + AHEAD < 8) ? 1 : 0) + (((I & 1) == 0 && (I >> 1) + 2 < 4) ? 1 : 0)>(), sched_group<0x008, 1>()), ...);
-}
 
-// Linear block id -> (column, query tile), column = (item, split, head).  Workgroups go to the 8 XCDs round-robin by
-// id and each XCD has its own L2, so the query tiles of one column, which read the same K/V codes, get ids that are
-// multiples of 8 apart and next to each other in dispatch order: they run on one XCD at about the same time and the
-// second and third read of a tile is served by that XCD's L2 instead of HBM.  Columns are taken in groups of 8 (the
-// last group may be smaller): id = group * 8 * n_qtiles + qt * group_size + (column within the group).
-__device__ __forceinline__ void decode_block(int bid, int n_cols, int n_qtiles, int& col, int& qt) {
-  const int per_group = 8 * n_qtiles;
-  const int grp = bid / per_group;
-  const int rest = bid - grp * per_group;
-  const int gsize = min(8, n_cols - grp * 8);
-  qt = rest / gsize;
-  col = grp * 8 + (rest - qt * gsize);
-}
-
-// KB = VB = 16: the uncompressed bf16 cache with bf16 inputs (with fp32 inputs it goes through the F32IN kernels).
-template <int KB, int VB, bool F32IN, int N>
+template <int KB, int VB, int N>
 __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
   int bid, qt;
-  decode_block(blockIdx.x, g.H * g.n_splits * b.n_items, g.n_qtiles, bid, qt);
+  tile::decode_block(blockIdx.x, g.H * g.n_splits * b.n_items, g.n_qtiles, bid, qt);
   const int h = bid % g.H; bid /= g.H;
   const int split = bid % g.n_splits; bid /= g.n_splits;
   const int item_idx = bid;
@@ -198,10 +148,9 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
   const int hf = lane >> 5;
 
   __shared__ __attribute__((aligned(16))) uint16_t lds_khi[2][kTileElems];
-  constexpr bool UNC = KB == 16;
-  __shared__ __attribute__((aligned(16))) uint16_t lds_klo[UNC ? 1 : 2][UNC ? 8 : kTileElems];
+  __shared__ __attribute__((aligned(16))) uint16_t lds_klo[2][kTileElems];
   __shared__ __attribute__((aligned(16))) uint16_t lds_v[2][kTileElems];
-  constexpr int kQSets = F32IN ? 2 : 1;                   // bf16 queries: one fragment set; fp32: hi and lo
+  constexpr int kQSets = 2;                               // query fragments: hi and lo
   __shared__ uint4 lds_q[kAttnMaxWaves * kQSets * 4 * 64];   // waves x sets x 4 channel steps x 64 lanes
 
   const int n = g.n_new;                                  // query rows = the call's own keys: one frame, or a chunk of frames
@@ -214,13 +163,8 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
   const int tile_end = (int)(((int64_t)nt * (split + 1)) / g.n_splits);
 
   const uint8_t* half = cache_half(g, it.cache, it.cur);
-  const bool compressed = F32IN ? !g.uncompressed : !UNC;
+  const bool compressed = !g.uncompressed;
   const float sc = g.scale_log2;
-  // Uncompressed keys enter the product as they are, so it could leave fp32's range where the logit does not.  A factor below
-  // one is therefore taken in two parts: its power of two with the queries (exact, once per workgroup: 0.3 % of the two-layer
-  // clip above), the rest with the logits.
-  const int sc_exp = UNC ? max(min((int)(__float_as_uint(sc) >> 23) - 127, 0), -126) : 0;
-  const float q_factor = __uint_as_float((uint32_t)(127 + sc_exp) << 23), s_factor = UNC ? ldexpf(sc, -sc_exp) : sc;
   // Query rows of this wave: block `wave` of the tile's q_blocks 32-row blocks; a wave
   // without rows (fewer than 8 blocks in the tile, or a ragged last tile) only stages.
   constexpr int NB = 1;
@@ -234,9 +178,8 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
 
   // ---- this wave's query fragments (B operand of S^T = K Q^T) ---------------------
   // They live in a private LDS region of the wave, one 16-byte entry per lane and
-  // 16-channel step (fp32 input: a second set for the lo parts), and are re-read every
-  // tile: the registers they would occupy hold the -m block below instead (the kernel of the
-  // uncompressed cache takes its accumulators from zero and has no such block).
+  // 16-channel step and part, and are re-read every
+  // tile: the registers they would occupy hold the -m block below instead.
   // They are loaded together with the first tile's raw data, so that the two global
   // latencies overlap (rows past the frame repeat its last row; their output is not stored).
   uint4* qbase = lds_q + (wave * kQSets * 4) * 64 + lane;
@@ -244,8 +187,8 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
     if (!nblk) return;
     const int qi = min(row0 + l32, n - 1);
     const uint8_t* qrow = reinterpret_cast<const uint8_t*>(it.q) +
-                          ((int64_t)qi * g.tok_stride + (int64_t)h * g.head_stride + hf * 8) * (F32IN ? 4 : 2);
-    if constexpr (F32IN) {
+                          ((int64_t)qi * g.tok_stride + (int64_t)h * g.head_stride + hf * 8) * 4;
+    {
       uint4 a[4], c[4];
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
@@ -262,24 +205,6 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
         qbase[(0 * 4 + ks) * 64] = make_uint4(hi[0], hi[1], hi[2], hi[3]);
         qbase[(1 * 4 + ks) * 64] = make_uint4(lo[0], lo[1], lo[2], lo[3]);
       }
-    } else {
-      uint4 q0 = *reinterpret_cast<const uint4*>(qrow), q1 = *reinterpret_cast<const uint4*>(qrow + 32);
-      uint4 q2 = *reinterpret_cast<const uint4*>(qrow + 64), q3 = *reinterpret_cast<const uint4*>(qrow + 96);
-      if constexpr (UNC) {
-        // (a word's lower half rides along in the upper one's significand and is cut off again)
-        auto scaled = [&](uint32_t w) __attribute__((always_inline)) {
-          return __builtin_amdgcn_perm(__float_as_uint(__uint_as_float(w) * q_factor), __float_as_uint(__uint_as_float(w << 16) * q_factor), 0x07060302u);
-        };
-        auto scaled4 = [&](uint4 q) __attribute__((always_inline)) { return make_uint4(scaled(q.x), scaled(q.y), scaled(q.z), scaled(q.w)); };
-        q0 = scaled4(q0);
-        q1 = scaled4(q1);
-        q2 = scaled4(q2);
-        q3 = scaled4(q3);
-      }
-      qbase[0 * 64] = q0;
-      qbase[1 * 64] = q1;
-      qbase[2 * 64] = q2;
-      qbase[3 * 64] = q3;
     }
   };
 
@@ -358,30 +283,22 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
         const int trow = (tile - ntc) * kTileK;
         const int lim = n - 1 - trow;                                   // rows past the frame are zeroed when decoded
         const uint32_t r0 = (uint32_t)min(key_a, lim), r1 = (uint32_t)min(key_a + 1, lim);
-        constexpr uint32_t elt = F32IN ? 4 : 2;
+        constexpr uint32_t elt = 4;
         ba = reinterpret_cast<const uint8_t*>(ROLE_K ? it.k : it.v) + ((int64_t)trow * g.tok_stride + (int64_t)h * g.head_stride) * elt;
         const uint32_t ts = (uint32_t)g.tok_stride;
         const uint32_t q0 = (r0 * ts + co * 8) * elt, q1 = (r1 * ts + co * 8) * elt;
-        if constexpr (F32IN) {
-          oa0 = q0; oa1 = q0 + 16; oa2 = q1; oa3 = q1 + 16;
-        } else {
-          oa0 = q0; oa1 = q1; oa2 = oa3 = q0;
-        }
+        oa0 = q0; oa1 = q0 + 16; oa2 = q1; oa3 = q1 + 16;
       }
       bz = bc = bm = ba;
       oc0 = oc1 = om0 = om1 = oa0;
     }
-    if constexpr (!UNC) {
-      raw.c[0] = *reinterpret_cast<const CodeT*>(bc + oc0);
-      raw.c[1] = *reinterpret_cast<const CodeT*>(bc + oc1);
-    }
+    raw.c[0] = *reinterpret_cast<const CodeT*>(bc + oc0);
+    raw.c[1] = *reinterpret_cast<const CodeT*>(bc + oc1);
     raw.a[0] = *reinterpret_cast<const uint4*>(ba + oa0);
     raw.a[1] = *reinterpret_cast<const uint4*>(ba + oa1);
-    if constexpr ((ROLE_K && !UNC) || F32IN) {
-      raw.a[2] = *reinterpret_cast<const uint4*>(bz + oa2);
-      raw.a[3] = *reinterpret_cast<const uint4*>(bz + oa3);
-    }
-    if constexpr (!ROLE_K && !UNC) {
+    raw.a[2] = *reinterpret_cast<const uint4*>(bz + oa2);
+    raw.a[3] = *reinterpret_cast<const uint4*>(bz + oa3);
+    if constexpr (!ROLE_K) {
       raw.m[0] = *reinterpret_cast<const uint2*>(bm + om0);
       raw.m[1] = *reinterpret_cast<const uint2*>(bm + om1);
     }
@@ -405,7 +322,7 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
   // De-quantise / convert the raw registers of `tile` into LDS buffer `buf`.
   auto decode_store = [&](auto rolec, const auto& raw, int tile, int buf) __attribute__((always_inline)) {
     constexpr bool ROLE_K = decltype(rolec)::value;
-    if constexpr (!UNC) if (tile < ntc && compressed) {
+    if (tile < ntc && compressed) {
       // s * (code - z) evaluated as fma(code, s, -z * s): one conversion and one fused
       // operation per value (the result differs from Eq. 10's by a rounding of z * s, far
       // below what the bf16 pair or the f16 value keeps)
@@ -449,18 +366,9 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
       int base_row, limit;
       if (tile < ntc) { base_row = tile * kTileK; limit = t_c; } else { base_row = (tile - ntc) * kTileK; limit = n; }
       const bool ok0 = base_row + key_a < limit, ok1 = base_row + key_a + 1 < limit;
-      if constexpr (ROLE_K && UNC) {
-        // bf16 keys as they are, the logit factor is applied to their logits
-        uint4 r0 = raw.a[0], r1 = raw.a[1];
-        if (!ok0) r0 = make_uint4(0, 0, 0, 0);
-        if (!ok1) r1 = make_uint4(0, 0, 0, 0);
-        *reinterpret_cast<uint4*>(lds_khi[buf] + key_a * kLdsRow + co * 8) = r0;
-        *reinterpret_cast<uint4*>(lds_khi[buf] + (key_a + 1) * kLdsRow + co * 8) = r1;
-        return;
-      }
       float x0[8], x1[8];
-      if (F32IN && tile >= ntc) {
-        if constexpr (F32IN) {
+      if (tile >= ntc) {
+        {
           const uint32_t r0[8] = {raw.a[0].x, raw.a[0].y, raw.a[0].z, raw.a[0].w, raw.a[1].x, raw.a[1].y, raw.a[1].z, raw.a[1].w};
           const uint32_t r1[8] = {raw.a[2].x, raw.a[2].y, raw.a[2].z, raw.a[2].w, raw.a[3].x, raw.a[3].y, raw.a[3].z, raw.a[3].w};
 #pragma unroll
@@ -503,39 +411,14 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
       const int ks = i >> 1, mb = i & 1;
       const int aoff = (mb * 32 + l32) * kLdsRow + ks * 16 + hf * 8;
       ah[i] = *reinterpret_cast<const bf16x8*>(lds_khi[kbuf] + aoff);
-      if constexpr (!UNC) al[i] = *reinterpret_cast<const bf16x8*>(lds_klo[kbuf] + aoff);
+      al[i] = *reinterpret_cast<const bf16x8*>(lds_klo[kbuf] + aoff);
     };
     auto read_q = [&](int ks) __attribute__((always_inline)) {
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) qh[ks][nb] = __builtin_bit_cast(bf16x8, qbase[ks * 64]);
-      if constexpr (F32IN) ql[ks] = __builtin_bit_cast(bf16x8, qbase[(1 * 4 + ks) * 64]);
+      ql[ks] = __builtin_bit_cast(bf16x8, qbase[(1 * 4 + ks) * 64]);
     };
-    if constexpr (UNC) {
-      // bf16 keys, unscaled: one MFMA per step
-      f32x16 zero;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) zero[r] = 0.f;
-      read_q(0);
-#pragma unroll
-      for (int i = 0; i < kAhead; ++i) read_k(i);
-      read_q(1);
-      __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int ks = i >> 1, mb = i & 1;
-        if (i + kAhead < 8) read_k(i + kAhead);
-        if (mb == 0 && ks + 2 < 4) read_q(ks + 2);
-        s[mb][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], qh[ks][0], ks == 0 ? zero : s[mb][0], 0, 0, 0);
-      }
-      sched_group<0x100, kAhead + 2>();
-      pin_qk1_steps<kAhead>(std::make_integer_sequence<int, 8>{});
-      __builtin_amdgcn_s_setprio(0);
-      const float nm = -m_ref[0];
-#pragma unroll
-      for (int mb = 0; mb < 2; ++mb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) s[mb][0][r] = __builtin_fmaf(s[mb][0][r], s_factor, nm);
-    } else {
+    {
     read_q(0);
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) read_k(i);
@@ -551,12 +434,12 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
         if (ks == 0) s[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], qh[ks][nb], negm[nb], 0, 0, 0);
         else s[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], qh[ks][nb], s[mb][nb], 0, 0, 0);
         s[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al[i], qh[ks][nb], s[mb][nb], 0, 0, 0);
-        if constexpr (F32IN) s[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], ql[ks], s[mb][nb], 0, 0, 0);
+        s[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah[i], ql[ks], s[mb][nb], 0, 0, 0);
       }
     }
     // pin the order: the initial reads, then per step the reads issued for later steps and its MFMAs
-    sched_group<0x100, 2 * kAhead + 2 * NB + (F32IN ? 2 : 0)>();
-    pin_qk_steps<NB, F32IN, kAhead>(std::make_integer_sequence<int, 8>{});
+    sched_group<0x100, 2 * kAhead + 2 * NB + 2>();
+    pin_qk_steps<NB, true, kAhead>(std::make_integer_sequence<int, 8>{});
     __builtin_amdgcn_s_setprio(0);
     }
 
@@ -639,7 +522,7 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
 #pragma unroll
           for (int r = 0; r < 16; ++r) s[mb][nb][r] -= delta;
 #pragma unroll
-        for (int r = 0; r < 16 && !UNC; ++r) negm[nb][r] = -m_ref[nb];
+        for (int r = 0; r < 16; ++r) negm[nb][r] = -m_ref[nb];
       }
       probabilities();
     }
@@ -804,24 +687,20 @@ static void launch_attn_t(const KvxBatch& b, hipStream_t st, hipEvent_t ev_start
   const Geometry& g = b.g;
   dim3 grid(g.n_qtiles * g.H * b.n_items * g.n_splits);
   const dim3 block(64 * (g.q_blocks > 8 ? g.q_blocks : 8));      // a wave per query block, at least the 8 staging waves
-  // with events: the runtime stamps them at the kernel's own start and end (what a kernel trace reports)
-  if constexpr (KB == 16) {
-    if (ev_start) with_batch(b, [&](const auto& bb) { hipExtLaunchKernelGGL((attn_kernel<KB, VB, false, KVX_ITEMS(bb)>), grid, block, 0, st, ev_start, ev_stop, 0, bb); });
-    else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((attn_kernel<KB, VB, false, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
-  } else if (ev_start) {
-    if (g.in_f32) with_batch(b, [&](const auto& bb) { hipExtLaunchKernelGGL((attn_kernel<KB, VB, true, KVX_ITEMS(bb)>), grid, block, 0, st, ev_start, ev_stop, 0, bb); });
-    else with_batch(b, [&](const auto& bb) { hipExtLaunchKernelGGL((attn_kernel<KB, VB, false, KVX_ITEMS(bb)>), grid, block, 0, st, ev_start, ev_stop, 0, bb); });
-  } else {
-    if (g.in_f32) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((attn_kernel<KB, VB, true, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
-    else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((attn_kernel<KB, VB, false, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
-  }
+  if (ev_start) with_batch(b, [&](const auto& bb) { hipExtLaunchKernelGGL((attn_kernel<KB, VB, KVX_ITEMS(bb)>), grid, block, 0, st, ev_start, ev_stop, 0, bb); });
+  else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((attn_kernel<KB, VB, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
 }
 
 void launch_attention(const KvxBatch& b, int /*max_tiles*/, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (b.g.uncompressed && !b.g.in_f32) { launch_attn_t<16, 16>(b, st, ev_start, ev_stop); return; }
+  if (b.g.uncompressed && !b.g.in_f32) { tile::launch_tile<tile::kBf16, 16, 16>(b, st, ev_start, ev_stop); return; }
   // fp32 inputs over an uncompressed cache: the code widths play no part
   const int kb = b.g.uncompressed ? 4 : b.g.k_bits, vb = b.g.uncompressed ? 4 : b.g.v_bits;
-#define KVX_CASE(K, V) if (kb == K && vb == V) { launch_attn_t<K, V>(b, st, ev_start, ev_stop); return; }
+#define KVX_CASE(K, V) \
+  if (kb == K && vb == V) { \
+    if (b.g.in_f32) launch_attn_t<K, V>(b, st, ev_start, ev_stop); \
+    else tile::launch_tile<tile::kMeta32, K, V>(b, st, ev_start, ev_stop); \
+    return; \
+  }
   KVX_CASE(4, 4) KVX_CASE(8, 8) KVX_CASE(2, 4) KVX_CASE(2, 2) KVX_CASE(4, 8) KVX_CASE(8, 4) KVX_CASE(4, 2) KVX_CASE(2, 8) KVX_CASE(8, 2)
 #undef KVX_CASE
 }

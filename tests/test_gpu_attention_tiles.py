@@ -1,0 +1,53 @@
+"""The attention kernels at the edges of their tiling, against the oracle: one to twelve query blocks a workgroup (waves
+with no, one and two blocks), a last block of one row, cache ends on and off a tile, key ranges that begin and end in the
+cache, at its ragged last tile and in the frame's own keys, and logits that outgrow the softmax reference of earlier keys."""
+import numpy as np
+import pytest
+
+import synth_inputs as si
+from oracle import xstream_oracle as xo
+from tests import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+
+def run(w, frames, splits, meta16, grow=1.0, dtype="bf16"):
+    import torch
+    h = pu.make_handle(w, meta_format=1 if meta16 else 0)
+    h.set_option("attention_splits", splits)
+    cache = xo.OracleCache(pu.oracle_cfg(w, meta16))
+    sigma = si.key_channel_scales(w, 0, 0)
+    for t in range(frames):
+        q, k, v = si.frame_qkv(w, t, 0, 0, sigma)
+        k = (k * np.float32(grow ** t)).astype(np.float32)        # a power of two: still bf16 values
+        ref = cache.step(q, k, v)
+        tq, tk, tv = (pu.to_device(a, w) for a in (q, k, v))
+        out = torch.empty(tq.shape, dtype=torch.float32, device=tq.device)
+        h.step(tq, tk, tv, out)
+        torch.cuda.synchronize()
+        pu.check_output(out.cpu().numpy(), ref, f"n {w.tokens_per_frame} splits {splits} frame {t}")
+    h.close()
+
+
+@pytest.mark.parametrize("meta16", [True, False])
+@pytest.mark.parametrize("n,budget", [(1, 5), (31, 64), (33, 70), (64, 192), (128, 320), (129, 390), (225, 512), (256, 513), (257, 640),
+                                      (289, 600), (352, 1000), (384, 768), (385, 800)])
+@pytest.mark.parametrize("splits", [1, 5])
+def test_query_blocks_and_key_ranges(n, budget, splits, meta16):
+    w = si.Workload("tiles", 2, 64, n, min(1, n - 1), 16, budget, 4, 1, 1, 4, 64, 4, 64, "bf16", 61)
+    run(w, 4, splits, meta16)
+
+
+@pytest.mark.parametrize("meta16", [True, False])
+@pytest.mark.parametrize("n,budget,splits", [(70, 300, 1), (300, 1300, 1), (300, 1300, 2)])
+def test_logits_outgrow_the_reference(n, budget, splits, meta16):
+    """Keys eight times those of the frame before: a later tile's logits exceed the first tile's by far more than the 16 log2
+    units that half-precision probabilities hold, in cached tiles and in the frame's own (every path that raises the reference)."""
+    w = si.Workload("grow", 2, 64, n, 1, 16, budget, 4, 1, 1, 4, 64, 4, 64, "bf16", 62)
+    run(w, 4, splits, meta16, grow=8.0)
+
+
+@pytest.mark.parametrize("k_bits,k_group,v_bits,v_group", [(4, 32, 2, 32), (2, 64, 8, 64), (2, 32, 8, 32), (4, 64, 8, 32)])
+def test_code_widths(k_bits, k_group, v_bits, v_group):
+    w = si.Workload("widths", 3, 64, 290, 2, 16, 1111, 5, 1, 1, k_bits, k_group, v_bits, v_group, "bf16", 63)
+    run(w, 5, 2, True)
