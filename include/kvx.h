@@ -298,13 +298,15 @@ int kv_read_timing(kv_handle* h, float* total_ms, int32_t* launches);
  *                                 time each, so a benchmark samples them rather than paying them per step
  *   "debug_checks"                1: every step first scans q, k and v for infinities and NaNs
  *                                 and reports them through kv_stats (nonfinite_flag); 0 (default)
- *   "overlap_update"              1 (default): when attention alone cannot fill the chip (one or
- *                                 a few caches per call) and is long enough to repay the fork and
+ *   "overlap_update"              1 (default): a call on one cache of bf16 inputs (of more than
+ *                                 n_cus / 16 heads x query tiles) scores and selects inside
+ *                                 the attention launch; otherwise, when attention alone cannot fill the
+ *                                 chip (one or a few caches per call) and is long enough to repay the fork and
  *                                 join (about 40 us of host time a call), scoring, pruning and re-quantisation
  *                                 run on a second stream of the library next to attention,
  *                                 joined back into hip_stream before kv_step returns (slot
  *                                 layout: pooling, scoring and selection do; its writers always
- *                                 follow attention); 2: the same at any launch size, which a call
+ *                                 follow attention); 2: the second stream at any launch size, which a call
  *                                 whose host time does not count (recorded into a graph, or issued
  *                                 while the GPU has other work) gains from somewhat earlier: 523 tokens
  *                                 at a budget of 2048 take 53 us of GPU time and 60 in order, 400 at

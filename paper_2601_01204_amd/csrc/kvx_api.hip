@@ -390,7 +390,7 @@ int kv_init(const kv_config* cfg, kv_handle** out) {
     const int tiles_max = (g.t_cap + kTileK - 1) / kTileK + (gf.n_new + kTileK - 1) / kTileK;
     for (int items = 1; items <= std::min<int64_t>(kMaxItems, n_caches); ++items)
       for (int tiles = tiles_max; tiles >= 1; tiles = tiles > 1 ? (tiles + 1) / 2 : 0)
-        for (int target : {h->target_wgs, cus}) {
+        for (int target : {h->target_wgs, cus, std::max(1, cus - kSideBlocks)}) {
           const int sp = pick_splits(h, gf, items, tiles, target);
           rows_cap = std::max(rows_cap, (int64_t)items * sp * gf.n_pad);
         }
@@ -539,9 +539,17 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     // cache of 16384 tokens (523 tokens a frame, 6 heads) takes 107 us a step in order and 82 beside.
     double steps = 0.0;
     pick_splits(h, b.g, cnt, max_tiles, h->n_cus, &steps);
-    const bool beside = may_overlap && (h->overlap == 2 || (small_launch && (steps == 0.0 || steps >= kOverlapSteps)));
-    // a small launch leaves a quarter of the compute units to the chain next to it
-    b.g.n_splits = pick_splits(h, b.g, cnt, min_tiles, ((beside && small_launch) || h->target_explicit) ? h->target_wgs : h->n_cus);
+    // One cache that prunes, with more columns than kMaxSplits of them fill the units: scoring and selection ride in the attention
+    // launch (its first workgroups), and the step is a handful of launches on the caller's stream.  us a step against the rules
+    // above (second stream, or in order): 24 layers of 782 tokens at a budget of 2048, one call each, 58 -> 42; 1041 tokens at
+    // 4096 63 -> 52, at 8192 93 -> 88; four frames of 1041 at 8192 263 -> 264.  With fewer columns attention leaves most of the
+    // chip idle whatever the split, and the rules above stand.
+    const int side_blocks = side_blocks_of(b, max_tc);
+    const bool inside = may_overlap && h->overlap == 1 && small_launch && any_prune && side_blocks > 0 &&
+                        (int64_t)g0.H * b.g.n_qtiles * kMaxSplits > h->n_cus;
+    const bool beside = may_overlap && !inside && (h->overlap == 2 || (small_launch && (steps == 0.0 || steps >= kOverlapSteps)));
+    // a small launch leaves a quarter of the compute units to the chain next to it, or a unit to each of the scoring blocks in it
+    b.g.n_splits = pick_splits(h, b.g, cnt, min_tiles, ((beside && small_launch) || h->target_explicit) ? h->target_wgs : inside ? std::max(1, h->n_cus - side_blocks) : h->n_cus);
     // never more splits than the partial-result buffers hold (an explicit "attention_splits" may ask for more)
     b.g.n_splits = (int32_t)std::max<int64_t>(1, std::min<int64_t>(b.g.n_splits, rows_cap / ((int64_t)cnt * b.g.n_pad)));
 
@@ -552,9 +560,13 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
       sb = h->side;
     }
     // the slot layout is updated in place: its writers follow attention, which reads the same buffer
-    const bool rebuild_after = g0.slots && !update_first;
+    const bool rebuild_after = (g0.slots && !update_first) || inside;
+    // (while the parts are timed they are launched one by one)
+    if (inside && !h->timing_now) b.g.side_blocks = side_blocks;
     if (!g0.uncompressed) {
-      if (any_prune) {
+      if (b.g.side_blocks) {
+        launch_pool(b, max_tc, st);
+      } else if (any_prune) {
         record(h, KV_K_POOL, true, sb);
         launch_pool(b, max_tc, sb);
         record(h, KV_K_POOL, false, sb);

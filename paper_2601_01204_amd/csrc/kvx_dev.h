@@ -49,7 +49,7 @@ struct ScratchLayout {
   int64_t keep;       // [t_cap] int32: kept positions, ascending
   int64_t newtok;     // [t_cap] int32, slot layout: index of the call's token a slot receives, -1 for a slot whose token stays
   int64_t assign;     // [tokens of the largest call] int32, slot layout: slot of the call's i-th token
-  int64_t sel;        // [16] int32: [0] first dropped position, [1] first rebuilt key group, [2] groups rebuilt (running), [3] kept middle tokens, [5] groups quantised with a zero-point beyond +-2^20 (running), [6] non-finite input seen (debug checks)
+  int64_t sel;        // [16] int32: [0] first dropped position, [1] first rebuilt key group, [2] groups rebuilt (running), [3] kept middle tokens, [5] groups quantised with a zero-point beyond +-2^20 (running), [6] non-finite input seen (debug checks), [7] scoring blocks of an attention launch that have finished (0 between launches)
   int64_t bytes;
 };
 
@@ -88,6 +88,7 @@ struct Geometry {
   int32_t meta16;         // 1: 16-bit scales and zero-points
   int32_t slots;          // 1: slot-stable layout (one buffer, tokens never move), 0: compacting double buffer
   int32_t n_cus;          // compute units of the device
+  int32_t side_blocks;    // workgroups in front of a one-cache attention launch that score and select (0: launches of their own)
 };
 
 struct Item {
@@ -144,6 +145,16 @@ inline int score_blocks(const KvxBatch& b, int max_tc) {
 constexpr int kMeanRows = 128;      // pooled rows brought into LDS at a time
 inline bool mean_in_score(const KvxBatch& b, int max_tc) {
   return score_blocks(b, max_tc) * b.n_items <= b.g.n_cus && b.g.n_pooled * (b.g.n_new / b.g.n) <= kMeanRows;
+}
+
+// Scoring workgroups inside a one-cache attention launch (0: the launch cannot carry them: several caches, fp32 inputs).  Each
+// takes positions in turn and holds a compute unit meanwhile, so that few are better as long as they and the selection are done
+// before attention is.
+constexpr int kSideBlocks = 16;
+inline int side_blocks_of(const KvxBatch& b, int max_tc) {
+  if (b.n_items != 1 || b.g.in_f32 || b.g.uncompressed) return 0;
+  const int blocks = score_blocks(b, max_tc);
+  return blocks < kSideBlocks ? blocks : kSideBlocks;
 }
 
 // Waves of a scoring block, which take turns over the heads.  Up to a block per compute unit latency counts: all of 16 heads
