@@ -18,6 +18,7 @@
 // raised for every row whose largest key exceeds it by more than kRescaleGap, O and l are rescaled and the tile's
 // probabilities are formed again.
 #include "attn_tile.h"
+#include "combine_block.h"
 
 #include <type_traits>
 #include <utility>
@@ -636,50 +637,10 @@ __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatch
   }
 }
 
-// Merge the split-KV partials: out = sum_s w_s O_s / sum_s w_s l_s, w_s = 2^(m_s - max m).
 template <int N>
 __global__ __launch_bounds__(256) void combine_kernel(const KvxBatchT<N> b) {
-  const Geometry& g = b.g;
   const Item it = b.items[blockIdx.z];
-  const int h = blockIdx.y;
-  const int qi = blockIdx.x * 16 + (threadIdx.x >> 4);
-  const int c = (threadIdx.x & 15) * 4;
-  if (qi >= g.n_new) return;
-  // all partials are requested before any is used
-  const int64_t row0 = ((int64_t)blockIdx.z * g.n_splits * g.H + h) * g.n_pad + qi;
-  const int64_t row_step = (int64_t)g.H * g.n_pad;
-  float2 ml[kMaxSplits];
-  float4 po[kMaxSplits];
-#pragma unroll
-  for (int s = 0; s < kMaxSplits; ++s) {
-    if (s < g.n_splits) {
-      const int64_t row = row0 + s * row_step;
-      ml[s] = *reinterpret_cast<const float2*>(g.part_ml + row * 2);
-      po[s] = *reinterpret_cast<const float4*>(g.part_o + row * kHeadDim + c);
-    }
-  }
-  float m_max = kNegBig;
-#pragma unroll
-  for (int s = 0; s < kMaxSplits; ++s)
-    if (s < g.n_splits) m_max = fmaxf(m_max, ml[s].x);
-  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  float l = 0.f;
-#pragma unroll
-  for (int s = 0; s < kMaxSplits; ++s) {
-    if (s < g.n_splits) {
-      const float w = __builtin_amdgcn_exp2f(ml[s].x - m_max);
-      acc.x += w * po[s].x; acc.y += w * po[s].y; acc.z += w * po[s].z; acc.w += w * po[s].w;
-      l += w * ml[s].y;
-    }
-  }
-  const float inv = 1.0f / l;
-  const int64_t off = (int64_t)qi * g.out_tok_stride + (int64_t)h * g.out_head_stride + c;
-  if (g.out_f32) {
-    *reinterpret_cast<float4*>(reinterpret_cast<float*>(it.out) + off) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
-  } else {
-    *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(it.out) + off) =
-        make_uint2(pack_bf16(acc.x * inv, acc.y * inv), pack_bf16(acc.z * inv, acc.w * inv));
-  }
+  combine_block<kMaxSplits>(b.g, it, blockIdx.z, blockIdx.y, blockIdx.x);
 }
 
 template <int KB, int VB>
@@ -708,7 +669,7 @@ void launch_attention(const KvxBatch& b, int /*max_tiles*/, hipStream_t st, hipE
 void launch_combine(const KvxBatch& b, hipStream_t st) {
   const Geometry& g = b.g;
   if (g.n_splits <= 1) return;
-  dim3 grid((g.n_new + 15) / 16, g.H, b.n_items);
+  dim3 grid((g.n_new + kCombineRows - 1) / kCombineRows, g.H, b.n_items);
   with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((combine_kernel<KVX_ITEMS(bb)>), grid, dim3(256), 0, st, bb); });
 }
 

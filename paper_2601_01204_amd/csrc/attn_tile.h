@@ -40,8 +40,7 @@
 //
 // Domain: |k * softmax scale * log2 e| (16-bit metadata) and |v| below 65504 (the half range), finite inputs.
 #pragma once
-#include "score_block.h"
-#include "select_block.h"
+#include "score_select.h"
 
 #include <hip/hip_ext.h>
 
@@ -188,35 +187,6 @@ __device__ __forceinline__ void decode_block(int bid, int n_cols, int n_qtiles, 
 }
 
 template <int I> using Int = std::integral_constant<int, I>;
-
-// Scoring and selection inside a one-cache attention launch.  Both only read what attention reads, and in launches of their own
-// they take 4 and 8 to 20 us of one chip that is mostly idle, before attention or, on a second stream, beside it at the price
-// of two event records and waits (40 us of issue a call).  Here the first g.side_blocks workgroups of the launch share the
-// scoring blocks of the cache, and the one that finishes last selects.  Nobody waits for anybody: a block that is not the last
-// one leaves.  Each block's stores are released once by its first thread, so that no more than kSideBlocks of them write an
-// XCD's cache back.
-// Against the second stream, us a step: 782 tokens at a budget of 2048 58 -> 42, 1041 at 4096 63 -> 52, at 8192 93 -> 88.
-template <int KB>
-__device__ __forceinline__ void side_block(const Geometry& g, const Item& it, void* lds) {
-  float* rows = reinterpret_cast<float*>(lds);
-  float* mean = rows + kMeanRows * kHeadDim;
-  const float qc = pooled_mean(g, it, rows, mean);
-  const int first = g.n / 64, blocks = (it.t_c + 63) / 64 - first;
-  for (int x = blockIdx.x; x < blocks; x += g.side_blocks) {
-    __syncthreads();                          // the dots of the positions before have been read
-    score_block<KB>(g, it, (first + x) * 64, mean + kHeadDim, [&]() { return qc; });
-  }
-  int32_t* done = reinterpret_cast<int32_t*>(cache_scratch(g, it.cache) + g.sl.sel) + 7;
-  __shared__ int ticket;
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // every wave's scores have left it before the first thread releases them
-  __syncthreads();
-  if (threadIdx.x == 0) ticket = __hip_atomic_fetch_add(done, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-  __syncthreads();
-  if (ticket != g.side_blocks - 1) return;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  if (threadIdx.x == 0) __hip_atomic_store(done, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  select_cache<kThreads>(g, it, reinterpret_cast<int*>(lds));
-}
 #define KVX_PIN() __builtin_amdgcn_sched_barrier(0)
 
 template <Format FMT, int KB, int VB, int N>
@@ -231,7 +201,7 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
   if constexpr (kSide) {
     side = g.side_blocks;
     if ((int)blockIdx.x < side) {
-      side_block<KB>(g, b.items[0], lds);
+      score_and_select<KB, kThreads>(g, b.items[0], blockIdx.x, side, lds);
       return;
     }
   }

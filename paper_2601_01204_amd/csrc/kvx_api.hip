@@ -560,8 +560,11 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
       sb = h->side;
     }
     // the slot layout is updated in place: its writers follow attention, which reads the same buffer
-    const bool rebuild_after = (g0.slots && !update_first) || inside;
+    // so do those of everything in order: there they share a launch with the merge of attention's partial results
+    const bool rebuild_after = !g0.uncompressed && !update_first && (g0.slots || sb == st);
     // (while the parts are timed they are launched one by one)
+    b.g.merge = rebuild_after && !h->timing_now;
+    b.g.score_selects = selects_in_score(b, max_tc) && !h->timing_now;
     if (inside && !h->timing_now) b.g.side_blocks = side_blocks;
     if (!g0.uncompressed) {
       if (b.g.side_blocks) {
@@ -603,9 +606,11 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
         launch_attention(b, 0, st, e0, e1);
       }
     }
-    record(h, KV_K_COMBINE, true, st);
-    launch_combine(b, st);
-    record(h, KV_K_COMBINE, false, st);
+    if (!b.g.merge) {
+      record(h, KV_K_COMBINE, true, st);
+      launch_combine(b, st);
+      record(h, KV_K_COMBINE, false, st);
+    }
     if (g0.uncompressed) {
       record(h, KV_K_REBUILD_V, true, st);
       launch_append_bf16(b, st);

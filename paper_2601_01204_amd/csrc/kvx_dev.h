@@ -49,7 +49,7 @@ struct ScratchLayout {
   int64_t keep;       // [t_cap] int32: kept positions, ascending
   int64_t newtok;     // [t_cap] int32, slot layout: index of the call's token a slot receives, -1 for a slot whose token stays
   int64_t assign;     // [tokens of the largest call] int32, slot layout: slot of the call's i-th token
-  int64_t sel;        // [16] int32: [0] first dropped position, [1] first rebuilt key group, [2] groups rebuilt (running), [3] kept middle tokens, [5] groups quantised with a zero-point beyond +-2^20 (running), [6] non-finite input seen (debug checks), [7] scoring blocks of an attention launch that have finished (0 between launches)
+  int64_t sel;        // [16] int32: [0] first dropped position, [1] first rebuilt key group, [2] groups rebuilt (running), [3] kept middle tokens, [5] groups quantised with a zero-point beyond +-2^20 (running), [6] non-finite input seen (debug checks), [7] scoring blocks of the running launch that have finished, where the last one selects (0 between launches)
   int64_t bytes;
 };
 
@@ -88,6 +88,8 @@ struct Geometry {
   int32_t meta16;         // 1: 16-bit scales and zero-points
   int32_t slots;          // 1: slot-stable layout (one buffer, tokens never move), 0: compacting double buffer
   int32_t n_cus;          // compute units of the device
+  int32_t merge;          // 1: the launch that rewrites the cache merges the attention partials too (it follows attention)
+  int32_t score_selects;  // 1: the scoring launch selects too
   int32_t side_blocks;    // workgroups in front of a one-cache attention launch that score and select (0: launches of their own)
 };
 
@@ -145,6 +147,14 @@ inline int score_blocks(const KvxBatch& b, int max_tc) {
 constexpr int kMeanRows = 128;      // pooled rows brought into LDS at a time
 inline bool mean_in_score(const KvxBatch& b, int max_tc) {
   return score_blocks(b, max_tc) * b.n_items <= b.g.n_cus && b.g.n_pooled * (b.g.n_new / b.g.n) <= kMeanRows;
+}
+
+// The last block of a short scoring launch selects, which saves a launch (4 us): 34.4 -> 32.6 us a step of 69 tokens at a budget
+// of 256, 33.6 -> 30.6 for two frames of 62 tokens at 421.  Every block has its scores written back for the one that selects, so
+// that many blocks lose: three caches of 5001 tokens (210 blocks) take 5 us more than with two launches.
+constexpr int kScoreSelectBlocks = 32;
+inline bool selects_in_score(const KvxBatch& b, int max_tc) {
+  return mean_in_score(b, max_tc) && score_blocks(b, max_tc) * b.n_items <= kScoreSelectBlocks;
 }
 
 // Scoring workgroups inside a one-cache attention launch (0: the launch cannot carry them: several caches, fp32 inputs).  Each

@@ -7,7 +7,7 @@
 // fp32 with one rounding per operation: s = (max - min) / (2^b - 1) with an IEEE divide,
 // z = rint(-min / s), code = clamp(int(rint(x / s)) + z, 0, 2^b - 1), rint to nearest
 // even.  A constant group takes s = |min| (1 when min is 0).
-#include "kvx_dev.h"
+#include "combine_block.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -574,11 +574,18 @@ __global__ __launch_bounds__(256) void rebuild_v_kernel(const KvxBatchT<N> b, in
 // own, because each holds the key blocks' 22 KB of LDS: 24 caches of 16384 take 328 us against 231 + 88, 48 of 24576
 // 958 against 666 + 253, so from about 100 us on (kMergedBlocks) the two go separately.
 constexpr int kMergedBlocks = 32768;
+// n_c: blocks per head in front of them that merge the attention partials (0: a launch of its own).  Nothing in the rewrite
+// touches what the merge reads or writes, so where the rewrite follows attention the two share a launch: us a step, 782 tokens
+// at a budget of 2048 42 -> 40, 1041 at 8192 88 -> 82, eight caches of 782 at 4096 (slot layout) 234 -> 224.
 template <int KB, int VB, bool M16, bool SLOTS, int N>
-__global__ __launch_bounds__(256, 8) void rebuild_kernel(const KvxBatchT<N> b, int n_k, int n_v, int n_copy_blocks) {
+__global__ __launch_bounds__(256, 8) void rebuild_kernel(const KvxBatchT<N> b, int n_c, int n_k, int n_v, int n_copy_blocks) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.z];
-  const uint32_t tot = (uint32_t)(n_k + n_v), x = blockIdx.x;
+  if ((int)blockIdx.x < n_c) {
+    combine_block<4>(g, it, blockIdx.z, blockIdx.y, blockIdx.x);
+    return;
+  }
+  const uint32_t tot = (uint32_t)(n_k + n_v), x = blockIdx.x - n_c;
   const int v = (int)(x * (uint32_t)n_v / tot);                    // value blocks before this one
   if ((int)((x + 1) * (uint32_t)n_v / tot) > v) rebuild_v_block<VB, M16>(g, it, v, n_copy_blocks);
   else rebuild_k_block<KB, M16, SLOTS>(g, it, (int)x - v);
@@ -625,9 +632,11 @@ template <int KB, int VB, bool M16, bool SLOTS>
 static void launch_rebuild_t(const KvxBatch& b, int n_k, int n_v, int n_copy, hipStream_t st) {
   const dim3 block(256);
   if (n_k > 0 && n_v > 0 && (int64_t)(n_k + n_v) * b.g.H * b.n_items <= kMergedBlocks) {
-    with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((rebuild_kernel<KB, VB, M16, SLOTS, KVX_ITEMS(bb)>), dim3(n_k + n_v, b.g.H, b.n_items), block, 0, st, bb, n_k, n_v, n_copy); });
+    const int n_c = b.g.merge && b.g.n_splits > 1 ? (b.g.n_new + kCombineRows - 1) / kCombineRows : 0;
+    with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((rebuild_kernel<KB, VB, M16, SLOTS, KVX_ITEMS(bb)>), dim3(n_c + n_k + n_v, b.g.H, b.n_items), block, 0, st, bb, n_c, n_k, n_v, n_copy); });
     return;
   }
+  if (b.g.merge) launch_combine(b, st);
   if (n_k > 0) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((rebuild_k_kernel<KB, M16, SLOTS, KVX_ITEMS(bb)>), dim3(n_k, b.g.H, b.n_items), block, 0, st, bb); });
   if (n_v > 0) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((rebuild_v_kernel<VB, M16, KVX_ITEMS(bb)>), dim3(n_v, b.g.H, b.n_items), block, 0, st, bb, n_copy); });
 }

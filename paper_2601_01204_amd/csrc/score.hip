@@ -4,7 +4,7 @@
 // q~ the mean of the pooled, head-averaged query rows.  Every value here feeds top-k,
 // so each kernel evaluates in fp32 with one rounding per operation and the fixed order
 // of additions stated at the kernel (compiled without FMA contraction).
-#include "score_block.h"
+#include "score_select.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -140,8 +140,25 @@ void launch_pool(const KvxBatch& b, int max_tc, hipStream_t st) {
   if (!b.g.side_blocks && !mean_in_score(b, max_tc)) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((pool_mean_kernel<KVX_ITEMS(bb)>), dim3(b.n_items), dim3(1024), 0, st, bb); });
 }
 
+// Scoring and selection together (selects_in_score).
+template <int B, int N>
+__global__ __launch_bounds__(kScoreWaves * 64) void score_select_kernel(const KvxBatchT<N> b) {
+  const Geometry& g = b.g;
+  const Item it = b.items[blockIdx.y];
+  if (!it.prune) return;
+  const int blocks = (it.t_c + 63) / 64 - g.n / 64;
+  if ((int)blockIdx.x >= blocks) return;
+  extern __shared__ __attribute__((aligned(16))) float lds[];
+  score_and_select<B, kScoreWaves * 64>(g, it, blockIdx.x, blocks, lds);
+}
+
 template <int B>
 static void launch_score_t(const KvxBatch& b, int max_tc, hipStream_t st) {
+  if (b.g.score_selects) {
+    const size_t lds = score_select_lds_bytes(b.g.H, kScoreWaves, max_tc - b.g.n);
+    with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((score_select_kernel<B, KVX_ITEMS(bb)>), dim3(score_blocks(b, max_tc), b.n_items), dim3(kScoreWaves * 64), lds, st, bb); });
+    return;
+  }
   const int blocks = score_blocks(b, max_tc), waves = score_waves(b.g.H, B, blocks * b.n_items, b.g.n_cus);
   const dim3 grid(blocks, b.n_items), block(64 * waves);
   const size_t lds = score_lds_bytes(b.g.H, waves);
