@@ -298,9 +298,9 @@ int kv_read_timing(kv_handle* h, float* total_ms, int32_t* launches);
  *                                 time each, so a benchmark samples them rather than paying them per step
  *   "debug_checks"                1: every step first scans q, k and v for infinities and NaNs
  *                                 and reports them through kv_stats (nonfinite_flag); 0 (default)
- *   "overlap_update"              1 (default): a call on one cache of bf16 inputs (of more than
- *                                 n_cus / 16 heads x query tiles) scores and selects inside
- *                                 the attention launch; otherwise, when attention alone cannot fill the
+ *   "overlap_update"              1 (default): a call on one or a few caches of bf16 inputs (of more
+ *                                 than n_cus / 16 heads x query tiles) scores and selects
+ *                                 inside the attention launch; otherwise, when attention alone cannot fill the
  *                                 chip (one or a few caches per call) and is long enough to repay the fork and
  *                                 join (about 40 us of host time a call), scoring, pruning and re-quantisation
  *                                 run on a second stream of the library next to attention,

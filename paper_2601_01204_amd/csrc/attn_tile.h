@@ -194,14 +194,15 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
   const Geometry& g = b.g;
   constexpr int kParts = FMT == kMeta32 ? 2 : 1;          // operands a cached key is staged as
   constexpr int kLdsV = kParts * kBufs * kTileElems;      // the tiles of V lie behind those of K: one lane offset addresses both
-  constexpr bool kSide = N == 1 && FMT != kBf16;          // the launch may carry scoring blocks
+  constexpr bool kSide = FMT != kBf16;                    // the launch may carry scoring blocks
   constexpr int kLdsElems = kLdsV + kBufs * kTileElems, kSideElems = (int)select_lds_bytes(32768) / 2;
   __shared__ __attribute__((aligned(16))) uint16_t lds[kSide && kSideElems > kLdsElems ? kSideElems : kLdsElems];
   int side = 0;
   if constexpr (kSide) {
-    side = g.side_blocks;
+    side = g.side_blocks * b.n_items;
     if ((int)blockIdx.x < side) {
-      score_and_select<KB, kThreads>(g, b.items[0], blockIdx.x, side, lds);
+      const Item it = b.items[blockIdx.x / g.side_blocks];
+      if (it.prune) score_and_select<KB, kThreads>(g, it, blockIdx.x % g.side_blocks, g.side_blocks, lds);
       return;
     }
   }
@@ -885,7 +886,7 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
 template <Format FMT, int KB, int VB>
 void launch_tile(const KvxBatch& b, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   const Geometry& g = b.g;
-  const dim3 grid(g.side_blocks + g.n_qtiles * g.H * b.n_items * g.n_splits), block(kThreads);
+  const dim3 grid(g.side_blocks * b.n_items + g.n_qtiles * g.H * b.n_items * g.n_splits), block(kThreads);
   // with events: the runtime stamps them at the kernel's own start and end (what a kernel trace reports)
   if (ev_start) with_batch(b, [&](const auto& bb) { hipExtLaunchKernelGGL((attn_tile_kernel<FMT, KB, VB, KVX_ITEMS(bb)>), grid, block, 0, st, ev_start, ev_stop, 0, bb); });
   else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((attn_tile_kernel<FMT, KB, VB, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });

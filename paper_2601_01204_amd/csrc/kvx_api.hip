@@ -201,13 +201,17 @@ int validate(const kv_config* c) {
   return KV_OK;
 }
 
-constexpr double kOverlapSteps = 10.0;   // attention estimate (tile steps of about 2.3 us) from which the second stream pays
+constexpr double kOverlapSteps = 13.0;   // attention estimate (tile steps) from which the second stream pays
 
-// Key-range splits per (item, head, query tile) column.  A workgroup occupies a compute
-// unit by itself, so a launch runs in rounds of `target_wgs` workgroups; the estimate below
-// is rounds x (tiles per workgroup + a fixed per-workgroup cost of about three tiles for the
-// first loads and the partial-result store), and the split count with the smallest
-// estimate wins (fewer splits on ties: less merge traffic).
+// Key-range splits per (item, head, query tile) column.  A workgroup occupies a compute unit by itself, so a launch runs in
+// rounds of `target_wgs` workgroups; the estimate is rounds x (tiles per workgroup + kWorkgroupTiles) plus, with splits, the
+// partial results' way through memory, and the split count with the smallest estimate wins (fewer splits on ties).  In tiles
+// of about 1.5 us: the first loads and the store of a workgroup cost five, a row of 64 channels written and read again
+// 4e-5.  With three and a merge that cost one tile whatever its size the choice was worse for, us a step: three caches of 5001
+// tokens (12 heads, 523 queries) 6 ranges 108, 3 ranges 100; 1374 queries on one cache of 8192 7 ranges 93, 3 ranges 87; 24
+// caches of 4096 2 ranges 763, one 708.  Where the two agree (one cache of 2048 to 16384, 6 of 8192, 24 of 16384, eight of
+// 4096) nothing measured is better than the choice.
+constexpr double kWorkgroupTiles = 5.0, kMergeTilesPerRow = 4e-5;
 int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tiles, int target_wgs, double* estimate = nullptr) {
   int s;
   if (h->splits_override > 0) {
@@ -222,8 +226,9 @@ int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tile
     if (estimate) *estimate = 0.0;
     for (int c = 1; c <= cap; ++c) {
       const int64_t rounds = (base * c + target_wgs - 1) / target_wgs;
-      const double cost = (double)rounds * ((double)tiles / c + 3.0) + (c > 1 ? 1.0 : 0.0);
-      if (c == 1 || cost < best * 0.98) { best = cost; s = c; }
+      const double cost = (double)rounds * ((double)tiles / c + kWorkgroupTiles) +
+                          (c > 1 ? 1.0 + kMergeTilesPerRow * c * (double)n_items * g.H * g.n_pad : 0.0);
+      if (c == 1 || cost < best * 0.99) { best = cost; s = c; }
     }
     if (estimate) *estimate = best;
   }
@@ -539,17 +544,20 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     // cache of 16384 tokens (523 tokens a frame, 6 heads) takes 107 us a step in order and 82 beside.
     double steps = 0.0;
     pick_splits(h, b.g, cnt, max_tiles, h->n_cus, &steps);
-    // One cache that prunes, with more columns than kMaxSplits of them fill the units: scoring and selection ride in the attention
-    // launch (its first workgroups), and the step is a handful of launches on the caller's stream.  us a step against the rules
-    // above (second stream, or in order): 24 layers of 782 tokens at a budget of 2048, one call each, 58 -> 42; 1041 tokens at
-    // 4096 63 -> 52, at 8192 93 -> 88; four frames of 1041 at 8192 263 -> 264.  With fewer columns attention leaves most of the
-    // chip idle whatever the split, and the rules above stand.
-    const int side_blocks = side_blocks_of(b, max_tc);
-    const bool inside = may_overlap && h->overlap == 1 && small_launch && any_prune && side_blocks > 0 &&
-                        (int64_t)g0.H * b.g.n_qtiles * kMaxSplits > h->n_cus;
+    // A small launch that prunes, with more columns than kMaxSplits of them fill the units: scoring and selection ride in the
+    // attention launch (its first workgroups), and the step is a handful of launches on the caller's stream.  us a step against
+    // the rules above (second stream, or in order): 24 layers of 782 tokens at a budget of 2048, one call each, 58 -> 42 a
+    // layer; 1041 tokens at 4096 63 -> 52, at 8192 93 -> 88; four frames of 1041 at 8192 263 -> 264; three caches of 8192
+    // 193 -> 177.  With fewer columns attention leaves most of the chip idle whatever the split, and with several caches that
+    // take three quarters of it in one round the second stream has the rest (six caches of 523 tokens at 4096: 116, inside
+    // 118): there the rules above stand.
+    const int side_blocks = side_blocks_of(b, max_tc, steps);
+    const int64_t columns = (int64_t)cnt * g0.H * b.g.n_qtiles;
+    const bool inside = may_overlap && h->overlap == 1 && any_prune && side_blocks > 0 && columns + side_blocks * cnt <= h->n_cus &&
+                        columns * kMaxSplits > h->n_cus && (cnt == 1 || columns < h->target_wgs);
     const bool beside = may_overlap && !inside && (h->overlap == 2 || (small_launch && (steps == 0.0 || steps >= kOverlapSteps)));
     // a small launch leaves a quarter of the compute units to the chain next to it, or a unit to each of the scoring blocks in it
-    b.g.n_splits = pick_splits(h, b.g, cnt, min_tiles, ((beside && small_launch) || h->target_explicit) ? h->target_wgs : inside ? std::max(1, h->n_cus - side_blocks) : h->n_cus);
+    b.g.n_splits = pick_splits(h, b.g, cnt, min_tiles, ((beside && small_launch) || h->target_explicit) ? h->target_wgs : inside ? std::max(1, h->n_cus - side_blocks * cnt) : h->n_cus);
     // never more splits than the partial-result buffers hold (an explicit "attention_splits" may ask for more)
     b.g.n_splits = (int32_t)std::max<int64_t>(1, std::min<int64_t>(b.g.n_splits, rows_cap / ((int64_t)cnt * b.g.n_pad)));
 
@@ -565,7 +573,7 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     // (while the parts are timed they are launched one by one)
     b.g.merge = rebuild_after && !h->timing_now;
     b.g.score_selects = selects_in_score(b, max_tc) && !h->timing_now;
-    if (inside && !h->timing_now) b.g.side_blocks = side_blocks;
+    if (inside && !h->timing_now) b.g.side_blocks = side_blocks;      // per cache
     if (!g0.uncompressed) {
       if (b.g.side_blocks) {
         launch_pool(b, max_tc, st);

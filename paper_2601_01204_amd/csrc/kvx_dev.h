@@ -90,7 +90,7 @@ struct Geometry {
   int32_t n_cus;          // compute units of the device
   int32_t merge;          // 1: the launch that rewrites the cache merges the attention partials too (it follows attention)
   int32_t score_selects;  // 1: the scoring launch selects too
-  int32_t side_blocks;    // workgroups in front of a one-cache attention launch that score and select (0: launches of their own)
+  int32_t side_blocks;    // workgroups per cache in front of an attention launch that score and select (0: launches of their own)
 };
 
 struct Item {
@@ -157,14 +157,19 @@ inline bool selects_in_score(const KvxBatch& b, int max_tc) {
   return mean_in_score(b, max_tc) && score_blocks(b, max_tc) * b.n_items <= kScoreSelectBlocks;
 }
 
-// Scoring workgroups inside a one-cache attention launch (0: the launch cannot carry them: several caches, fp32 inputs).  Each
-// takes positions in turn and holds a compute unit meanwhile, so that few are better as long as they and the selection are done
-// before attention is.
-constexpr int kSideBlocks = 16;
-inline int side_blocks_of(const KvxBatch& b, int max_tc) {
-  if (b.n_items != 1 || b.g.in_f32 || b.g.uncompressed) return 0;
+// Scoring workgroups per cache inside an attention launch (0: the launch cannot carry them: many caches, fp32 inputs).  Each
+// takes 64 positions after 64, up to 5 us each, and holds a compute unit meanwhile, and the selection takes another 20 us: so few
+// that both are done in about 0.6 of attention's estimate (tile steps of 1.5 us), no more than kSideBlocks per cache and
+// kSideBlocksMax in all.  Sixteen in all whatever the lengths: six caches of 4096 (523 tokens) 113 -> 124 us a step.
+constexpr int kSideBlocks = 16, kSideBlocksMax = 64;
+inline int side_blocks_of(const KvxBatch& b, int max_tc, double steps) {
+  if (b.g.in_f32 || b.g.uncompressed) return 0;
   const int blocks = score_blocks(b, max_tc);
-  return blocks < kSideBlocks ? blocks : kSideBlocks;
+  const double each = (0.9 * steps - 20.0) / 5.0;
+  int n = each <= 1.0 ? blocks : (int)((double)blocks / each) + 1;
+  n = n < kSideBlocks ? n : kSideBlocks;
+  n = n < blocks ? n : blocks;
+  return n * b.n_items <= kSideBlocksMax ? n : 0;
 }
 
 // Waves of a scoring block, which take turns over the heads.  Up to a block per compute unit latency counts: all of 16 heads

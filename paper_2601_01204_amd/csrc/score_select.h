@@ -1,4 +1,4 @@
-// Scoring and selection in one launch, of their own (score_select_kernel) or in front of the attention of a one-cache call
+// Scoring and selection in one launch, of their own (score_select_kernel) or in front of the attention of a small call
 // (attn_tile_kernel).  n_blocks workgroups share a cache's positions; the one that finishes last selects.  Nobody waits for
 // anybody: a block that is not the last one leaves.  A block's scores are released once, by its first thread, so that an XCD's
 // cache is written back no more often than there are blocks.

@@ -45,3 +45,30 @@ def test_the_largest_selection_and_launches_of_their_own():
     a, b = (h.export() for h in hs)
     for key in ("ids", "k_codes", "k_scale", "k_zero", "v_codes", "v_scale", "v_zero", "last_keep", "last_scores"):
         assert np.array_equal(a[key], b[key]), key
+
+
+def test_three_caches_of_different_lengths():
+    """Three caches a call, one of them not full yet: scoring blocks of their own each, against single calls without them."""
+    import torch
+    w = si.Workload("inside_three", 8, 64, 70, 3, 16, 1100, 30, 3, 1, 4, 64, 4, 64, "bf16", 73)
+    a = pu.make_handle(w, n_streams=3, meta_format=1)
+    b = pu.make_handle(w, n_streams=3, meta_format=1)
+    b.set_option("overlap_update", 0)
+    for h in (a, b):
+        h.set_option("attention_splits", 1)      # (a call's ranges go by its shortest cache)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(6)
+    for t in range(24):
+        streams = [s for s in range(3) if t >= (0, 2, 12)[s]]
+        f = {s: [torch.randn((70, 8, 64), generator=gen, device="cuda:0").to(torch.bfloat16) for _ in range(3)] for s in streams}
+        outs = [{s: torch.empty((70, 8, 64), dtype=torch.float32, device="cuda:0") for s in streams} for _ in range(2)]
+        a.step_batched([(s, 0, *f[s], outs[0][s]) for s in streams])
+        for s in streams:
+            b.step(*f[s], outs[1][s], stream=s)
+        torch.cuda.synchronize()
+        for s in streams:
+            assert torch.equal(outs[0][s], outs[1][s]), (t, s)
+    for s in range(3):
+        x, y = a.export(s, 0), b.export(s, 0)
+        for key in ("ids", "k_codes", "k_scale", "k_zero", "v_codes", "v_scale", "v_zero"):
+            assert np.array_equal(x[key], y[key]), (s, key)
