@@ -17,11 +17,13 @@ __device__ __forceinline__ void combine_block(const Geometry& g, const Item& it,
   float2 ml[kMaxSplits];
   float4 po[BATCH];
 #pragma unroll
-  for (int s = 0; s < kMaxSplits; ++s)
-    if (s < g.n_splits) ml[s] = *reinterpret_cast<const float2*>(g.part_ml + (row0 + s * row_step) * 2);
-#pragma unroll
-  for (int s = 0; s < BATCH; ++s)
-    if (s < g.n_splits) po[s] = *reinterpret_cast<const float4*>(g.part_o + (row0 + s * row_step) * kHeadDim + c);
+  for (int s = 0; s < kMaxSplits; ++s) {
+    if (s < g.n_splits) {
+      const int64_t row = row0 + s * row_step;
+      ml[s] = *reinterpret_cast<const float2*>(g.part_ml + row * 2);
+      if (s < BATCH) po[s] = *reinterpret_cast<const float4*>(g.part_o + row * kHeadDim + c);
+    }
+  }
   float m_max = -1.0e30f;               // what a range without a key leaves
 #pragma unroll
   for (int s = 0; s < kMaxSplits; ++s)
@@ -32,10 +34,12 @@ __device__ __forceinline__ void combine_block(const Geometry& g, const Item& it,
   for (int s = 0; s < kMaxSplits; ++s) {
     if (s < g.n_splits) {
       const float w = __builtin_amdgcn_exp2f(ml[s].x - m_max);
-      float4& p = po[s % BATCH];
+      const float4 p = po[s % BATCH];
       acc.x += w * p.x; acc.y += w * p.y; acc.z += w * p.z; acc.w += w * p.w;
       l += w * ml[s].y;
-      if (s + BATCH < kMaxSplits && s + BATCH < g.n_splits) p = *reinterpret_cast<const float4*>(g.part_o + (row0 + (s + BATCH) * row_step) * kHeadDim + c);
+      if constexpr (BATCH < kMaxSplits)
+        if (s + BATCH < kMaxSplits && s + BATCH < g.n_splits)
+          po[s % BATCH] = *reinterpret_cast<const float4*>(g.part_o + (row0 + (s + BATCH) * row_step) * kHeadDim + c);
     }
   }
   const float inv = 1.0f / l;

@@ -136,6 +136,18 @@ inline void with_batch(const KvxBatch& b, F&& f) {
 // inside f: the number of caches its argument holds, as a constant
 #define KVX_ITEMS(bb) (std::remove_reference_t<decltype(bb)>::kItems)
 
+// ---- launch shape of the cache rewrite -------------------------------------------
+// Copy blocks (a lane moves 16 bytes of a survivor's value codes; none in the slot layout, which never moves one), and all
+// blocks of a launch.  Keys and values share a launch of up to kMergedBlocks blocks (see rebuild_kernel).
+constexpr int kMergedBlocks = 32768;
+inline int rebuild_copy_blocks(const Geometry& g, int max_tnew) {
+  const int rows_per_block = 256 / (g.v_bits / 2), carried = max_tnew > g.n_new ? max_tnew - g.n_new : 0;
+  return g.slots ? 0 : (carried + rows_per_block - 1) / rows_per_block;
+}
+inline int64_t rebuild_blocks(const KvxBatch& b, int max_tnew) {
+  return (int64_t)((max_tnew + kTileK - 1) / kTileK + rebuild_copy_blocks(b.g, max_tnew) + (b.g.n_new + kTileK - 1) / kTileK) * b.g.H * b.n_items;
+}
+
 // ---- launch shape of the scoring kernel ------------------------------------------
 // Blocks of 64 positions per cache that hold middle tokens: behind the first frame.
 inline int score_blocks(const KvxBatch& b, int max_tc) {

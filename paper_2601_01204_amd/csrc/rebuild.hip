@@ -573,7 +573,6 @@ __global__ __launch_bounds__(256) void rebuild_v_kernel(const KvxBatchT<N> b, in
 // caches of 4096 in the slot layout 283 -> 275 us.  In a long launch the value blocks stream more slowly than on their
 // own, because each holds the key blocks' 22 KB of LDS: 24 caches of 16384 take 328 us against 231 + 88, 48 of 24576
 // 958 against 666 + 253, so from about 100 us on (kMergedBlocks) the two go separately.
-constexpr int kMergedBlocks = 32768;
 // n_c: blocks per head in front of them that merge the attention partials (0: a launch of its own).  Nothing in the rewrite
 // touches what the merge reads or writes, so where the rewrite follows attention the two share a launch: us a step, 782 tokens
 // at a budget of 2048 42 -> 40, 1041 at 8192 88 -> 82, eight caches of 782 at 4096 (slot layout) 234 -> 224.
@@ -643,9 +642,7 @@ static void launch_rebuild_t(const KvxBatch& b, int n_k, int n_v, int n_copy, hi
 
 void launch_rebuild(const KvxBatch& b, int max_tnew, bool keys, bool values, hipStream_t st) {
   const Geometry& g = b.g;
-  const int rows_per_block = 256 / (g.v_bits / 2);           // 16 bytes of codes per lane
-  // the slot layout never moves a survivor: only the call's tokens are written
-  const int n_copy = g.slots ? 0 : (std::max(max_tnew - g.n_new, 0) + rows_per_block - 1) / rows_per_block;
+  const int n_copy = rebuild_copy_blocks(g, max_tnew);
   const int n_k = keys ? (max_tnew + kTileK - 1) / kTileK : 0;
   const int n_v = values ? n_copy + (g.n_new + kTileK - 1) / kTileK : 0;
 #define KVX_RB(K, V)                                                                                \

@@ -118,7 +118,7 @@ __device__ __forceinline__ void score_block(const Geometry& g, const Item& it, i
       }
     }
   };
-  if (wave < g.H) load_head(wave, w, rs, rz);      // requested first: its latency runs beside the row mean
+  load_head(min(wave, g.H - 1), w, rs, rz);      // requested first: its latency runs beside the row mean (no branch around it)
   const float qc = mean();
   for (int h = wave; h < g.H; h += n_waves) {
 #pragma unroll
