@@ -271,7 +271,7 @@ def aux_small_budgets(torch, kvx, si, dev, steps):
     needs frames of at most 1024 tokens (first and current frame are always kept), so it runs on 518 x 294 frames
     (782 tokens); 4096 and 8192 on 518 x 392 frames (1041 tokens)."""
     import dataclasses
-    out = {"kernel_us": "timed kernel by kernel, with key and value rebuild launched apart; the timed steps launch them as one"}
+    out = {"kernel_us": "timed kernel by kernel, every part in a launch of its own; the timed steps score and select inside the attention launch and merge and rebuild in one"}
     base = si.WORKLOADS["vggt_layer"]
     for n, L in ((782, 2048), (1041, 4096), (1041, 8192)):
         w = dataclasses.replace(base, tokens_per_frame=n, budget_tokens=L)

@@ -306,11 +306,8 @@ int kv_read_timing(kv_handle* h, float* total_ms, int32_t* launches);
  *                                 run on a second stream of the library next to attention,
  *                                 joined back into hip_stream before kv_step returns (slot
  *                                 layout: pooling, scoring and selection do; its writers always
- *                                 follow attention); 2: the second stream at any launch size, which a call
- *                                 whose host time does not count (recorded into a graph, or issued
- *                                 while the GPU has other work) gains from somewhat earlier: 523 tokens
- *                                 at a budget of 2048 take 53 us of GPU time and 60 in order, 400 at
- *                                 1024 54 and 49; 0: everything in order on hip_stream */
+ *                                 follow attention); 2: the second stream at any launch size;
+ *                                 0: everything in order on hip_stream */
 int kv_set_option(kv_handle* h, const char* name, int64_t value);
 
 /* Machine probes (measurement aids, no handle needed; they allocate and free their own

@@ -535,11 +535,10 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     const bool may_overlap = h->overlap != 0 && h->side && !g0.uncompressed && !update_first;
     const bool small_launch = (int64_t)cnt * g0.H * g0.n_qtiles <= (int64_t)h->n_cus;
     // The fork and the join cost the host about 40 us a call (an event record and a wait each), so that a call with the
-    // second stream issues in 60 us or more and one without in 27.  A short attention launch is not worth that.  In order
-    // and beside, us a step, calls back to back: 69 tokens, fp32 (4.4 tile steps) 34 and 59; 400 at a budget of 1024 (6.9)
-    // 47 and 64; 523 at 2048 (9.1) 57 and 64; 1374 at 2800, 6 heads (10.6) 61 and 62; 782 at 1600 (11.6) 61 and 61, at
-    // 2048 (13.0) 62 and 59; 1041 at 2400 (15.0) 70 and 60, at 4096 (20.2) 81 and 66.  Where other work of the GPU hides
-    // the issue the two meet earlier (400 tokens 49 and 54, 523 at 1500 58 and 54, at 2048 60 and 53).
+    // second stream issues in 60 us or more and one without in 20 to 27.  A short attention launch is not worth that.  In order
+    // and beside, us a step, calls back to back, with all the parts in launches of their own: 69 tokens, fp32, 34 and 59; 400 at
+    // a budget of 1024 47 and 64; 523 at 2048 57 and 64; 1374 at 2800, 6 heads, 61 and 62; 1041 at 2400 70 and 60, at 4096 81
+    // and 66.  Where other work of the GPU hides the issue the two meet earlier (523 at 1500 58 and 54).
     // A launch lasts as long as its longest cache, so the estimate goes by that one: a stream that starts beside a full
     // cache of 16384 tokens (523 tokens a frame, 6 heads) takes 107 us a step in order and 82 beside.
     double steps = 0.0;
