@@ -714,9 +714,9 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
         asm volatile("" : "+v"(negm[i]));
         started[i] = true;
       }
-      // the pipeline starts with units of no weight
+      // the pipeline starts with units of no weight: infinitely far below any reference, also after a small logit factor
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s_cur[r] = kNegBig;
+      for (int r = 0; r < 16; ++r) s_cur[r] = -__builtin_inff();
 #pragma unroll
       for (int e = 0; e < 8; ++e) w_prev[e] = 0;
       int rv = r0;

@@ -51,3 +51,28 @@ def test_logits_outgrow_the_reference(n, budget, splits, meta16):
 def test_code_widths(k_bits, k_group, v_bits, v_group):
     w = si.Workload("widths", 3, 64, 290, 2, 16, 1111, 5, 1, 1, k_bits, k_group, v_bits, v_group, "bf16", 63)
     run(w, 5, 2, True)
+
+
+@pytest.mark.parametrize("mode", ["meta16", "meta32", "uncompressed"])
+def test_a_tiny_logit_factor_averages_the_values(mode):
+    """A logit factor of 1e-30 makes every logit 0 to all accuracy: each value weighs the same.  The bound: values in halves
+    (2^-11 of |v| < 8 at most), nothing else rounds in a plain mean."""
+    import paper_2601_01204_amd as kvx
+    import torch
+    n, H = 192, 2
+    w = si.Workload("equal", H, 64, n, 1, 16, 8 * n, 1, 1, 1, 4, 64, 4, 64, "bf16", 64)
+    extra = dict(mode=kvx.KV_UNCOMPRESSED_BF16, max_frames=2) if mode == "uncompressed" else dict(meta_format=1 if mode == "meta16" else 0)
+    h = pu.make_handle(w, softmax_scale=1e-30, **extra)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(6)
+    v = torch.randn((n, H, 64), generator=gen, device="cuda:0").to(torch.bfloat16)
+    q, k = torch.full_like(v, 1.0), torch.full_like(v, 1.0)
+    for splits in (1, 2):
+        h.reset()
+        h.set_option("attention_splits", splits)
+        out = torch.empty(v.shape, dtype=torch.float32, device="cuda:0")
+        h.step(q, k, v, out)
+        torch.cuda.synchronize()
+        err = (out.double() - v.double().mean(0, keepdim=True)).abs().max().item()
+        assert err <= 8 * 2.0 ** -11, f"splits {splits}: {err}"
+    h.close()
