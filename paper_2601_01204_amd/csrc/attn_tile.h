@@ -159,10 +159,14 @@ __device__ __forceinline__ void split_bf16(float a, float b, uint32_t& hi, uint3
   lo = __builtin_amdgcn_perm(__float_as_uint(rb), __float_as_uint(ra), 0x07060302u);
 }
 
-// The larger of a lane's value and that of the lane 32 away.
+// The larger, and the sum, of a lane's value and that of the lane 32 away.
 __device__ __forceinline__ float max_halves(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float add_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
 // What the cache holds.
@@ -313,6 +317,15 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
     auto sums = [&](const uint32_t (&w)[8]) __attribute__((always_inline)) {
       const f32x4 x = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, frag(w, 0), no_sum, 0, 0, 0);
       return __builtin_amdgcn_mfma_f32_16x16x32_f16(ones, frag(w, 1), x, 0, 0, 0)[0];
+    };
+    // The same sum lane by lane, for units in which some row saw infinities or NaNs: there the ones matrix's zeros times that
+    // row's probabilities would spoil the sum of the row it shares a column with (slower, and rare).
+    auto lane_sums = [&](const uint32_t (&w)[8]) __attribute__((always_inline)) {
+      const f16x2 one = {(_Float16)1.0f, (_Float16)1.0f};
+      float x = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x = __builtin_amdgcn_fdot2(as_h2(w[e]), one, x, false);
+      return add_halves(x);
     };
     auto probabilities = [&](const f32x16& s, uint32_t (&w)[8]) __attribute__((always_inline)) {
 #pragma unroll
@@ -675,7 +688,7 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
       pv(3); KVX_PIN();
       if (__builtin_expect(over != 0, 0)) {
         const float delta = raise(bs, s_cur, w, false);
-        unit_sum = sums(w);
+        unit_sum = lane_sums(w);
         if constexpr (NB == 1 && !OWN) {
 #pragma unroll
           for (int r = 0; r < 16; ++r) s_nxt[r] -= delta;       // the next unit's logits were formed with the old reference
@@ -751,7 +764,7 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
       float unit_sum = sums(w);
       if (__any(!(unit_sum < kSumLimit))) {
         raise(bs, s_cur, w, false);
-        unit_sum = sums(w);
+        unit_sum = lane_sums(w);
       }
       l[bs] += unit_sum;
 #pragma unroll
@@ -791,7 +804,7 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
               float unit_sum = sums(w);
               if (__any(!started[i] || !(unit_sum < kSumLimit))) {
                 raise(i, s, w, !started[i]);
-                unit_sum = sums(w);
+                unit_sum = lane_sums(w);
                 started[i] = true;
               }
               l[i] += unit_sum;

@@ -76,3 +76,38 @@ def test_a_tiny_logit_factor_averages_the_values(mode):
         err = (out.double() - v.double().mean(0, keepdim=True)).abs().max().item()
         assert err <= 8 * 2.0 ** -11, f"splits {splits}: {err}"
     h.close()
+
+
+@pytest.mark.parametrize("mode", ["meta16", "meta32", "uncompressed"])
+@pytest.mark.parametrize("n,frames,splits", [(70, 1, 1), (70, 2, 1), (300, 2, 1), (300, 2, 3)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_a_bad_query_row_stays_alone(mode, n, frames, splits, bad):
+    """A query row that is not finite spoils its own output row and no other: the rest equals the outputs of the same frames
+    with that row finite.  Sums of a unit's probabilities may be added in another order for its neighbours: 32 terms of 2^-24
+    relative each, over values below 8."""
+    import paper_2601_01204_amd as kvx
+    import torch
+    H = 2
+    w = si.Workload("bad", H, 64, n, 1, 16, 8 * n, frames, 1, 1, 4, 64, 4, 64, "bf16", 65)
+    extra = dict(mode=kvx.KV_UNCOMPRESSED_BF16, max_frames=frames) if mode == "uncompressed" else dict(meta_format=1 if mode == "meta16" else 0)
+    hs = [pu.make_handle(w, **extra) for _ in range(2)]
+    rows = [3, 21, 40, n - 1]
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(7)
+    for h in hs:
+        h.set_option("attention_splits", splits)
+    for t in range(frames):
+        q, k, v = (torch.randn((n, H, 64), generator=gen, device="cuda:0").to(torch.bfloat16) for _ in range(3))
+        spoilt = q.clone()
+        spoilt[rows, 0, 5] = bad
+        outs = [torch.empty(q.shape, dtype=torch.float32, device="cuda:0") for _ in hs]
+        hs[0].step(q, k, v, outs[0])
+        hs[1].step(spoilt, k, v, outs[1])
+        torch.cuda.synchronize()
+        assert torch.isfinite(outs[0]).all()
+        keep = torch.ones((n, H), dtype=torch.bool, device="cuda:0")
+        keep[rows, 0] = False
+        err = (outs[1][keep] - outs[0][keep]).abs().max().item()
+        assert err <= 8 * 32 * 2.0 ** -24, f"frame {t}: rows beside a bad one differ by {err}"
+    for h in hs:
+        h.close()
