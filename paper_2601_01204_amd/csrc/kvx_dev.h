@@ -169,18 +169,29 @@ inline bool selects_in_score(const KvxBatch& b, int max_tc) {
   return mean_in_score(b, max_tc) && score_blocks(b, max_tc) * b.n_items <= kScoreSelectBlocks;
 }
 
-// Scoring workgroups per cache inside an attention launch (0: the launch cannot carry them: many caches, fp32 inputs).  Each
-// takes 64 positions after 64, up to 5 us each, and holds a compute unit meanwhile, and the selection takes another 20 us: so few
-// that both are done in about 0.6 of attention's estimate (tile steps of 1.5 us), no more than kSideBlocks per cache and
-// kSideBlocksMax in all.  Sixteen in all whatever the lengths: six caches of 4096 (523 tokens) 113 -> 124 us a step.
+// Scoring workgroups per cache inside an attention launch (0: the launch cannot carry them: many caches, fp32 inputs, or scoring
+// that would outlast attention).  Each takes 64 positions after 64, up to 5 us each for 16 heads and in proportion for more, and
+// holds a compute unit meanwhile, and the selection takes another 20 us: so few that both are done in about 0.6 of attention's
+// estimate (tile steps of 1.5 us), no more than kSideBlocks per cache and kSideBlocksMax in all.  Sixteen in all whatever the
+// lengths: six caches of 4096 (523 tokens) 113 -> 124 us a step.
+// Where sixteen are not enough the launch waits for them.  What they take then, from steps bound by it (17 to 64 heads, 69 to 780
+// tokens, budgets of 512 to 16384): per 64 positions 0.18 us a head (8-bit codes 0.26) and 0.3, the selection 8 us and 0.08 per 64
+// positions.  Up to 40 us (20 more with every further cache: launches in order take the longer, and so does their issue) that is
+// still the shortest step whatever attention takes: 64 heads, 130 tokens, budget 2048, 50 us against 58 in order and 67 on the
+// second stream; 32 heads at 4096 51, 52 and 66; two caches of 12 heads, 200 tokens, 8192 58, 62 and 85.  Beyond, it has to fit
+// into attention's estimate: 64 heads of 130 tokens at 8192 take 127 us inside, 97 in order and 86 on the second stream, 32 heads
+// of 300 at 16384 141, 117 and 100, but 17 heads of 780 at 16384 114, 126 and 120.
 constexpr int kSideBlocks = 16, kSideBlocksMax = 64;
 inline int side_blocks_of(const KvxBatch& b, int max_tc, double steps) {
   if (b.g.in_f32 || b.g.uncompressed) return 0;
-  const int blocks = score_blocks(b, max_tc);
-  const double each = (0.9 * steps - 20.0) / 5.0;
+  const int blocks = score_blocks(b, max_tc), H = b.g.H;
+  const bool wide = b.g.k_bits == 8;
+  const double each = (0.9 * steps - 20.0) / (5.0 * (H > 16 ? H / 16.0 : 1.0) * (wide ? 1.4 : 1.0));
   int n = each <= 1.0 ? blocks : (int)((double)blocks / each) + 1;
   n = n < kSideBlocks ? n : kSideBlocks;
   n = n < blocks ? n : blocks;
+  const double us = (double)((blocks + n - 1) / n) * (0.3 + (wide ? 0.26 : 0.18) * H) + 8.0 + 0.08 * blocks;
+  if (steps > 0.0 && us > 20.0 + 20.0 * b.n_items && us > 1.35 * steps) return 0;      // (an explicit split count leaves no estimate)
   return n * b.n_items <= kSideBlocksMax ? n : 0;
 }
 

@@ -40,6 +40,9 @@ inline const char* hipGetErrorString(hipError_t) { return "stub"; }
 inline hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
 inline int stub_cus = 256;             // compute units of the pretended device
 inline bool stub_mean_in_score;        // last scoring launch: whether its blocks form the row mean
+// last attention launch: key ranges, scoring blocks per cache inside it; last step: whether the rewrite takes the merge along and
+// scoring selects
+inline int stub_splits, stub_side_blocks, stub_merge, stub_score_selects;
 inline hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = stub_cus; return hipSuccess; }
 inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = reinterpret_cast<hipStream_t>(std::malloc(1)); return hipSuccess; }
 inline hipError_t hipStreamDestroy(hipStream_t s) { std::free(s); return hipSuccess; }

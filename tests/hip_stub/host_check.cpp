@@ -235,9 +235,44 @@ void score_block_shapes() {
     }
 }
 
+// A handle of `caches` streams of H heads and n tokens a frame, one layer each, full at budget L.
+struct Full {
+  kv_handle* h = nullptr;
+  kv_config c;
+  std::vector<uint16_t> q;
+  std::vector<kv_step_item> items;
+  Full(int caches, int H, int n, int L, int k_bits = 4, int frames = 1) : c(base_config(KV_META_F32, KV_LAYOUT_COMPACT, k_bits, 64, 4, 64)), items(caches) {
+    c.n_streams = caches; c.n_layers = 1; c.n_heads = H; c.tokens_per_frame = n; c.budget_tokens = L; c.max_frames_per_step = frames;
+    CHECK(kv_init(&c, &h) == KV_OK && h);
+    q.resize((size_t)frames * n * H * 64);
+    for (int i = 0; i < caches; ++i) { items[i].stream = i; items[i].layer = 0; items[i].q = items[i].k = items[i].v = items[i].out = q.data(); }
+    for (int t = 0; t < L; t += n) step();
+  }
+  void step() { CHECK(kv_step_batched(h, (int)items.size(), items.data(), (int64_t)c.n_heads * 64, 64, nullptr) == KV_OK); }
+  ~Full() { kv_destroy(h); }
+};
+
+// Scoring blocks inside the attention launch: as many as finish under it, none where scoring would outlast it.
+void scoring_blocks_inside_attention() {
+  struct { int caches, H, n, L, k_bits, blocks; } cases[] = {
+    {1, 16, 1041, 8192, 4, 16},  {1, 16, 782, 2048, 4, 16},  {1, 64, 130, 2048, 4, 16},  {1, 32, 130, 4096, 4, 16},    // short, or under attention
+    {1, 17, 780, 16384, 4, 16},  {2, 12, 200, 8192, 4, 16},  {3, 6, 300, 4096, 4, 16},   {1, 24, 1041, 16384, 8, 16},
+    {1, 32, 130, 8192, 4, 0},    {1, 32, 300, 16384, 4, 0},  {1, 48, 200, 8192, 4, 0},   {1, 64, 130, 24576, 4, 0},    // outlast it
+    {1, 64, 300, 8192, 4, 0},    {1, 16, 400, 16384, 8, 0},  {1, 32, 400, 16384, 8, 0},
+    {1, 16, 384, 4096, 4, 0},    {6, 16, 300, 4096, 4, 0},                                                            // few columns; many caches
+  };
+  for (const auto& x : cases) {
+    Full f(x.caches, x.H, x.n, x.L, x.k_bits);
+    f.step();
+    if (stub_side_blocks != x.blocks) std::fprintf(stderr, "%d caches, %d heads, %d tokens, budget %d: %d blocks\n", x.caches, x.H, x.n, x.L, stub_side_blocks);
+    CHECK(stub_side_blocks == x.blocks);
+  }
+}
+
 }  // namespace
 
 int main() {
+  scoring_blocks_inside_attention();
   score_block_shapes();
   launch_rules_by_the_device(64, true);
   launch_rules_by_the_device(48, false);
