@@ -212,7 +212,9 @@ constexpr double kOverlapSteps = 13.0;   // attention estimate (tile steps) from
 // caches of 4096 2 ranges 763, one 708.  Where the two agree (one cache of 2048 to 16384, 6 of 8192, 24 of 16384, eight of
 // 4096) nothing measured is better than the choice.
 constexpr double kWorkgroupTiles = 5.0, kMergeTilesPerRow = 4e-5;
-int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tiles, int target_wgs, double* estimate = nullptr) {
+// rows_cap: (cache, split) slots x padded query rows the partial-result buffers hold; the choice is among the counts that fit.
+int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tiles, int target_wgs, int64_t rows_cap, double* estimate = nullptr) {
+  const int fit = (int)std::max<int64_t>(1, std::min<int64_t>(kMaxSplits, rows_cap / ((int64_t)n_items * g.n_pad)));
   int s;
   if (h->splits_override > 0) {
     s = h->splits_override;
@@ -220,7 +222,7 @@ int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tile
     const int64_t base = (int64_t)n_items * g.H * g.n_qtiles;
     const int tiles = std::max(1, std::min(min_tiles, 1 << 20));
     // up to two rounds' worth of workgroups, and at least four splits to choose from
-    const int cap = (int)std::min<int64_t>(kMaxSplits, std::max<int64_t>(4, (2 * (int64_t)target_wgs) / base));
+    const int cap = (int)std::min<int64_t>(fit, std::max<int64_t>(4, (2 * (int64_t)target_wgs) / base));
     double best = 0.0;
     s = 1;
     if (estimate) *estimate = 0.0;
@@ -232,7 +234,7 @@ int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tile
     }
     if (estimate) *estimate = best;
   }
-  s = std::max(1, std::min(s, (int)kMaxSplits));
+  s = std::max(1, std::min(s, fit));      // (an explicit "attention_splits" may ask for more)
   s = std::min(s, std::max(1, min_tiles));
   return s;
 }
@@ -386,19 +388,24 @@ int kv_init(const kv_config* cfg, kv_handle** out) {
   h->caches.assign((size_t)n_caches, CacheState());
   h->seen_in_call.assign((size_t)n_caches, 0);
   h->stream_n.assign((size_t)c.n_streams, c.tokens_per_frame);
-  // Partial results of the key-range splits: room for the largest (caches per launch) x (splits) x (padded query rows)
-  // the automatic choice can reach, found by running it over every launch shape this handle can see.
+  // Partial results of the key-range splits: room for the largest (caches per launch) x (splits) x (padded query rows) the
+  // automatic choice reaches over calls of the handle's frame size: every number of frames and caches, every workgroup target (with
+  // and without the second stream, and what scoring blocks inside the launch leave), key counts in steps of two.  A call that
+  // would gain from more (streams of smaller frames, key counts in between) takes the best count that fits.
   int64_t rows_cap = 0;
   for (int f = 1; f <= h->f_max; ++f) {
     Geometry gf = g;
     set_query_tiling(gf, f * g.n);
     const int tiles_max = (g.t_cap + kTileK - 1) / kTileK + (gf.n_new + kTileK - 1) / kTileK;
     for (int items = 1; items <= std::min<int64_t>(kMaxItems, n_caches); ++items)
-      for (int tiles = tiles_max; tiles >= 1; tiles = tiles > 1 ? (tiles + 1) / 2 : 0)
-        for (int target : {h->target_wgs, cus, std::max(1, cus - kSideBlocks)}) {
-          const int sp = pick_splits(h, gf, items, tiles, target);
+      for (int tiles = tiles_max; tiles >= 1; tiles = tiles > 1 ? (tiles + 1) / 2 : 0) {
+        auto reach = [&](int target) {
+          const int sp = pick_splits(h, gf, items, tiles, target, INT64_MAX);
           rows_cap = std::max(rows_cap, (int64_t)items * sp * gf.n_pad);
-        }
+        };
+        reach(h->target_wgs);
+        for (int s = 0; s <= kSideBlocks && s * items <= kSideBlocksMax; ++s) reach(std::max(1, cus - s * items));
+      }
   }
   set_query_tiling(g, g.n);
   h->part_rows_cap = rows_cap;
@@ -542,7 +549,7 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     // A launch lasts as long as its longest cache, so the estimate goes by that one: a stream that starts beside a full
     // cache of 16384 tokens (523 tokens a frame, 6 heads) takes 107 us a step in order and 82 beside.
     double steps = 0.0;
-    pick_splits(h, b.g, cnt, max_tiles, h->n_cus, &steps);
+    pick_splits(h, b.g, cnt, max_tiles, h->n_cus, rows_cap, &steps);
     // A small launch that prunes, with more columns than kMaxSplits of them fill the units: scoring and selection ride in the
     // attention launch (its first workgroups), and the step is a handful of launches on the caller's stream.  us a step against
     // the rules above (second stream, or in order): 24 layers of 782 tokens at a budget of 2048, one call each, 58 -> 42 a
@@ -556,9 +563,8 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
                         columns * kMaxSplits > h->n_cus && (cnt == 1 || columns < h->target_wgs);
     const bool beside = may_overlap && !inside && (h->overlap == 2 || (small_launch && (steps == 0.0 || steps >= kOverlapSteps)));
     // a small launch leaves a quarter of the compute units to the chain next to it, or a unit to each of the scoring blocks in it
-    b.g.n_splits = pick_splits(h, b.g, cnt, min_tiles, ((beside && small_launch) || h->target_explicit) ? h->target_wgs : inside ? std::max(1, h->n_cus - side_blocks * cnt) : h->n_cus);
-    // never more splits than the partial-result buffers hold (an explicit "attention_splits" may ask for more)
-    b.g.n_splits = (int32_t)std::max<int64_t>(1, std::min<int64_t>(b.g.n_splits, rows_cap / ((int64_t)cnt * b.g.n_pad)));
+    const int target = ((beside && small_launch) || h->target_explicit) ? h->target_wgs : inside ? std::max(1, h->n_cus - side_blocks * cnt) : h->n_cus;
+    b.g.n_splits = pick_splits(h, b.g, cnt, min_tiles, target, rows_cap);
 
     hipStream_t sb = st;          // stream of the cache-update chain
     if (beside) {

@@ -269,9 +269,30 @@ void scoring_blocks_inside_attention() {
   }
 }
 
+// Several caches with scoring blocks beside them: the buffers hold the split count that the launch's rounds ask for (rounds of
+// the units the blocks leave x (key tiles per range + 5), the merge on top), which a cut count misses by half.
+void split_counts_fit_the_buffers() {
+  struct { int caches, H, n, L; } cases[] = {{2, 6, 1174, 24050}, {2, 12, 425, 24454}, {2, 8, 821, 24218}, {3, 4, 900, 20000}, {4, 4, 300, 16384}, {2, 16, 523, 16384}};
+  for (const auto& x : cases) {
+    Full f(x.caches, x.H, x.n, x.L);
+    CHECK(kv_set_option(f.h, "overlap_update", 1) == KV_OK);
+    const int waits = stub_stream_waits;
+    f.step();
+    const int target = stub_stream_waits > waits ? 192 : 256 - stub_side_blocks * x.caches;
+    const int blocks = (x.n + 31) / 32, qtiles = (blocks + 11) / 12, pad = qtiles * ((blocks + qtiles - 1) / qtiles) * 32, cols = x.caches * x.H * qtiles;
+    const int tiles = (x.L + 63) / 64 + (x.n + 63) / 64;
+    auto cost = [&](int c) { return (cols * c + target - 1) / target * ((double)tiles / c + 5.0) + (c > 1 ? 1.0 + 4e-5 * c * x.caches * x.H * pad : 0.0); };
+    double best = cost(1);
+    for (int c = 2; c <= std::min(16, std::max(4, 2 * target / cols)); ++c) best = std::min(best, cost(c));
+    if (cost(stub_splits) > 1.05 * best) std::fprintf(stderr, "%d caches, %d heads, %d tokens, budget %d: %d splits\n", x.caches, x.H, x.n, x.L, stub_splits);
+    CHECK(cost(stub_splits) <= 1.05 * best);
+  }
+}
+
 }  // namespace
 
 int main() {
+  split_counts_fit_the_buffers();
   scoring_blocks_inside_attention();
   score_block_shapes();
   launch_rules_by_the_device(64, true);
