@@ -176,9 +176,9 @@ inline bool selects_in_score(const KvxBatch& b, int max_tc) {
 // lengths: six caches of 4096 (523 tokens) 113 -> 124 us a step.
 // Where sixteen are not enough the launch waits for them.  What they take then, from steps bound by it (17 to 64 heads, 69 to 780
 // tokens, budgets of 512 to 16384): per 64 positions 0.18 us a head (8-bit codes 0.26) and 0.3, the selection 8 us and 0.08 per 64
-// positions.  Up to 40 us (20 more with every further cache: launches in order take the longer, and so does their issue) that is
+// positions.  Up to 44 us (20 more with every further cache: launches in order take the longer, and so does their issue) that is
 // still the shortest step whatever attention takes: 64 heads, 130 tokens, budget 2048, 50 us against 58 in order and 67 on the
-// second stream; 32 heads at 4096 51, 52 and 66; two caches of 12 heads, 200 tokens, 8192 58, 62 and 85.  Beyond, it has to fit
+// second stream; 32 heads at 4096 51, 52 and 66; two caches of 64 heads at 4096 87, 94 and 96.  Beyond, it has to fit
 // into attention's estimate: 64 heads of 130 tokens at 8192 take 127 us inside, 97 in order and 86 on the second stream, 32 heads
 // of 300 at 16384 141, 117 and 100, but 17 heads of 780 at 16384 114, 126 and 120.
 constexpr int kSideBlocks = 16, kSideBlocksMax = 64;
@@ -191,7 +191,7 @@ inline int side_blocks_of(const KvxBatch& b, int max_tc, double steps) {
   n = n < kSideBlocks ? n : kSideBlocks;
   n = n < blocks ? n : blocks;
   const double us = (double)((blocks + n - 1) / n) * (0.3 + (wide ? 0.26 : 0.18) * H) + 8.0 + 0.08 * blocks;
-  if (steps > 0.0 && us > 20.0 + 20.0 * b.n_items && us > 1.35 * steps) return 0;      // (an explicit split count leaves no estimate)
+  if (steps > 0.0 && us > 24.0 + 20.0 * b.n_items && us > 1.35 * steps) return 0;      // (an explicit split count leaves no estimate)
   return n * b.n_items <= kSideBlocksMax ? n : 0;
 }
 

@@ -256,6 +256,7 @@ struct Full {
 void scoring_blocks_inside_attention() {
   struct { int caches, H, n, L, k_bits, blocks; } cases[] = {
     {1, 16, 1041, 8192, 4, 16},  {1, 16, 782, 2048, 4, 16},  {1, 64, 130, 2048, 4, 16},  {1, 32, 130, 4096, 4, 16},    // short, or under attention
+    {2, 64, 130, 4096, 4, 16},   {1, 40, 130, 4096, 4, 16},
     {1, 17, 780, 16384, 4, 16},  {2, 12, 200, 8192, 4, 16},  {3, 6, 300, 4096, 4, 16},   {1, 24, 1041, 16384, 8, 16},
     {1, 32, 130, 8192, 4, 0},    {1, 32, 300, 16384, 4, 0},  {1, 48, 200, 8192, 4, 0},   {1, 64, 130, 24576, 4, 0},    // outlast it
     {1, 64, 300, 8192, 4, 0},    {1, 16, 400, 16384, 8, 0},  {1, 32, 400, 16384, 8, 0},
