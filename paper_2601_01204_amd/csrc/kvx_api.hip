@@ -201,7 +201,9 @@ int validate(const kv_config* c) {
   return KV_OK;
 }
 
-constexpr double kOverlapSteps = 13.0;   // attention estimate (tile steps) from which the second stream pays
+// Attention's own estimate (tile steps, without the merge) from which the second stream pays; a tile step of fp32 inputs takes
+// the longer.
+constexpr double kOverlapSteps = 13.0, kOverlapStepsF32 = 11.0;
 
 // Key-range splits per (item, head, query tile) column.  A workgroup occupies a compute unit by itself, so a launch runs in
 // rounds of `target_wgs` workgroups; the estimate is rounds x (tiles per workgroup + kWorkgroupTiles) plus, with splits, the
@@ -212,8 +214,9 @@ constexpr double kOverlapSteps = 13.0;   // attention estimate (tile steps) from
 // caches of 4096 2 ranges 763, one 708.  Where the two agree (one cache of 2048 to 16384, 6 of 8192, 24 of 16384, eight of
 // 4096) nothing measured is better than the choice.
 constexpr double kWorkgroupTiles = 5.0, kMergeTilesPerRow = 4e-5;
+struct Estimate { double attention = 0.0, step = 0.0; };      // tile steps: of the attention launch, and with the merge (0: an explicit count)
 // rows_cap: (cache, split) slots x padded query rows the partial-result buffers hold; the choice is among the counts that fit.
-int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tiles, int target_wgs, int64_t rows_cap, double* estimate = nullptr) {
+int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tiles, int target_wgs, int64_t rows_cap, Estimate* estimate = nullptr) {
   const int fit = (int)std::max<int64_t>(1, std::min<int64_t>(kMaxSplits, rows_cap / ((int64_t)n_items * g.n_pad)));
   int s;
   if (h->splits_override > 0) {
@@ -225,14 +228,16 @@ int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tile
     const int cap = (int)std::min<int64_t>(fit, std::max<int64_t>(4, (2 * (int64_t)target_wgs) / base));
     double best = 0.0;
     s = 1;
-    if (estimate) *estimate = 0.0;
     for (int c = 1; c <= cap; ++c) {
       const int64_t rounds = (base * c + target_wgs - 1) / target_wgs;
-      const double cost = (double)rounds * ((double)tiles / c + kWorkgroupTiles) +
-                          (c > 1 ? 1.0 + kMergeTilesPerRow * c * (double)n_items * g.H * g.n_pad : 0.0);
-      if (c == 1 || cost < best * 0.99) { best = cost; s = c; }
+      const double alone = (double)rounds * ((double)tiles / c + kWorkgroupTiles);
+      const double cost = alone + (c > 1 ? 1.0 + kMergeTilesPerRow * c * (double)n_items * g.H * g.n_pad : 0.0);
+      if (c == 1 || cost < best * 0.99) {
+        best = cost;
+        s = c;
+        if (estimate) *estimate = {alone, cost};
+      }
     }
-    if (estimate) *estimate = best;
   }
   s = std::max(1, std::min(s, fit));      // (an explicit "attention_splits" may ask for more)
   s = std::min(s, std::max(1, min_tiles));
@@ -542,13 +547,13 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     const bool may_overlap = h->overlap != 0 && h->side && !g0.uncompressed && !update_first;
     const bool small_launch = (int64_t)cnt * g0.H * g0.n_qtiles <= (int64_t)h->n_cus;
     // The fork and the join cost the host about 40 us a call (an event record and a wait each), so that a call with the
-    // second stream issues in 60 us or more and one without in 20 to 27.  A short attention launch is not worth that.  In order
-    // and beside, us a step, calls back to back, with all the parts in launches of their own: 69 tokens, fp32, 34 and 59; 400 at
-    // a budget of 1024 47 and 64; 523 at 2048 57 and 64; 1374 at 2800, 6 heads, 61 and 62; 1041 at 2400 70 and 60, at 4096 81
-    // and 66.  Where other work of the GPU hides the issue the two meet earlier (523 at 1500 58 and 54).
+    // second stream issues in 60 us or more and one without in 20 to 27.  A short attention launch is not worth that, and its
+    // merge, which shares the rebuild launch in order, does not count.  In order and beside, us a step of one cache, calls back to
+    // back (tile steps): bf16, 16 heads of 384 tokens at 3000 50 and 66 (8.8), at 4096 52 and 64 (9.7), at 6000 57 and 61 (11.3),
+    // at 8192 63 and 63 (13.4), at 24576 115 and 90 (30); fp32 inputs 59 and 65, 62 and 65, 70 and 66, 79 and 68, 150 and 125.
     // A launch lasts as long as its longest cache, so the estimate goes by that one: a stream that starts beside a full
     // cache of 16384 tokens (523 tokens a frame, 6 heads) takes 107 us a step in order and 82 beside.
-    double steps = 0.0;
+    Estimate steps;
     pick_splits(h, b.g, cnt, max_tiles, h->n_cus, rows_cap, &steps);
     // A small launch that prunes, with more columns than kMaxSplits of them fill the units: scoring and selection ride in the
     // attention launch (its first workgroups), and the step is a handful of launches on the caller's stream.  us a step against
@@ -557,11 +562,11 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     // 193 -> 177.  With fewer columns attention leaves most of the chip idle whatever the split, and with several caches that
     // take three quarters of it in one round the second stream has the rest (six caches of 523 tokens at 4096: 116, inside
     // 118): there the rules above stand.
-    const int side_blocks = side_blocks_of(b, max_tc, steps);
+    const int side_blocks = side_blocks_of(b, max_tc, steps.step);
     const int64_t columns = (int64_t)cnt * g0.H * b.g.n_qtiles;
     const bool inside = may_overlap && h->overlap == 1 && any_prune && side_blocks > 0 && columns + side_blocks * cnt <= h->n_cus &&
                         columns * kMaxSplits > h->n_cus && (cnt == 1 || columns < h->target_wgs);
-    const bool beside = may_overlap && !inside && (h->overlap == 2 || (small_launch && (steps == 0.0 || steps >= kOverlapSteps)));
+    const bool beside = may_overlap && !inside && (h->overlap == 2 || (small_launch && (steps.attention == 0.0 || steps.attention >= (g0.in_f32 ? kOverlapStepsF32 : kOverlapSteps))));
     // a small launch leaves a quarter of the compute units to the chain next to it, or a unit to each of the scoring blocks in it
     const int target = ((beside && small_launch) || h->target_explicit) ? h->target_wgs : inside ? std::max(1, h->n_cus - side_blocks * cnt) : h->n_cus;
     b.g.n_splits = pick_splits(h, b.g, cnt, min_tiles, target, rows_cap);

@@ -241,10 +241,10 @@ struct Full {
   kv_config c;
   std::vector<uint16_t> q;
   std::vector<kv_step_item> items;
-  Full(int caches, int H, int n, int L, int k_bits = 4, int frames = 1) : c(base_config(KV_META_F32, KV_LAYOUT_COMPACT, k_bits, 64, 4, 64)), items(caches) {
-    c.n_streams = caches; c.n_layers = 1; c.n_heads = H; c.tokens_per_frame = n; c.budget_tokens = L; c.max_frames_per_step = frames;
+  Full(int caches, int H, int n, int L, int k_bits = 4, int frames = 1, int dtype = KV_BF16) : c(base_config(KV_META_F32, KV_LAYOUT_COMPACT, k_bits, 64, 4, 64)), items(caches) {
+    c.n_streams = caches; c.n_layers = 1; c.n_heads = H; c.tokens_per_frame = n; c.budget_tokens = L; c.max_frames_per_step = frames; c.in_dtype = dtype;
     CHECK(kv_init(&c, &h) == KV_OK && h);
-    q.resize((size_t)frames * n * H * 64);
+    q.resize((size_t)frames * n * H * 64 * (dtype == KV_F32 ? 2 : 1));
     for (int i = 0; i < caches; ++i) { items[i].stream = i; items[i].layer = 0; items[i].q = items[i].k = items[i].v = items[i].out = q.data(); }
     for (int t = 0; t < L; t += n) step();
   }
@@ -267,6 +267,18 @@ void scoring_blocks_inside_attention() {
     f.step();
     if (stub_side_blocks != x.blocks) std::fprintf(stderr, "%d caches, %d heads, %d tokens, budget %d: %d blocks\n", x.caches, x.H, x.n, x.L, stub_side_blocks);
     CHECK(stub_side_blocks == x.blocks);
+  }
+}
+
+// The merge does not count towards an attention launch that is long enough for the second stream; fp32 inputs are sooner.
+void second_stream_by_attention_alone() {
+  struct { int L; bool f32, beside; } cases[] = {{3000, false, false}, {4096, false, false}, {6000, false, false}, {8192, false, true},
+                                                 {3000, true, false}, {4096, true, false}, {6000, true, true}, {8192, true, true}};
+  for (const auto& x : cases) {
+    Full f(1, 16, 384, x.L, 4, 1, x.f32 ? KV_F32 : KV_BF16);
+    const int waits = stub_stream_waits;
+    f.step();
+    CHECK(stub_stream_waits - waits == (x.beside ? 2 : 0));
   }
 }
 
@@ -293,6 +305,7 @@ void split_counts_fit_the_buffers() {
 }  // namespace
 
 int main() {
+  second_stream_by_attention_alone();
   split_counts_fit_the_buffers();
   scoring_blocks_inside_attention();
   score_block_shapes();
