@@ -284,8 +284,12 @@ enum kv_kernel_id {
 /* Measurement aid: while bit (1 << id) of kernel_mask is set, every launch of that class
  * is bracketed by HIP events recorded on the stream it runs on.  kv_read_timing waits
  * for the recorded events, writes per class the summed duration in milliseconds and the
- * number of launches (host arrays of KV_K_COUNT entries) and clears the record.  While
- * either rebuild class is timed, key and value rebuild are launched separately. */
+ * number of launches (host arrays of KV_K_COUNT entries) and clears the record.  A call
+ * that is timed runs as an untimed one does, except that a timed part has a launch of its
+ * own where it would share one: scoring and selection (timed: neither is inside the other's
+ * launch or attention's), the merge (timed, or a rebuild class: not inside the rebuild's), key and
+ * value rebuild (either timed: a launch each).  Attention's time is its launch's, with the
+ * scoring and selection that ride in it unless one of those is timed as well. */
 int kv_set_timing(kv_handle* h, uint32_t kernel_mask);
 int kv_read_timing(kv_handle* h, float* total_ms, int32_t* launches);
 

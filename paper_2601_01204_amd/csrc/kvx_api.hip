@@ -244,8 +244,12 @@ int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tile
   return s;
 }
 
+// Whether this call times a launch class, or either of two.
+bool times(const kv_handle* h, int kernel) { return h->timing_now && (h->timing_mask & (1u << kernel)); }
+bool times(const kv_handle* h, int a, int b) { return times(h, a) || times(h, b); }
+
 void record(kv_handle* h, int kernel, bool start, hipStream_t st) {
-  if (!h->timing_now || !(h->timing_mask & (1u << kernel))) return;
+  if (!times(h, kernel)) return;
   if (start) {
     TimedLaunch t;
     if (!h->free_events.empty()) {
@@ -268,7 +272,7 @@ void record(kv_handle* h, int kernel, bool start, hipStream_t st) {
 // An event pair for a launch that stamps its own events (nothing is recorded here).
 void timed_pair(kv_handle* h, int kernel, hipEvent_t* start, hipEvent_t* stop) {
   *start = *stop = nullptr;
-  if (!h->timing_now || !(h->timing_mask & (1u << kernel))) return;
+  if (!times(h, kernel)) return;
   TimedLaunch t;
   if (!h->free_events.empty()) {
     t = h->free_events.back();
@@ -286,7 +290,7 @@ void timed_pair(kv_handle* h, int kernel, hipEvent_t* start, hipEvent_t* stop) {
 
 // The cache rewrite: keys and values in one launch, or in one each while their times are recorded.
 void enqueue_rebuild(kv_handle* h, const KvxBatch& b, int max_tnew, hipStream_t st) {
-  if (!h->timing_now || !(h->timing_mask & ((1u << KV_K_REBUILD_K) | (1u << KV_K_REBUILD_V)))) {
+  if (!times(h, KV_K_REBUILD_K, KV_K_REBUILD_V)) {
     launch_rebuild(b, max_tnew, true, true, st);
     return;
   }
@@ -583,17 +587,18 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     // writes are still on their way when the next call pools and scores, 24 caches of 16384 tokens 70 -> 81 us for the two.)
     const bool rebuild_after = !g0.uncompressed && !update_first &&
                                (g0.slots || inside || (sb == st && rebuild_blocks(b, max_tnew) <= kMergedBlocks));
-    // (while the parts are timed they are launched one by one)
-    b.g.merge = rebuild_after && !h->timing_now;
-    b.g.score_selects = selects_in_score(b, max_tc) && !h->timing_now;
-    if (inside && !h->timing_now) b.g.side_blocks = side_blocks;      // per cache
+    // (a part that is timed has a launch of its own; the others stay as they are)
+    const bool score_apart = times(h, KV_K_SCORE, KV_K_SELECT);
+    b.g.merge = rebuild_after && !times(h, KV_K_COMBINE) && !times(h, KV_K_REBUILD_K, KV_K_REBUILD_V);
+    b.g.score_selects = selects_in_score(b, max_tc) && !score_apart;
+    if (inside && !score_apart) b.g.side_blocks = side_blocks;      // per cache
     if (!g0.uncompressed) {
-      if (b.g.side_blocks) {
-        launch_pool(b, max_tc, st);
-      } else if (any_prune) {
+      if (any_prune) {
         record(h, KV_K_POOL, true, sb);
         launch_pool(b, max_tc, sb);
         record(h, KV_K_POOL, false, sb);
+      }
+      if (any_prune && !b.g.side_blocks) {
         record(h, KV_K_SCORE, true, sb);
         launch_score(b, max_tc, sb);
         record(h, KV_K_SCORE, false, sb);

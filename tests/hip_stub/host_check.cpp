@@ -282,6 +282,28 @@ void second_stream_by_attention_alone() {
   }
 }
 
+// A timed call keeps the schedule of an untimed one but for the parts that are timed.
+void timing_parts_only_what_it_times() {
+  struct { int H, n, L, timed, side, merge, selects; } cases[] = {
+    {16, 1041, 8192, -1, 16, 1, 0},            {16, 1041, 8192, KV_K_ATTENTION, 16, 1, 0}, {16, 1041, 8192, KV_K_POOL, 16, 1, 0},
+    {16, 1041, 8192, KV_K_SCORE, 0, 1, 0},     {16, 1041, 8192, KV_K_SELECT, 0, 1, 0},     {16, 1041, 8192, KV_K_COMBINE, 16, 0, 0},
+    {16, 1041, 8192, KV_K_REBUILD_K, 16, 0, 0}, {16, 1041, 8192, KV_K_REBUILD_V, 16, 0, 0},
+    {4, 69, 256, -1, 0, 1, 1},                 {4, 69, 256, KV_K_ATTENTION, 0, 1, 1},      {4, 69, 256, KV_K_SCORE, 0, 1, 0},
+    {4, 69, 256, KV_K_SELECT, 0, 1, 0},        {4, 69, 256, KV_K_COMBINE, 0, 0, 1},
+  };
+  for (const auto& x : cases) {
+    Full f(1, x.H, x.n, x.L);
+    CHECK(kv_set_timing(f.h, x.timed < 0 ? 0u : 1u << x.timed) == KV_OK);
+    const int waits = stub_stream_waits;
+    f.step();
+    CHECK(stub_side_blocks == x.side && stub_merge == x.merge && stub_score_selects == x.selects && stub_stream_waits == waits);
+    float ms[KV_K_COUNT];
+    int32_t launches[KV_K_COUNT];
+    CHECK(kv_read_timing(f.h, ms, launches) == KV_OK);
+    for (int k = 0; k < KV_K_COUNT; ++k) CHECK(launches[k] == (k == x.timed ? 1 : 0));
+  }
+}
+
 // Several caches with scoring blocks beside them: the buffers hold the split count that the launch's rounds ask for (rounds of
 // the units the blocks leave x (key tiles per range + 5), the merge on top), which a cut count misses by half.
 void split_counts_fit_the_buffers() {
@@ -305,6 +327,7 @@ void split_counts_fit_the_buffers() {
 }  // namespace
 
 int main() {
+  timing_parts_only_what_it_times();
   second_stream_by_attention_alone();
   split_counts_fit_the_buffers();
   scoring_blocks_inside_attention();
