@@ -222,7 +222,8 @@ def aux_vggt_layer(torch, kvx, si, dev, steps):
     w = si.WORKLOADS["vggt_layer"]
     n, H, d = w.tokens_per_frame, w.n_heads, w.head_dim
     fill = -(-w.budget_tokens // n) + 1
-    out = {"workload": "vggt_layer: 1 layer, budget 8192, INT4/INT4 g64, one cache per call"}
+    out = {"workload": "vggt_layer: 1 layer, budget 8192, INT4/INT4 g64, one cache per call",
+           "attention_us": "the attention launch, with the scoring and selection that ride in it; from calls after the timed ones"}
     variants = (("kv_step", dict(), 1), ("kv_step_meta16", dict(meta_format=kvx.KV_META_F16), 1),
                 ("kv_step_frames_4", dict(max_frames_per_step=4), 4),
                 ("kv_step_frames_4_meta16", dict(max_frames_per_step=4, meta_format=kvx.KV_META_F16), 4),
@@ -239,14 +240,17 @@ def aux_vggt_layer(torch, kvx, si, dev, steps):
         calls = max(steps // F, 10)
         for i in range(fill + 3):
             call(i)
-        run.h.set_option("timing_every", 8 if F == 1 else 1)
-        run.h.set_timing(1)
         torch.cuda.synchronize()
         t0 = time.perf_counter()
         for i in range(calls):
             call(i)
         torch.cuda.synchronize()
         dt = time.perf_counter() - t0
+        run.h.set_option("timing_every", 1)
+        run.h.set_timing(1)
+        for i in range(min(calls, 50)):
+            call(calls + i)
+        torch.cuda.synchronize()
         ms, cnt = run.h.read_timing()["attention"]
         run.h.set_timing(0)
         a_us = ms * 1e3 / max(cnt, 1)
