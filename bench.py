@@ -27,7 +27,7 @@ PEAK_HBM_GBS = 8000.0          # MI355X HBM3E
 # HBM bytes per launch of the dominant kernel come from a rocprofv3 --pmc run whose summary and figures are
 # tracked in profiles/; the file names the sources it was measured on, and a stale file yields traffic = null.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "attn_kernel_vggt_stack_traffic.json")
-KERNEL_SOURCES = ("attn.hip", "attn16.hip", "attn_tile.h", "kvx_dev.h")
+KERNEL_SOURCES = ("attn.hip", "attn16.hip", "attn_tile.h", "combine_block.h", "kvx_dev.h", "score_block.h", "score_select.h", "select_block.h")
 
 
 def kernel_source_hash() -> str:
