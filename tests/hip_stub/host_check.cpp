@@ -243,6 +243,7 @@ struct Full {
   std::vector<kv_step_item> items;
   Full(int caches, int H, int n, int L, int k_bits = 4, int frames = 1, int dtype = KV_BF16) : c(base_config(KV_META_F32, KV_LAYOUT_COMPACT, k_bits, 64, 4, 64)), items(caches) {
     c.n_streams = caches; c.n_layers = 1; c.n_heads = H; c.tokens_per_frame = n; c.budget_tokens = L; c.max_frames_per_step = frames; c.in_dtype = dtype;
+    c.n_special = std::min(c.n_special, n);
     CHECK(kv_init(&c, &h) == KV_OK && h);
     q.resize((size_t)frames * n * H * 64 * (dtype == KV_F32 ? 2 : 1));
     for (int i = 0; i < caches; ++i) { items[i].stream = i; items[i].layer = 0; items[i].q = items[i].k = items[i].v = items[i].out = q.data(); }
@@ -267,6 +268,43 @@ void scoring_blocks_inside_attention() {
     f.step();
     if (stub_side_blocks != x.blocks) std::fprintf(stderr, "%d caches, %d heads, %d tokens, budget %d: %d blocks\n", x.caches, x.H, x.n, x.L, stub_side_blocks);
     CHECK(stub_side_blocks == x.blocks);
+  }
+}
+
+// The calls by which the GPU tests check scoring and selection inside the attention launch do have them there; a static call too.
+void the_tested_calls_take_the_tested_launch() {
+  struct { int caches, H, n, L, k_bits, splits, blocks; } cases[] = {
+    {1, 17, 3, 40, 4, 0, 1},      {1, 20, 60, 130, 2, 0, 3},     {1, 64, 40, 200, 4, 0, 4},      {1, 17, 129, 1100, 8, 0, 16},
+    {1, 18, 130, 1230, 4, 0, 16}, {1, 17, 64, 2304, 2, 0, 16},   {1, 17, 900, 32768, 4, 4, 16},  {3, 8, 70, 1100, 4, 1, 16},
+    {1, 20, 133, 700, 4, 3, 9},
+  };
+  for (const auto& x : cases) {
+    Full f(x.caches, x.H, x.n, x.L, x.k_bits);
+    CHECK(kv_set_option(f.h, "attention_splits", x.splits) == KV_OK);
+    for (int is_static = 0; is_static < (x.caches == 1 && x.n < 900 ? 2 : 1); ++is_static) {
+      const kv_step_item& it = f.items[0];
+      if (is_static) CHECK(kv_step_static(f.h, 0, 0, it.q, it.k, it.v, (int64_t)x.H * 64, 64, it.out, nullptr) == KV_OK);
+      else f.step();
+      if (stub_side_blocks != x.blocks) std::fprintf(stderr, "%d caches, %d heads, %d tokens, budget %d: %d blocks\n", x.caches, x.H, x.n, x.L, stub_side_blocks);
+      CHECK(stub_side_blocks == x.blocks && stub_merge == 1);
+    }
+    CHECK(kv_set_option(f.h, "overlap_update", 0) == KV_OK);
+    f.step();
+    CHECK(stub_side_blocks == 0);
+  }
+}
+
+// A scoring launch of up to 32 blocks selects; a rewrite in order of up to 32768 blocks takes the merge along.
+void shared_launches() {
+  struct { int caches, H, n, L, selects, merge; } cases[] = {
+    {1, 4, 64, 2112, 1, 1}, {1, 4, 64, 2113, 0, 1}, {2, 4, 64, 1088, 1, 1}, {2, 4, 64, 1089, 0, 1},
+    {1, 64, 64, 21632, 0, 1}, {1, 64, 64, 22016, 0, 0},
+  };
+  for (const auto& x : cases) {
+    Full f(x.caches, x.H, x.n, x.L);
+    CHECK(kv_set_option(f.h, "overlap_update", 0) == KV_OK);
+    f.step();
+    CHECK(stub_score_selects == x.selects && stub_merge == x.merge);
   }
 }
 
@@ -327,6 +365,8 @@ void split_counts_fit_the_buffers() {
 }  // namespace
 
 int main() {
+  the_tested_calls_take_the_tested_launch();
+  shared_launches();
   timing_parts_only_what_it_times();
   second_stream_by_attention_alone();
   split_counts_fit_the_buffers();

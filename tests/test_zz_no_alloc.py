@@ -50,6 +50,11 @@ def test_static_scratch_step_matches_kv_step_twice_in_a_row():
     _pair_run(small, 6, 3)
 
 
+def test_static_scratch_step_with_scoring_inside_attention():
+    """More than 16 workgroup columns: scoring and selection ride in the attention launch of both entry points."""
+    _pair_run(si.Workload("static_inside", 20, 64, 133, 5, 16, 700, 8, 1, 1, 4, 64, 4, 64, "bf16", 44), 8, 3)
+
+
 def test_static_scratch_step_rejects_frames_beyond_the_array():
     import torch
     import paper_2601_01204_amd as kvx
