@@ -25,42 +25,11 @@
 
 namespace kvx {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
+using namespace tile;      // the operand types, conversions and limits of the other kernel
 
-constexpr int kLdsRow = 72;                       // 16-bit elements per LDS row: 64 + 8 pad (144 B)
-constexpr int kTileElems = kTileK * kLdsRow;      // one K or V^T tile
-constexpr float kNegBig = -1.0e30f;
-constexpr float kRescaleGap = 8.0f;               // log2 units
 constexpr int kAttnMaxWaves = 12;                 // waves (= 32-row query blocks) per workgroup, three per SIMD
-constexpr float kSumLimit = 1.0e37f;              // a row sum at or above this (or NaN) saw an f16 overflow
 
 #define KVX_FENCE() __builtin_amdgcn_sched_barrier(0)
-
-__device__ __forceinline__ int swap23(int x) { return (x & ~0xC) | ((x & 4) << 1) | ((x & 8) >> 1); }
-
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-  const f32x2 x = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, bf16x2));
-}
-// Two fp32 values -> packed f16, round to nearest even (v_cvt_pk_f16_f32).
-__device__ __forceinline__ uint32_t pack_f16(float a, float b) {
-  const f32x2 x = {a, b};
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector(x, f16x2));
-}
-// Two fp32 values -> packed bf16 truncations (hi) and packed bf16 truncated remainders (lo).
-__device__ __forceinline__ void split_bf16(float a, float b, uint32_t& hi, uint32_t& lo) {
-  const uint32_t ua = __float_as_uint(a), ub = __float_as_uint(b);
-  hi = __builtin_amdgcn_perm(ub, ua, 0x07060302u);          // the upper halves of a (low) and b (high)
-  const float ra = a - __uint_as_float(ua & 0xFFFF0000u), rb = b - __uint_as_float(ub & 0xFFFF0000u);
-  lo = __builtin_amdgcn_perm(__float_as_uint(rb), __float_as_uint(ra), 0x07060302u);
-}
-__device__ __forceinline__ float bf16lo_to_f32(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float bf16hi_to_f32(uint32_t w) { return __uint_as_float(w & 0xFFFF0000u); }
 
 // The codes of eight consecutive channels of one row: 2, 4 or 8 bytes.
 template <int B> struct Octet;
@@ -68,35 +37,13 @@ template <> struct Octet<2> { typedef uint16_t type; };
 template <> struct Octet<4> { typedef uint32_t type; };
 template <> struct Octet<8> { typedef uint2 type; };
 
-template <int B>
-__device__ __forceinline__ int octet_code(const typename Octet<B>::type& w, int e) {
-  if constexpr (B == 4) return (int)((w >> (4 * e)) & 0xFu);
-  else if constexpr (B == 2) return (int)(((uint32_t)w >> (2 * e)) & 0x3u);
-  else return (int)(((e < 4 ? w.x : w.y) >> (8 * (e & 3))) & 0xFFu);
-}
-
-// The same eight codes as floats.  Bytes convert in one instruction each, so 4-bit codes
-// are first spread into the bytes of two words (even and odd channels).
-// Byte K of a word as a float (v_cvt_f32_ubyteK; written out because the compiler would
-// otherwise merge the nibble masks below back into one bit-field extract per value).
-template <int K>
-__device__ __forceinline__ float byte_to_float(uint32_t w) {
-  float f;
-  if constexpr (K == 0) asm("v_cvt_f32_ubyte0 %0, %1" : "=v"(f) : "v"(w));
-  else if constexpr (K == 1) asm("v_cvt_f32_ubyte1 %0, %1" : "=v"(f) : "v"(w));
-  else if constexpr (K == 2) asm("v_cvt_f32_ubyte2 %0, %1" : "=v"(f) : "v"(w));
-  else asm("v_cvt_f32_ubyte3 %0, %1" : "=v"(f) : "v"(w));
-  return f;
-}
+// The same eight codes as floats.
 template <int B>
 __device__ __forceinline__ void octet_floats(const typename Octet<B>::type& w, float (&f)[8]) {
   if constexpr (B == 8) {
-    f[0] = byte_to_float<0>(w.x); f[1] = byte_to_float<1>(w.x); f[2] = byte_to_float<2>(w.x); f[3] = byte_to_float<3>(w.x);
-    f[4] = byte_to_float<0>(w.y); f[5] = byte_to_float<1>(w.y); f[6] = byte_to_float<2>(w.y); f[7] = byte_to_float<3>(w.y);
+    bytes_to_floats(w.x, w.y, f);
   } else if constexpr (B == 4) {
-    const uint32_t ev = w & 0x0F0F0F0Fu, od = (w >> 4) & 0x0F0F0F0Fu;
-    f[0] = byte_to_float<0>(ev); f[2] = byte_to_float<1>(ev); f[4] = byte_to_float<2>(ev); f[6] = byte_to_float<3>(ev);
-    f[1] = byte_to_float<0>(od); f[3] = byte_to_float<1>(od); f[5] = byte_to_float<2>(od); f[7] = byte_to_float<3>(od);
+    nibbles_to_floats(w, f);
   } else {
 #pragma unroll
     for (int e = 0; e < 8; ++e) f[e] = (float)(((uint32_t)w >> (2 * e)) & 0x3u);
@@ -137,7 +84,7 @@ template <int KB, int VB, int N>
 __global__ __launch_bounds__(kAttnMaxWaves * 64) void attn_kernel(const KvxBatchT<N> b) {
   const Geometry& g = b.g;
   int bid, qt;
-  tile::decode_block(blockIdx.x, g.H * g.n_splits * b.n_items, g.n_qtiles, bid, qt);
+  decode_block(blockIdx.x, g.H * g.n_splits * b.n_items, g.n_qtiles, bid, qt);
   const int h = bid % g.H; bid /= g.H;
   const int split = bid % g.n_splits; bid /= g.n_splits;
   const int item_idx = bid;
@@ -652,14 +599,14 @@ static void launch_attn_t(const KvxBatch& b, hipStream_t st, hipEvent_t ev_start
   else with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((attn_kernel<KB, VB, KVX_ITEMS(bb)>), grid, block, 0, st, bb); });
 }
 
-void launch_attention(const KvxBatch& b, int /*max_tiles*/, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (b.g.uncompressed && !b.g.in_f32) { tile::launch_tile<tile::kBf16, 16, 16>(b, st, ev_start, ev_stop); return; }
+void launch_attention(const KvxBatch& b, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  if (b.g.uncompressed && !b.g.in_f32) { launch_tile<kBf16, 16, 16>(b, st, ev_start, ev_stop); return; }
   // fp32 inputs over an uncompressed cache: the code widths play no part
   const int kb = b.g.uncompressed ? 4 : b.g.k_bits, vb = b.g.uncompressed ? 4 : b.g.v_bits;
 #define KVX_CASE(K, V) \
   if (kb == K && vb == V) { \
     if (b.g.in_f32) launch_attn_t<K, V>(b, st, ev_start, ev_stop); \
-    else tile::launch_tile<tile::kMeta32, K, V>(b, st, ev_start, ev_stop); \
+    else launch_tile<kMeta32, K, V>(b, st, ev_start, ev_stop); \
     return; \
   }
   KVX_CASE(4, 4) KVX_CASE(8, 8) KVX_CASE(2, 4) KVX_CASE(2, 2) KVX_CASE(4, 8) KVX_CASE(8, 4) KVX_CASE(4, 2) KVX_CASE(2, 8) KVX_CASE(8, 2)

@@ -89,7 +89,6 @@ __device__ __forceinline__ uint4 bf16_octet_to_half_pairs(const uint4& r) {
                     pack_f16(bf16lo_to_f32(r.y), bf16lo_to_f32(r.w)), pack_f16(bf16hi_to_f32(r.y), bf16hi_to_f32(r.w)));
 }
 
-
 // Code words as they are loaded: four bytes (8-bit value codes in the launch: eight) with the codes of eight consecutive
 // channels of a row somewhere in them; 2-bit codes take half a word, `sel` says which (a v_perm selector).
 typedef uint32_t u32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
@@ -124,27 +123,13 @@ __device__ __forceinline__ void val_pairs(const W& a, const W& b, uint32_t sel, 
   }
 }
 
-// The codes of eight channels as floats.  Bytes convert in one instruction each, so 4-bit codes are first spread into the
-// bytes of two words (even and odd channels); written out because the compiler would merge the masks into one bit-field
-// extract per value.  half_shift: 16 where the eight 2-bit codes are in the word's upper half.
-template <int K>
-__device__ __forceinline__ float byte_to_float(uint32_t w) {
-  float f;
-  if constexpr (K == 0) asm("v_cvt_f32_ubyte0 %0, %1" : "=v"(f) : "v"(w));
-  else if constexpr (K == 1) asm("v_cvt_f32_ubyte1 %0, %1" : "=v"(f) : "v"(w));
-  else if constexpr (K == 2) asm("v_cvt_f32_ubyte2 %0, %1" : "=v"(f) : "v"(w));
-  else asm("v_cvt_f32_ubyte3 %0, %1" : "=v"(f) : "v"(w));
-  return f;
-}
+// The codes of eight channels as floats.  half_shift: 16 where the eight 2-bit codes are in the word's upper half.
 template <int B, typename W>
 __device__ __forceinline__ void code_floats(const W& w, uint32_t half_shift, float (&f)[8]) {
   if constexpr (B == 8) {
-    f[0] = byte_to_float<0>(w.x); f[1] = byte_to_float<1>(w.x); f[2] = byte_to_float<2>(w.x); f[3] = byte_to_float<3>(w.x);
-    f[4] = byte_to_float<0>(w.y); f[5] = byte_to_float<1>(w.y); f[6] = byte_to_float<2>(w.y); f[7] = byte_to_float<3>(w.y);
+    bytes_to_floats(w.x, w.y, f);
   } else if constexpr (B == 4) {
-    const uint32_t ev = w.x & 0x0F0F0F0Fu, od = (w.x >> 4) & 0x0F0F0F0Fu;
-    f[0] = byte_to_float<0>(ev); f[2] = byte_to_float<1>(ev); f[4] = byte_to_float<2>(ev); f[6] = byte_to_float<3>(ev);
-    f[1] = byte_to_float<0>(od); f[3] = byte_to_float<1>(od); f[5] = byte_to_float<2>(od); f[7] = byte_to_float<3>(od);
+    nibbles_to_floats(w.x, f);
   } else {
     const uint32_t x = w.x >> half_shift;
 #pragma unroll
@@ -221,7 +206,6 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31;
   const int hf = lane >> 5;
-
 
   const int n = g.n_new;                                  // query rows = the call's own keys: one frame, or a chunk of frames
   const int t_c = it.t_c;

@@ -150,8 +150,8 @@ int fail(kv_handle* h, int code, const char* fmt, ...) {
 
 bool is_bits(int b) { return b == 2 || b == 4 || b == 8; }
 
-// Query tiling of a call that brings `rows` query rows: an attention workgroup holds up to 12 waves, one 32-row
-// query block each; the blocks are spread evenly over the fewest workgroups.
+// Query tiling of a call that brings `rows` query rows: an attention workgroup takes up to twelve 32-row query blocks; the blocks
+// are spread evenly over the fewest workgroups.
 void set_query_tiling(Geometry& g, int rows) {
   const int nblocks = (rows + 31) / 32;
   const int tile_blocks = 12;
@@ -625,11 +625,11 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
           ba.items[i].t_c = std::min(b.items[i].t_c + n_new, g0.budget);
         }
         if (g0.meta16) launch_attention16(ba, st, e0, e1);
-        else launch_attention(ba, 0, st, e0, e1);
+        else launch_attention(ba, st, e0, e1);
       } else if (g0.meta16) {
         launch_attention16(b, st, e0, e1);
       } else {
-        launch_attention(b, 0, st, e0, e1);
+        launch_attention(b, st, e0, e1);
       }
     }
     if (!b.g.merge) {

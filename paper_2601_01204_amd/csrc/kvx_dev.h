@@ -11,7 +11,6 @@ namespace kvx {
 
 constexpr int kHeadDim = 64;        // d; the kernels are written for 64 channels per head
 constexpr int kTileK = 64;          // keys per attention tile / tokens per rebuild block
-constexpr int kQTileMax = 384;      // most query rows per attention workgroup (12 waves x 32)
 constexpr int kMaxItems = 48;       // caches per launch (bounded by the kernel-argument size)
 constexpr int kMaxSplits = 16;      // key-range splits per attention workgroup column
 
@@ -82,7 +81,7 @@ struct Geometry {
   int32_t n_splits;
   int32_t n_pad;          // query rows of this call padded to n_qtiles * q_blocks * 32
   int32_t n_qtiles;       // query tiles (attention workgroups per head and key split)
-  int32_t q_blocks;       // 32-row query blocks per tile (<= 12, one per wave)
+  int32_t q_blocks;       // 32-row query blocks per tile (<= 12; fp32 inputs: a wave each, bf16: eight waves of up to two)
   float scale_log2;       // softmax scale * log2(e)
   float inv_scale_log2;   // fp32(1 / scale_log2): s = a * inv_scale_log2 in the 16-bit metadata format
   int32_t meta16;         // 1: 16-bit scales and zero-points
@@ -215,6 +214,30 @@ inline int score_waves(int H, int k_bits, int blocks, int n_cus) {
 // LDS of a scoring block: two groups' factors a and b of each wave, then the dots of every head.
 inline size_t score_lds_bytes(int H, int waves) { return (size_t)(waves * 4 * kHeadDim + H * 64) * 4; }
 
+// ---- codes as floats ---------------------------------------------------------------
+// Byte K of a word as a float (v_cvt_f32_ubyteK; written out because the compiler would merge the masks of 4-bit codes into one
+// bit-field extract per value).
+template <int K>
+__device__ __forceinline__ float byte_to_float(uint32_t w) {
+  float f;
+  if constexpr (K == 0) asm("v_cvt_f32_ubyte0 %0, %1" : "=v"(f) : "v"(w));
+  else if constexpr (K == 1) asm("v_cvt_f32_ubyte1 %0, %1" : "=v"(f) : "v"(w));
+  else if constexpr (K == 2) asm("v_cvt_f32_ubyte2 %0, %1" : "=v"(f) : "v"(w));
+  else asm("v_cvt_f32_ubyte3 %0, %1" : "=v"(f) : "v"(w));
+  return f;
+}
+// Eight 8-bit codes (two words), and eight 4-bit codes (one), which are first spread into the bytes of two words (even and odd
+// channels).
+__device__ __forceinline__ void bytes_to_floats(uint32_t x, uint32_t y, float (&f)[8]) {
+  f[0] = byte_to_float<0>(x); f[1] = byte_to_float<1>(x); f[2] = byte_to_float<2>(x); f[3] = byte_to_float<3>(x);
+  f[4] = byte_to_float<0>(y); f[5] = byte_to_float<1>(y); f[6] = byte_to_float<2>(y); f[7] = byte_to_float<3>(y);
+}
+__device__ __forceinline__ void nibbles_to_floats(uint32_t x, float (&f)[8]) {
+  const uint32_t ev = x & 0x0F0F0F0Fu, od = (x >> 4) & 0x0F0F0F0Fu;
+  f[0] = byte_to_float<0>(ev); f[2] = byte_to_float<1>(ev); f[4] = byte_to_float<2>(ev); f[6] = byte_to_float<3>(ev);
+  f[1] = byte_to_float<0>(od); f[3] = byte_to_float<1>(od); f[5] = byte_to_float<2>(od); f[7] = byte_to_float<3>(od);
+}
+
 // ---- device-side address helpers ------------------------------------------------
 __device__ __forceinline__ uint8_t* cache_half(const Geometry& g, int cache, int half) {
   return g.arena + (int64_t)cache * g.lay.cache_bytes + (int64_t)half * g.lay.half_bytes;
@@ -224,7 +247,7 @@ __device__ __forceinline__ uint8_t* cache_scratch(const Geometry& g, int cache) 
 }
 
 // ---- launchers (each enqueues on `st`, never synchronises) ----------------------
-void launch_attention(const KvxBatch& b, int max_tiles, hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+void launch_attention(const KvxBatch& b, hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 void launch_attention16(const KvxBatch& b, hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 void launch_combine(const KvxBatch& b, hipStream_t st);
 void launch_pool(const KvxBatch& b, int max_tc, hipStream_t st);

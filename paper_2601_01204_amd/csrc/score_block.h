@@ -1,5 +1,5 @@
 // Scoring of 64 cache positions by a workgroup (paper Sec. 3.2, Eq. 5-6 and the row mean of Eq. 6): the body of score_kernel and
-// of the scoring blocks that ride in a one-cache attention launch.  fp32, one rounding per operation, fixed order of additions
+// of the scoring blocks that ride in the attention launch of a small call.  fp32, one rounding per operation, fixed order of additions
 // (compiled without FMA contraction).
 #pragma once
 #include "kvx_dev.h"
@@ -33,37 +33,23 @@ __device__ __forceinline__ float pooled_mean(const Geometry& g, const Item& it, 
   return mean[lane];
 }
 
-// One row's codes as floats, channel by channel, through byte conversions (v_cvt_f32_ubyteN): 4-bit codes are
-// first spread into the bytes of two words per eight channels (even and odd channels), 2-bit codes into four.
-template <int K>
-__device__ __forceinline__ float byte_as_float(uint32_t w) {
-  float f;
-  if constexpr (K == 0) asm("v_cvt_f32_ubyte0 %0, %1" : "=v"(f) : "v"(w));
-  else if constexpr (K == 1) asm("v_cvt_f32_ubyte1 %0, %1" : "=v"(f) : "v"(w));
-  else if constexpr (K == 2) asm("v_cvt_f32_ubyte2 %0, %1" : "=v"(f) : "v"(w));
-  else asm("v_cvt_f32_ubyte3 %0, %1" : "=v"(f) : "v"(w));
-  return f;
-}
+// One row's codes as floats; 2-bit codes are spread into the bytes of four words.
 // f[0..7] = codes of channels 8 o .. 8 o + 7 of a row whose words are w
 template <int B>
 __device__ __forceinline__ void octet_as_floats(const uint32_t* w, int o, float (&f)[8]) {
   if constexpr (B == 8) {
-    const uint32_t x = w[2 * o], y = w[2 * o + 1];
-    f[0] = byte_as_float<0>(x); f[1] = byte_as_float<1>(x); f[2] = byte_as_float<2>(x); f[3] = byte_as_float<3>(x);
-    f[4] = byte_as_float<0>(y); f[5] = byte_as_float<1>(y); f[6] = byte_as_float<2>(y); f[7] = byte_as_float<3>(y);
+    bytes_to_floats(w[2 * o], w[2 * o + 1], f);
   } else if constexpr (B == 4) {
-    const uint32_t x = w[o], ev = x & 0x0F0F0F0Fu, od = (x >> 4) & 0x0F0F0F0Fu;
-    f[0] = byte_as_float<0>(ev); f[2] = byte_as_float<1>(ev); f[4] = byte_as_float<2>(ev); f[6] = byte_as_float<3>(ev);
-    f[1] = byte_as_float<0>(od); f[3] = byte_as_float<1>(od); f[5] = byte_as_float<2>(od); f[7] = byte_as_float<3>(od);
+    nibbles_to_floats(w[o], f);
   } else {
     const uint32_t x = (w[o >> 1] >> (16 * (o & 1))) & 0xFFFFu;          // eight 2-bit codes
     const uint32_t t = x | (x << 16);                                     // codes 0..3 in bits 0..7, codes 4..7 in bits 24..31
     const uint32_t lo = t & 0x03000003u, m1 = (t >> 2) & 0x03000003u, m2 = (t >> 4) & 0x03000003u, m3 = (t >> 6) & 0x03000003u;
     // byte 0 of each word holds code k, byte 3 holds code k + 4
-    f[0] = byte_as_float<0>(lo); f[4] = byte_as_float<3>(lo);
-    f[1] = byte_as_float<0>(m1); f[5] = byte_as_float<3>(m1);
-    f[2] = byte_as_float<0>(m2); f[6] = byte_as_float<3>(m2);
-    f[3] = byte_as_float<0>(m3); f[7] = byte_as_float<3>(m3);
+    f[0] = byte_to_float<0>(lo); f[4] = byte_to_float<3>(lo);
+    f[1] = byte_to_float<0>(m1); f[5] = byte_to_float<3>(m1);
+    f[2] = byte_to_float<0>(m2); f[6] = byte_to_float<3>(m2);
+    f[3] = byte_to_float<0>(m3); f[7] = byte_to_float<3>(m3);
   }
 }
 

@@ -7,7 +7,7 @@ static void noted(const Geometry& g) {
   stub_merge = g.merge;
   stub_score_selects = g.score_selects;
 }
-void launch_attention(const KvxBatch& b, int, hipStream_t, hipEvent_t, hipEvent_t) { noted(b.g); }
+void launch_attention(const KvxBatch& b, hipStream_t, hipEvent_t, hipEvent_t) { noted(b.g); }
 void launch_attention16(const KvxBatch& b, hipStream_t, hipEvent_t, hipEvent_t) { noted(b.g); }
 void launch_combine(const KvxBatch&, hipStream_t) {}
 void launch_pool(const KvxBatch&, int, hipStream_t) {}
