@@ -54,8 +54,8 @@ enum kv_meta_format {
                     /* log2 e)).  With 7 bits a * (code - z) is exact in half precision for 2- and 4-bit   */
                     /* codes, so Eq. 1 needs one matrix instruction per key tile instead of two.  Values   */
                     /* store s as a half inside [2^-14, 2048].  Zero-points are kept in [-1024, 1023].     */
-                    /* Needs k_bits of 2 or 4 and in_dtype KV_BF16; keys with |k * softmax_scale * log2 e| */
-                    /* >= 65504 are outside its domain.                                                    */
+                    /* Needs k_bits of 2 or 4 and in_dtype KV_BF16; queries and keys of 65504 and beyond,  */
+                    /* as given or (keys) times softmax_scale * log2 e, are outside its domain.            */
 };
 
 enum kv_order {
@@ -304,7 +304,8 @@ int kv_read_timing(kv_handle* h, float* total_ms, int32_t* launches);
  *                                 and reports them through kv_stats (nonfinite_flag); 0 (default)
  *   "overlap_update"              1 (default): a call on one or a few caches of bf16 inputs (of more
  *                                 than n_cus / 16 heads x query tiles) scores and selects
- *                                 inside the attention launch; otherwise, when attention alone cannot fill the
+ *                                 inside the attention launch where that finishes under attention or is
+ *                                 short by itself; otherwise, when attention alone cannot fill the
  *                                 chip (one or a few caches per call) and is long enough to repay the fork and
  *                                 join (about 40 us of host time a call), scoring, pruning and re-quantisation
  *                                 run on a second stream of the library next to attention,

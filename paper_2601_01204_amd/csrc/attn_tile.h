@@ -29,16 +29,18 @@
 // the source interleaves each matrix instruction (32 cycles) with two or three vector instructions that run under it.  Row sums
 // are matrix instructions too (below): v_dot2_f32_f16 shares the matrix core's operand path, and one of them per matrix
 // instruction costs 16 cycles (8 matrix instructions 258 cycles, with a dot product behind each 388, with 24 exponentials 266).
-// What bounds it: vector issue (48 exponentials of 8 cycles, 24 conversions, the staging's 75, about 9 cycles per matrix
-// instruction issued: some 2150 cycles per tile and SIMD with three blocks) and matrix work (1730, 2500 with key pairs) against
-// some 2800 measured, at a clock that power holds to 1.87 GHz (2.11 for the kernel before, which idled more).
+// What bounds it, in cycles per tile of a SIMD with three blocks (six units): vector issue (96 exponentials of 8, 48 conversions of
+// 4, the staging's 75 instructions of 4, 60 matrix instructions of about 9: 1800, addresses, checks and LDS operations on top) and
+// matrix work (1730, 2500 with key pairs) against some 2800 measured (3700 with key pairs), at a clock that power holds to 1.87 GHz
+// (2.11 for the kernel before, which idled more).
 // Against one block a wave, twelve waves, product - softmax - product one after the other and all waves staging, us a launch:
 // 24 caches of 16384 tokens, 1041 queries, 4-bit codes: 16-bit metadata 2030 -> 1783, fp32 2735 -> 2452; 48 caches of 24576,
 // 1374 queries, 2-bit keys 7718 -> 6690; four frames of 1041 on one cache of 8192 284 -> 250; one frame on it, fp32 metadata
 // 82.6 -> 74.4.  Staging by all eight waves, K first and V last, took 1885 where the four staging waves take 1783; without
 // their raised priority they take 1877.
 //
-// Domain: |k * softmax scale * log2 e| (16-bit metadata) and |v| below 65504 (the half range), finite inputs.
+// Domain: finite inputs, |v| below 65504 (the half range); 16-bit metadata: also |q|, |k| of the call's own tokens as they are, and
+// |k * softmax scale * log2 e| of those in the cache.  A query row outside it spoils its own output row only.
 #pragma once
 #include "score_select.h"
 

@@ -563,9 +563,13 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     // attention launch (its first workgroups), and the step is a handful of launches on the caller's stream.  us a step against
     // the rules above (second stream, or in order): 24 layers of 782 tokens at a budget of 2048, one call each, 58 -> 42 a
     // layer; 1041 tokens at 4096 63 -> 52, at 8192 93 -> 88; four frames of 1041 at 8192 263 -> 264; three caches of 8192
-    // 193 -> 177.  With fewer columns attention leaves most of the chip idle whatever the split, and with several caches that
-    // take three quarters of it in one round the second stream has the rest (six caches of 523 tokens at 4096: 116, inside
-    // 118): there the rules above stand.
+    // 193 -> 177.  With several caches that take three quarters of the chip in one round the second stream has the rest (six
+    // caches of 523 tokens at 4096: 116, inside 118): there the rules above stand.
+    // Where the lines lie is not where the two sides cross, both measured: with fewer columns long launches are the same either
+    // way (16 columns of 384 tokens at 16384 and more: within 1 %), and short ones would gain inside (16 heads of 300 tokens at
+    // 1024 44 us a step, inside 27; of 384 at 4096 52 and 46; 4 heads of 200 at 2048 37 and 26).  A small call that does not prune
+    // goes by the second stream's line for its rebuild alone, in order it would share the merge's launch (one layer of 1041
+    // tokens, frames 1 to 10: 55 us a frame, in order 49).
     const int side_blocks = side_blocks_of(b, max_tc, steps.step);
     const int64_t columns = (int64_t)cnt * g0.H * b.g.n_qtiles;
     const bool inside = may_overlap && h->overlap == 1 && any_prune && side_blocks > 0 && columns + side_blocks * cnt <= h->n_cus &&
