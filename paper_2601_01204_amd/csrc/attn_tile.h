@@ -20,9 +20,11 @@
 //     logit factor applied to the logits by the fused operation that subtracts the softmax reference.
 // P and V go through the f16 instruction in every format.
 //
-// Softmax.  p = 2^(s - m) without a prior maximum: cached logits leave the matrix core as s - m, because the first instruction
-// takes a block of 16 copies of -m as its accumulator.  f16 holds p up to 2^16; a key further above m makes p and the unit's
-// row sum infinite, and only then (rare, wave-uniform) is m raised, O and l rescaled and the probabilities formed again.
+// Softmax.  p = 2^(s - m) with m the largest logit of the range's first tile, without a prior maximum: cached logits leave the
+// matrix core as s - m, because the first instruction takes a block of 16 copies of -m as its accumulator.  f16 holds p up to 2^16;
+// a key further above m makes p and the unit's row sum infinite, and only then (rare, wave-uniform) is m raised, O and l rescaled
+// and the probabilities formed again.  (m from the first 32 keys instead: in a small cache one row in ten has its largest key,
+// whose p of 1 does not round, among the others; the error of 230 tokens at a budget of 1200 was 5 % higher.)
 //
 // Schedule.  The unit of work is 32 keys x one query block.  A step runs three units at once, the first product of one, the
 // softmax of the unit before and the second product of the one before that: nothing in it depends on anything else in it, and
@@ -237,7 +239,7 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
     f32x16 negm[NA];                         // 16 copies of -m, the accumulator input of a cached unit's first MFMA
     uint4 qf[NA][4];                         // query fragments (B operand of S^T = K Q^T): halves, octets permuted, or bf16
     float l[NA];                             // row sums
-    bool started[NA];                        // the block has computed a unit (the first one sets m)
+    bool started[NA];                        // the block has a reference (its first tile sets m)
     int row0[NA];
     // own keys a query may see (frame-wise causal mask, Sec. 3.1): the smallest and the largest number over the wave's rows
     int limit_lo = 1 << 30, limit_hi = 0;
@@ -317,16 +319,30 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
 #pragma unroll
       for (int e = 0; e < 8; ++e) w[e] = pack_f16(__builtin_amdgcn_exp2f(s[2 * e]), __builtin_amdgcn_exp2f(s[2 * e + 1]));
     };
-    // Raises m of the rows whose logits exceed it by more than the gap (on a block's first unit: sets it), rescales what has
-    // been accumulated and forms the unit's probabilities again.  Returns the raise.
-    auto raise = [&](int i, f32x16& s, uint32_t (&w)[8], bool first) __attribute__((always_inline)) {
+    // Sets m of a block: to the largest logit of its first tile (`a`: over this lane's keys, before the factor f).
+    auto set_reference = [&](int i, float a, float f) __attribute__((always_inline)) {
+      const float mq = max_halves(a);                              // both halves of a query agree
+      // rounded down, so that the largest key's fused logit below is not negative: near the top of fp32 the rounding error of m is
+      // more than the exponent's range, and that key would be lost (above the range it raises m)
+      float m0 = mq * f;
+      const uint32_t u = __float_as_uint(m0);
+      if (__builtin_fmaf(mq, f, -m0) < 0.f && (u << 1) != 0) m0 = __uint_as_float((int32_t)u < 0 ? u + 1 : u - 1);
+      // a query that sees none of the tile's keys (all masked) keeps zero
+      m0 = mq > -__builtin_inff() ? m0 : 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) negm[i][r] = -m0;
+      asm volatile("" : "+v"(negm[i]));     // opaque: the block stays in its registers
+      started[i] = true;
+    };
+    // Raises m of the rows whose logits exceed it by more than the gap, rescales what has been accumulated and forms the unit's
+    // probabilities again.  Returns the raise.
+    auto raise = [&](int i, f32x16& s, uint32_t (&w)[8]) __attribute__((always_inline)) {
       float a = s[0];
 #pragma unroll
       for (int r = 1; r < 16; ++r) a = fmaxf(a, s[r]);
-      const float mq = max_halves(a);                              // both halves of a query agree
-      // a query that sees none of the unit's keys (all masked) keeps its reference
-      const float delta = ((first && mq > 0.5f * kNegBig) || mq > kRescaleGap) ? mq : 0.f;
-      const float alpha = first ? 0.f : __builtin_amdgcn_exp2f(-delta);   // nothing accumulated before the first unit
+      const float mq = max_halves(a);
+      const float delta = mq > kRescaleGap ? mq : 0.f;
+      const float alpha = __builtin_amdgcn_exp2f(-delta);
       const float nm = negm[i][0] - delta;
       l[i] *= alpha;
 #pragma unroll
@@ -336,7 +352,7 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
         s[r] -= delta;
         negm[i][r] = nm;
       }
-      asm volatile("" : "+v"(negm[i]));     // opaque: the block stays in its registers
+      asm volatile("" : "+v"(negm[i]));
       probabilities(s, w);
       return delta;
     };
@@ -673,7 +689,7 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
       const uint64_t over = __ballot(!(unit_sum < kSumLimit)); KVX_PIN();
       pv(3); KVX_PIN();
       if (__builtin_expect(over != 0, 0)) {
-        const float delta = raise(bs, s_cur, w, false);
+        const float delta = raise(bs, s_cur, w);
         unit_sum = lane_sums(w);
         if constexpr (NB == 1 && !OWN) {
 #pragma unroll
@@ -694,24 +710,14 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         if (started[i]) continue;
-        // the block's first unit sets m: the largest logit of its 32 keys
-        const f32x16 s = logits(Int<P>{}, i, r0, 0);
-        float a = s[0];
+        float a = -__builtin_inff();
 #pragma unroll
-        for (int r = 1; r < 16; ++r) a = fmaxf(a, s[r]);
-        const float mq = max_halves(a);
-        float m0 = mq;
-        if constexpr (OWN) {
-          // rounded down, so that the largest key's fused logit below is not negative: near the top of fp32 the rounding error
-          // of m is more than the exponent's range, and that key would be lost (above the range it raises m)
-          m0 = mq * sc;
-          const uint32_t u = __float_as_uint(m0);
-          if (__builtin_fmaf(mq, sc, -m0) < 0.f && (u << 1) != 0) m0 = __uint_as_float((int32_t)u < 0 ? u + 1 : u - 1);
+        for (int kh = 0; kh < 2; ++kh) {
+          const f32x16 s = logits(Int<P>{}, i, r0, kh);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) a = fmaxf(a, s[r]);
         }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) negm[i][r] = -m0;
-        asm volatile("" : "+v"(negm[i]));
-        started[i] = true;
+        set_reference(i, a, OWN ? sc : 1.0f);
       }
       // the pipeline starts with units of no weight: infinitely far below any reference, also after a small logit factor
 #pragma unroll
@@ -749,7 +755,7 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
       probabilities(s_cur, w);
       float unit_sum = sums(w);
       if (__any(!(unit_sum < kSumLimit))) {
-        raise(bs, s_cur, w, false);
+        raise(bs, s_cur, w);
         unit_sum = lane_sums(w);
       }
       l[bs] += unit_sum;
@@ -772,26 +778,34 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
             for (int i = 0; i < 4; ++i) read_v(i >> 1, i & 1, r0, kh);
 #pragma unroll
             for (int i = 0; i < NB; ++i) {
-              f32x16 s;
-              if (kParts == 2 && !own) s = logits(Int<kParts>{}, i, r0, kh);
-              else s = logits(Int<1>{}, i, r0, kh);
+              auto product = [&](int x) __attribute__((always_inline)) {
+                return kParts == 2 && !own ? logits(Int<kParts>{}, i, r0, x) : logits(Int<1>{}, i, r0, x);
+              };
               const float f = own || FMT == kBf16 ? sc : 1.0f;         // cached keys in codes carry the logit factor
-              // keys this lane's query may see in the unit: valid rows of the cache's last tile, or own keys up to the end
+              // keys this lane's query may see in the tile: valid rows of the cache's last tile, or own keys up to the end
               // of the query's frame (also covers the ragged end of the call's rows)
               const int own_limit = n == g.n ? n : (min(row0[i] + l32, n - 1) / g.n + 1) * g.n;
-              const int valid = (own ? own_limit - (t - ntc) * kTileK : t_c - t * kTileK) - kh * 32;
+              const int valid = own ? own_limit - (t - ntc) * kTileK : t_c - t * kTileK;
+              const int lane_key = 4 * hf;                              // register r: key lane_key + 8 (r / 4) + r % 4 of a unit
+              if (!started[i]) {
+                float a = -__builtin_inff();
+#pragma unroll 1
+                for (int x = 0; x < 2; ++x) {
+                  const f32x16 s = product(x);
 #pragma unroll
-              for (int r = 0; r < 16; ++r) {
-                const int key = 8 * (r >> 2) + 4 * hf + (r & 3);
-                s[r] = key < valid ? __builtin_fmaf(s[r], f, negm[i][0]) : kNegBig;
+                  for (int r = 0; r < 16; ++r) a = lane_key + 8 * (r >> 2) + (r & 3) < valid - 32 * x ? fmaxf(a, s[r]) : a;
+                }
+                set_reference(i, a, f);
               }
+              f32x16 s = product(kh);
+#pragma unroll
+              for (int r = 0; r < 16; ++r) s[r] = lane_key + 8 * (r >> 2) + (r & 3) < valid - 32 * kh ? __builtin_fmaf(s[r], f, negm[i][0]) : kNegBig;
               uint32_t w[8];
               probabilities(s, w);
               float unit_sum = sums(w);
-              if (__any(!started[i] || !(unit_sum < kSumLimit))) {
-                raise(i, s, w, !started[i]);
+              if (__any(!(unit_sum < kSumLimit))) {
+                raise(i, s, w);
                 unit_sum = lane_sums(w);
-                started[i] = true;
               }
               l[i] += unit_sum;
 #pragma unroll

@@ -111,3 +111,33 @@ def test_a_bad_query_row_stays_alone(mode, n, frames, splits, bad):
         assert err <= 8 * 32 * 2.0 ** -24, f"frame {t}: rows beside a bad one differ by {err}"
     for h in hs:
         h.close()
+
+
+@pytest.mark.parametrize("mode", ["meta16", "meta32", "uncompressed"])
+@pytest.mark.parametrize("n,frames,splits", [(50, 1, 1), (50, 2, 1), (64, 2, 1), (150, 1, 1), (192, 3, 1), (192, 3, 4)])
+def test_the_order_of_a_tile_does_not_matter(mode, n, frames, splits):
+    """The softmax reference is the largest logit of a range's first 64 keys, so that the roundings of the probabilities do not
+    depend on their order within a tile of 64 (nor does a key group's quantisation): keys and values reversed inside every tile
+    give the same outputs but for the order of fp32 sums, 2^-24 sqrt(32 terms) of values below 8 in up to 24 of them (another
+    reference rounds every probability anew: 2^-12 each)."""
+    import paper_2601_01204_amd as kvx
+    import torch
+    H = 2
+    w = si.Workload("order", H, 64, n, 1, 16, 8 * n, frames, 1, 1, 4, 64, 4, 64, "bf16", 66)
+    extra = dict(mode=kvx.KV_UNCOMPRESSED_BF16, max_frames=frames) if mode == "uncompressed" else dict(meta_format=1 if mode == "meta16" else 0)
+    hs = [pu.make_handle(w, **extra) for _ in range(2)]
+    order = torch.cat([torch.arange(min(a + 64, n) - 1, a - 1, -1) for a in range(0, n, 64)]).to("cuda:0")
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(8)
+    for h in hs:
+        h.set_option("attention_splits", splits)
+    for t in range(frames):
+        q, k, v = (torch.randn((n, H, 64), generator=gen, device="cuda:0").to(torch.bfloat16) for _ in range(3))
+        outs = [torch.empty(q.shape, dtype=torch.float32, device="cuda:0") for _ in hs]
+        hs[0].step(q, k, v, outs[0])
+        hs[1].step(q, k[order].contiguous(), v[order].contiguous(), outs[1])
+        torch.cuda.synchronize()
+        err = (outs[1] - outs[0]).abs().max().item()
+        assert err <= 24 ** 0.5 * 32 ** 0.5 * 8 * 2.0 ** -24, f"frame {t}: {err}"
+    for h in hs:
+        h.close()
