@@ -323,10 +323,12 @@ __global__ __launch_bounds__(kThreads) void attn_tile_kernel(const KvxBatchT<N> 
     auto set_reference = [&](int i, float a, float f) __attribute__((always_inline)) {
       const float mq = max_halves(a);                              // both halves of a query agree
       // rounded down, so that the largest key's fused logit below is not negative: near the top of fp32 the rounding error of m is
-      // more than the exponent's range, and that key would be lost (above the range it raises m)
+      // more than the exponent's range, and that key would be lost (above the range it raises m).  A sum that starts from -m
+      // is rounded elsewhere than one from zero: the margin where that could be as much.
       float m0 = mq * f;
       const uint32_t u = __float_as_uint(m0);
       if (__builtin_fmaf(mq, f, -m0) < 0.f && (u << 1) != 0) m0 = __uint_as_float((int32_t)u < 0 ? u + 1 : u - 1);
+      if (FMT != kBf16 && fabsf(m0) >= 0x1p20f) m0 = __builtin_fmaf(fabsf(m0), -0x1p-16f, m0);
       // a query that sees none of the tile's keys (all masked) keeps zero
       m0 = mq > -__builtin_inff() ? m0 : 0.f;
 #pragma unroll

@@ -141,3 +141,37 @@ def test_the_order_of_a_tile_does_not_matter(mode, n, frames, splits):
         assert err <= 24 ** 0.5 * 32 ** 0.5 * 8 * 2.0 ** -24, f"frame {t}: {err}"
     for h in hs:
         h.close()
+
+
+@pytest.mark.parametrize("meta16", [True, False])
+@pytest.mark.parametrize("n,splits", [(40, 1), (192, 1), (192, 3)])
+def test_logits_far_beyond_the_exponent_range(n, splits, meta16):
+    """Logits of 1e9, in the frame's own tiles and in cached ones: a sum that starts from the reference is rounded elsewhere than
+    the reference was, by more than 2^-p covers.  Every row is one of its values (its largest key's, up to the few whose logits
+    fp32 cannot tell apart), never lost: finite and no further from zero than the largest value."""
+    import torch
+    H = 2
+    w = si.Workload("far", H, 64, n, 1, 16, 8 * n, 3, 1, 1, 4, 64, 4, 64, "bf16", 67)
+    h = pu.make_handle(w, meta_format=1 if meta16 else 0)
+    h.set_option("attention_splits", splits)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(9)
+    for t in range(3):
+        q, k, v = (torch.randn((n, H, 64), generator=gen, device="cuda:0") for _ in range(3))
+        q, k, v = (16384 * q).clamp(-60000, 60000).to(torch.bfloat16), (16384 * k).clamp(-60000, 60000).to(torch.bfloat16), v.to(torch.bfloat16)
+        out = torch.empty(q.shape, dtype=torch.float32, device="cuda:0")
+        h.step(q, k, v, out)
+        torch.cuda.synchronize()
+        assert torch.isfinite(out).all(), f"frame {t}"
+        assert out.abs().max().item() <= 1.25 * 6.0, f"frame {t}"       # values up to 6, their codes' error up to half a step of 12 / 15
+        if t == 0:
+            s = torch.einsum("qhd,khd->hqk", q.double().cpu(), k.double().cpu())
+            best = s.argmax(-1)
+            gap = s.topk(2, -1).values
+            clear = (gap[..., 0] - gap[..., 1]) * 0.18 > 2.0 ** -20 * s.abs().amax(-1) + 32
+            for hh in range(H):
+                want = v.double().cpu()[best[hh], hh]
+                err = (out.double().cpu()[:, hh] - want)[clear[hh]].abs().max().item()
+                assert err <= 8 * 2.0 ** -11, f"head {hh}: {err}"
+            assert clear.double().mean().item() > 0.9
+    h.close()
