@@ -160,12 +160,15 @@ inline bool mean_in_score(const KvxBatch& b, int max_tc) {
   return score_blocks(b, max_tc) * b.n_items <= b.g.n_cus && b.g.n_pooled * (b.g.n_new / b.g.n) <= kMeanRows;
 }
 
-// The last block of a short scoring launch selects, which saves a launch (4 us): 34.4 -> 32.6 us a step of 69 tokens at a budget
-// of 256, 33.6 -> 30.6 for two frames of 62 tokens at 421.  Every block has its scores written back for the one that selects, so
-// that many blocks lose: three caches of 5001 tokens (210 blocks) take 5 us more than with two launches.
-constexpr int kScoreSelectBlocks = 32;
+// The last block of a short scoring launch over several caches selects, which saves the issue of a launch with its 3.4 KB
+// argument.  us a step, update first, 69 tokens, 4 heads: two caches of 512 37 against 39 with two launches, four of 256 47 and 50,
+// eight of 256 70 and 72.  The device takes the longer: the block that selects waits for the others' scores to be written back and has
+// come last (17 us for the two against 6 and 10).  So not on one cache, whose step is bound by the device (69 tokens at 256 32.5 and
+// 30.8, 64 at 990 38.9 and 37.9), nor on two with more than a few blocks (128 tokens at 900, fp32, 26 blocks, 40.9 and 39.1), nor with
+// many: three caches of 5001 tokens (210 blocks) take 5 us more.
 inline bool selects_in_score(const KvxBatch& b, int max_tc) {
-  return mean_in_score(b, max_tc) && score_blocks(b, max_tc) * b.n_items <= kScoreSelectBlocks;
+  const int blocks = score_blocks(b, max_tc) * b.n_items;
+  return b.n_items > 1 && mean_in_score(b, max_tc) && blocks <= (b.n_items == 2 ? 16 : 32);
 }
 
 // Scoring workgroups per cache inside an attention launch (0: the launch cannot carry them: many caches, fp32 inputs, or scoring

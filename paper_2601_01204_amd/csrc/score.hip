@@ -140,9 +140,9 @@ void launch_pool(const KvxBatch& b, int max_tc, hipStream_t st) {
   if (!b.g.side_blocks && !mean_in_score(b, max_tc)) with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((pool_mean_kernel<KVX_ITEMS(bb)>), dim3(b.n_items), dim3(1024), 0, st, bb); });
 }
 
-// Scoring and selection together (selects_in_score).
-template <int B, int N>
-__global__ __launch_bounds__(kScoreWaves * 64) void score_select_kernel(const KvxBatchT<N> b) {
+// Scoring and selection together, on several caches (selects_in_score).
+template <int B>
+__global__ __launch_bounds__(kScoreWaves * 64) void score_select_kernel(const KvxBatch b) {
   const Geometry& g = b.g;
   const Item it = b.items[blockIdx.y];
   if (!it.prune) return;
@@ -156,7 +156,7 @@ template <int B>
 static void launch_score_t(const KvxBatch& b, int max_tc, hipStream_t st) {
   if (b.g.score_selects) {
     const size_t lds = score_select_lds_bytes(b.g.H, kScoreWaves, max_tc - b.g.n);
-    with_batch(b, [&](const auto& bb) { hipLaunchKernelGGL((score_select_kernel<B, KVX_ITEMS(bb)>), dim3(score_blocks(b, max_tc), b.n_items), dim3(kScoreWaves * 64), lds, st, bb); });
+    hipLaunchKernelGGL((score_select_kernel<B>), dim3(score_blocks(b, max_tc), b.n_items), dim3(kScoreWaves * 64), lds, st, b);
     return;
   }
   const int blocks = score_blocks(b, max_tc), waves = score_waves(b.g.H, B, blocks * b.n_items, b.g.n_cus);

@@ -294,10 +294,11 @@ void the_tested_calls_take_the_tested_launch() {
   }
 }
 
-// A scoring launch of up to 32 blocks selects; a rewrite in order of up to 32768 blocks takes the merge along.
+// A scoring launch of up to 16 blocks on two caches, or 32 on more, selects; a rewrite in order of up to 32768 blocks takes the
+// merge along.
 void shared_launches() {
   struct { int caches, H, n, L, selects, merge; } cases[] = {
-    {1, 4, 64, 2112, 1, 1}, {1, 4, 64, 2113, 0, 1}, {2, 4, 64, 1088, 1, 1}, {2, 4, 64, 1089, 0, 1},
+    {1, 4, 64, 256, 0, 1}, {2, 4, 64, 576, 1, 1}, {2, 4, 64, 577, 0, 1}, {4, 4, 64, 576, 1, 1}, {4, 4, 64, 577, 0, 1},
     {1, 64, 64, 21632, 0, 1}, {1, 64, 64, 22016, 0, 0},
   };
   for (const auto& x : cases) {
@@ -322,15 +323,15 @@ void second_stream_by_attention_alone() {
 
 // A timed call keeps the schedule of an untimed one but for the parts that are timed.
 void timing_parts_only_what_it_times() {
-  struct { int H, n, L, timed, side, merge, selects; } cases[] = {
-    {16, 1041, 8192, -1, 16, 1, 0},            {16, 1041, 8192, KV_K_ATTENTION, 16, 1, 0}, {16, 1041, 8192, KV_K_POOL, 16, 1, 0},
-    {16, 1041, 8192, KV_K_SCORE, 0, 1, 0},     {16, 1041, 8192, KV_K_SELECT, 0, 1, 0},     {16, 1041, 8192, KV_K_COMBINE, 16, 0, 0},
-    {16, 1041, 8192, KV_K_REBUILD_K, 16, 0, 0}, {16, 1041, 8192, KV_K_REBUILD_V, 16, 0, 0},
-    {4, 69, 256, -1, 0, 1, 1},                 {4, 69, 256, KV_K_ATTENTION, 0, 1, 1},      {4, 69, 256, KV_K_SCORE, 0, 1, 0},
-    {4, 69, 256, KV_K_SELECT, 0, 1, 0},        {4, 69, 256, KV_K_COMBINE, 0, 0, 1},
+  struct { int caches, H, n, L, timed, side, merge, selects; } cases[] = {
+    {1, 16, 1041, 8192, -1, 16, 1, 0},            {1, 16, 1041, 8192, KV_K_ATTENTION, 16, 1, 0}, {1, 16, 1041, 8192, KV_K_POOL, 16, 1, 0},
+    {1, 16, 1041, 8192, KV_K_SCORE, 0, 1, 0},     {1, 16, 1041, 8192, KV_K_SELECT, 0, 1, 0},     {1, 16, 1041, 8192, KV_K_COMBINE, 16, 0, 0},
+    {1, 16, 1041, 8192, KV_K_REBUILD_K, 16, 0, 0}, {1, 16, 1041, 8192, KV_K_REBUILD_V, 16, 0, 0},
+    {3, 4, 69, 256, -1, 0, 1, 1},                 {3, 4, 69, 256, KV_K_ATTENTION, 0, 1, 1},      {3, 4, 69, 256, KV_K_SCORE, 0, 1, 0},
+    {3, 4, 69, 256, KV_K_SELECT, 0, 1, 0},        {3, 4, 69, 256, KV_K_COMBINE, 0, 0, 1},
   };
   for (const auto& x : cases) {
-    Full f(1, x.H, x.n, x.L);
+    Full f(x.caches, x.H, x.n, x.L);
     CHECK(kv_set_timing(f.h, x.timed < 0 ? 0u : 1u << x.timed) == KV_OK);
     const int waits = stub_stream_waits;
     f.step();
