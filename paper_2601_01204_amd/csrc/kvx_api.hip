@@ -203,11 +203,12 @@ int validate(const kv_config* c) {
 
 // Attention's own estimate (tile steps, without the merge) from which the second stream pays; a tile step of fp32 inputs takes
 // the longer.
-constexpr double kOverlapSteps = 13.0, kOverlapStepsF32 = 11.0;
+constexpr double kOverlapSteps = 13.0, kOverlapStepsF32 = 11.5;
 
 // Key-range splits per (item, head, query tile) column.  A workgroup occupies a compute unit by itself, so a launch runs in
-// rounds of `target_wgs` workgroups; the estimate is rounds x (tiles per workgroup + kWorkgroupTiles) plus, with splits, the
-// partial results' way through memory, and the split count with the smallest estimate wins (fewer splits on ties).  In tiles
+// rounds of `target_wgs` workgroups; the estimate is rounds x (tiles of the longest range + kWorkgroupTiles) plus, with splits, the
+// partial results' way through memory, and the split count with the smallest estimate wins (fewer splits on ties).  (With a range
+// that is not whole tiles, 32 tiles went to 15 ranges, three tiles in the longest: 144 tokens, update first, 44.7 us, 16 ranges 43.6.)  In tiles
 // of about 1.5 us: the first loads and the store of a workgroup cost five, a row of 64 channels written and read again
 // 4e-5.  With three and a merge that cost one tile whatever its size the choice was worse for, us a step: three caches of 5001
 // tokens (12 heads, 523 queries) 6 ranges 108, 3 ranges 100; 1374 queries on one cache of 8192 7 ranges 93, 3 ranges 87; 24
@@ -230,7 +231,7 @@ int pick_splits(const kv_handle* h, const Geometry& g, int n_items, int min_tile
     s = 1;
     for (int c = 1; c <= cap; ++c) {
       const int64_t rounds = (base * c + target_wgs - 1) / target_wgs;
-      const double alone = (double)rounds * ((double)tiles / c + kWorkgroupTiles);
+      const double alone = (double)rounds * ((tiles + c - 1) / c + kWorkgroupTiles);
       const double cost = alone + (c > 1 ? 1.0 + kMergeTilesPerRow * c * (double)n_items * g.H * g.n_pad : 0.0);
       if (c == 1 || cost < best * 0.99) {
         best = cost;
@@ -399,7 +400,7 @@ int kv_init(const kv_config* cfg, kv_handle** out) {
   h->stream_n.assign((size_t)c.n_streams, c.tokens_per_frame);
   // Partial results of the key-range splits: room for the largest (caches per launch) x (splits) x (padded query rows) the
   // automatic choice reaches over calls of the handle's frame size: every number of frames and caches, every workgroup target (with
-  // and without the second stream, and what scoring blocks inside the launch leave), key counts in steps of two.  A call that
+  // and without the second stream, and what scoring blocks inside the launch leave), key counts in steps of 6 %.  A call that
   // would gain from more (streams of smaller frames, key counts in between) takes the best count that fits.
   int64_t rows_cap = 0;
   for (int f = 1; f <= h->f_max; ++f) {
@@ -407,7 +408,7 @@ int kv_init(const kv_config* cfg, kv_handle** out) {
     set_query_tiling(gf, f * g.n);
     const int tiles_max = (g.t_cap + kTileK - 1) / kTileK + (gf.n_new + kTileK - 1) / kTileK;
     for (int items = 1; items <= std::min<int64_t>(kMaxItems, n_caches); ++items)
-      for (int tiles = tiles_max; tiles >= 1; tiles = tiles > 1 ? (tiles + 1) / 2 : 0) {
+      for (int tiles = tiles_max; tiles >= 1; tiles -= std::max(1, tiles / 16)) {
         auto reach = [&](int target) {
           const int sp = pick_splits(h, gf, items, tiles, target, INT64_MAX);
           rows_cap = std::max(rows_cap, (int64_t)items * sp * gf.n_pad);
@@ -553,8 +554,8 @@ int step_impl(kv_handle* h, int32_t n_items, const kv_step_item* items, int32_t 
     // The fork and the join cost the host about 40 us a call (an event record and a wait each), so that a call with the
     // second stream issues in 60 us or more and one without in 20 to 27.  A short attention launch is not worth that, and its
     // merge, which shares the rebuild launch in order, does not count.  In order and beside, us a step of one cache, calls back to
-    // back (tile steps): bf16, 16 heads of 384 tokens at 3000 50 and 66 (8.8), at 4096 52 and 64 (9.7), at 6000 57 and 61 (11.3),
-    // at 8192 63 and 63 (13.4), at 24576 115 and 90 (30); fp32 inputs 59 and 65, 62 and 65, 70 and 66, 79 and 68, 150 and 125.
+    // back (tile steps): bf16, 16 heads of 384 tokens at 3000 50 and 66 (9), at 4096 52 and 64 (10), at 6000 57 and 61 (12),
+    // at 8192 63 and 63 (14), at 24576 115 and 90 (30); fp32 inputs 59 and 65, 62 and 65, 70 and 66, 79 and 68, 150 and 125. 
     // A launch lasts as long as its longest cache, so the estimate goes by that one: a stream that starts beside a full
     // cache of 16384 tokens (523 tokens a frame, 6 heads) takes 107 us a step in order and 82 beside.
     Estimate steps;

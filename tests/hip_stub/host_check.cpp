@@ -241,8 +241,8 @@ struct Full {
   kv_config c;
   std::vector<uint16_t> q;
   std::vector<kv_step_item> items;
-  Full(int caches, int H, int n, int L, int k_bits = 4, int frames = 1, int dtype = KV_BF16) : c(base_config(KV_META_F32, KV_LAYOUT_COMPACT, k_bits, 64, 4, 64)), items(caches) {
-    c.n_streams = caches; c.n_layers = 1; c.n_heads = H; c.tokens_per_frame = n; c.budget_tokens = L; c.max_frames_per_step = frames; c.in_dtype = dtype;
+  Full(int caches, int H, int n, int L, int k_bits = 4, int frames = 1, int dtype = KV_BF16, int order = KV_ATTEND_THEN_PRUNE) : c(base_config(KV_META_F32, KV_LAYOUT_COMPACT, k_bits, 64, 4, 64)), items(caches) {
+    c.n_streams = caches; c.n_layers = 1; c.n_heads = H; c.tokens_per_frame = n; c.budget_tokens = L; c.max_frames_per_step = frames; c.in_dtype = dtype; c.order = order;
     c.n_special = std::min(c.n_special, n);
     CHECK(kv_init(&c, &h) == KV_OK && h);
     q.resize((size_t)frames * n * H * 64 * (dtype == KV_F32 ? 2 : 1));
@@ -355,7 +355,7 @@ void split_counts_fit_the_buffers() {
     const int target = stub_stream_waits > waits ? 192 : 256 - stub_side_blocks * x.caches;
     const int blocks = (x.n + 31) / 32, qtiles = (blocks + 11) / 12, pad = qtiles * ((blocks + qtiles - 1) / qtiles) * 32, cols = x.caches * x.H * qtiles;
     const int tiles = (x.L + 63) / 64 + (x.n + 63) / 64;
-    auto cost = [&](int c) { return (cols * c + target - 1) / target * ((double)tiles / c + 5.0) + (c > 1 ? 1.0 + 4e-5 * c * x.caches * x.H * pad : 0.0); };
+    auto cost = [&](int c) { return (cols * c + target - 1) / target * ((tiles + c - 1) / c + 5.0) + (c > 1 ? 1.0 + 4e-5 * c * x.caches * x.H * pad : 0.0); };
     double best = cost(1);
     for (int c = 2; c <= std::min(16, std::max(4, 2 * target / cols)); ++c) best = std::min(best, cost(c));
     if (cost(stub_splits) > 1.05 * best) std::fprintf(stderr, "%d caches, %d heads, %d tokens, budget %d: %d splits\n", x.caches, x.H, x.n, x.L, stub_splits);
@@ -363,9 +363,21 @@ void split_counts_fit_the_buffers() {
   }
 }
 
+// A workgroup has whole tiles: 32 key tiles go to 16 ranges of two (not to 15, of which two have three) or to 11 of up to three, 19 to ten.
+void ranges_of_whole_tiles() {
+  struct { int n, L, splits; } cases[] = {{144, 2000, 16}, {300, 2000, 11}, {300, 1200, 10}};
+  for (const auto& x : cases) {
+    Full f(1, 16, x.n, x.L, 4, 1, KV_BF16, KV_PRUNE_THEN_ATTEND);
+    f.step();
+    if (stub_splits != x.splits) std::fprintf(stderr, "%d tokens, budget %d: %d splits\n", x.n, x.L, stub_splits);
+    CHECK(stub_splits == x.splits);
+  }
+}
+
 }  // namespace
 
 int main() {
+  ranges_of_whole_tiles();
   the_tested_calls_take_the_tested_launch();
   shared_launches();
   timing_parts_only_what_it_times();

@@ -39,7 +39,7 @@ def _same_export(a, b, what):
 @pytest.mark.parametrize("n_layers,heads,budget,frames", [(1, 16, 256, 8), (1, 2, 8192, 121), (24, 16, 256, 8)])
 def test_every_schedule_gives_the_same_bits(n_layers, heads, budget, frames, slots):
     import torch
-    # 8192 tokens of two heads in 16 key ranges: an estimate of 13.1 tile steps, above the 13 from which the second stream pays
+    # 8192 tokens of two heads in 16 key ranges: an estimate of 14 tile steps, above the 13 from which the second stream pays
     w = _w(n_layers=n_layers, n_heads=heads, budget_tokens=budget, frames=frames)
     # 24 caches x 16 heads x 1 query tile = 384 workgroup columns: more than the 256 compute units
     handles = []
