@@ -407,7 +407,7 @@ int kv_init(const kv_config* cfg, kv_handle** out) {
     Geometry gf = g;
     set_query_tiling(gf, f * g.n);
     const int tiles_max = (g.t_cap + kTileK - 1) / kTileK + (gf.n_new + kTileK - 1) / kTileK;
-    for (int items = 1; items <= std::min<int64_t>(kMaxItems, n_caches); ++items)
+    for (int items = 1; items <= (f == 1 ? std::min<int64_t>(kMaxItems, n_caches) : 1); ++items)      // (a chunk is one cache's)
       for (int tiles = tiles_max; tiles >= 1; tiles -= std::max(1, tiles / 16)) {
         auto reach = [&](int target) {
           const int sp = pick_splits(h, gf, items, tiles, target, INT64_MAX);
