@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("slots", [False, True])
 @pytest.mark.parametrize("heads,n,special,pool,budget,frames,k_bits,k_group,meta16", [
     (17, 3, 1, 2, 40, 20, 4, 64, True),          # one scoring block
-    (20, 60, 5, 16, 130, 6, 2, 32, True),        # two, most of them outside the middle
+    (20, 60, 5, 16, 130, 6, 2, 32, True),        # three, much of them outside the middle
     (64, 40, 0, 1, 200, 9, 4, 32, False),        # 64 heads
     (17, 129, 129, 16, 1100, 12, 8, 64, False),  # 129 pooled rows: two rounds of the row mean; 16 blocks
     (18, 130, 1, 1, 1230, 13, 4, 64, True),      # 130 pooled rows, 18 blocks shared by 16
